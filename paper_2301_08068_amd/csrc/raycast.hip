@@ -745,7 +745,7 @@ __global__ void __launch_bounds__(kBlock, 3) batch_kernel(BatchArgs B)
         }
     }
     if (threadIdx.x == 0) {
-        const uint32_t prev = __hip_atomic_fetch_add(B.work + 1, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t prev = __hip_atomic_fetch_add(B.work + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (prev == gridDim.x - 1) {
             __hip_atomic_store(B.work, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(B.work + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

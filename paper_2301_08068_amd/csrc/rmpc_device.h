@@ -96,6 +96,7 @@ struct Acc {
 // depend on timing.
 // ------------------------------------------------------------------------------------
 
+constexpr int kSumWords = 22;                 // 9 sums, 9 compensations, 4 counters
 constexpr int kRowWords = 23;                 // odd row stride: conflict-free column reads
 constexpr int kColLanes = 16;
 constexpr int kPairLanes = 9 * kColLanes;     // threads merging the compensated pairs
@@ -329,6 +330,13 @@ __device__ inline void resolve3(const double (&Sin)[3][3], const double (&b)[3],
     if (d2 / lmin_kept > 1e3) flags |= RMPC_Q_ILL;
 }
 
+// A store that the host can see as soon as it is acknowledged (wait_stores).
+template <typename T>
+__device__ __forceinline__ void store_system(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Turn a reduced accumulator into the public result (run by one thread).
 __device__ inline void finalize_result(const Acc &a, double rank_tol, int32_t n_rays,
                                        uint32_t extra_flags, rmpc_result *out)
@@ -346,35 +354,51 @@ __device__ inline void finalize_result(const Acc &a, double rank_tol, int32_t n_
     if (a.n_tie > 0) flags |= RMPC_Q_TIE;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        out->f[i] = f[i];
-        out->b[i] = b[i];
-        out->lambda[i] = lam[i];
+        store_system(&out->f[i], f[i]);
+        store_system(&out->b[i], b[i]);
+        store_system(&out->lambda[i], lam[i]);
 #pragma unroll
-        for (int j = 0; j < 3; ++j) out->A[3 * i + j] = S[i][j];
+        for (int j = 0; j < 3; ++j) store_system(&out->A[3 * i + j], S[i][j]);
     }
-    out->rank = rank;
-    out->n_hit = a.n_hit;
-    out->n_contrib = a.n_contrib;
-    out->n_tie = a.n_tie;
-    out->flags = flags;
-    out->n_rays = n_rays;
-    out->visits = a.visits;
+    store_system(&out->rank, rank);
+    store_system(&out->n_hit, a.n_hit);
+    store_system(&out->n_contrib, a.n_contrib);
+    store_system(&out->n_tie, a.n_tie);
+    store_system(&out->flags, flags);
+    store_system(&out->n_rays, n_rays);
+    store_system(&out->visits, (int64_t)a.visits);
 }
 
-// A row in partial layout (16-byte aligned: rows are 128 bytes apart) as six 16-byte loads.
-__device__ __forceinline__ void acc_from_partial(const float *p, Acc &a)
+// A row in partial layout, in LDS.
+__device__ __forceinline__ void acc_from_words(const float *w, Acc &a)
 {
-    const float4 *q4 = reinterpret_cast<const float4 *>(p);
-    float w[24];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        const float4 v = q4[k];
-        w[4 * k] = v.x; w[4 * k + 1] = v.y; w[4 * k + 2] = v.z; w[4 * k + 3] = v.w;
-    }
 #pragma unroll
     for (int k = 0; k < 9; ++k) { a.s[k] = w[k]; a.c[k] = w[9 + k]; }
     a.n_hit = __float_as_int(w[18]); a.n_contrib = __float_as_int(w[19]);
     a.n_tie = __float_as_int(w[20]); a.visits = __float_as_int(w[21]);
+}
+
+// A row that another block has written to device memory, past this XCD's L2 (8 bytes a load).
+__device__ __forceinline__ void acc_from_partial(const float *p, Acc &a)
+{
+    uint64_t *q = reinterpret_cast<uint64_t *>(const_cast<float *>(p));
+    float w[22];
+#pragma unroll
+    for (int k = 0; k < 11; ++k) {
+        const uint64_t v = __hip_atomic_load(q + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        w[2 * k] = __uint_as_float((uint32_t)v);
+        w[2 * k + 1] = __uint_as_float((uint32_t)(v >> 32));
+    }
+    acc_from_words(w, a);
+}
+
+// Waits until this wave's earlier stores have been acknowledged.  Stores and atomics of agent
+// (system) scope are acknowledged by the memory that all XCDs (and the host) share, so an atomic
+// issued after the wait is seen by nobody before them, without the write-back of the whole L2
+// that a release operation makes here.
+__device__ __forceinline__ void wait_stores()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // Where one reduction keeps its state: tile rows (one per tile), a ticket, the result slot,
@@ -394,6 +418,12 @@ struct FinishSlots {
 // merges all rows -- thread t takes rows t, t + 256, ... in that order, then the block tree
 // merges the threads -- so the result depends on the rows and their count only, never on the
 // order in which blocks finish.  It resolves, writes the result and publishes.
+//
+// Rows, tickets and results go past the L2 with agent- and system-scope accesses, ordered by
+// waiting for the stores before the ticket is taken.  With a release on every ticket and an
+// acquire in the last block, each block wrote its XCD's whole L2 back (and the last block
+// invalidated it) under the blocks still walking: a batch of 512 map queries (45,000 tiles) took
+// 2.88 ms instead of 2.23, a 65,536-point scan 12.3 us instead of 10.8.
 __device__ inline void grid_finish(const Acc &a, int b, int nb, const FinishSlots &F,
                                    double rank_tol, int32_t n_rays, uint32_t extra_flags, float *lds)
 {
@@ -401,22 +431,20 @@ __device__ inline void grid_finish(const Acc &a, int b, int nb, const FinishSlot
     __shared__ __align__(16) float tot[kPartialWords];
     block_reduce_store(a, lds, tot);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // one thread stores the block's row (the 22 words and 2 of padding) and takes the ticket
-        // with release order only: the release writes this XCD's L2 back so that the last
-        // block, on any XCD, reads the row; an acquire here would invalidate the L2 that the
-        // blocks still walking on this XCD read the map through
-        float4 *dst = reinterpret_cast<float4 *>(F.tile_rows + (size_t)b * kPartialWords);
-        const float4 *src = reinterpret_cast<const float4 *>(tot);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) dst[k] = src[k];
-        const uint32_t prev = __hip_atomic_fetch_add(F.tickets, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        last = prev == (uint32_t)(nb - 1);
+    if (threadIdx.x < kWave) {
+        // the first wave stores the block's row (one word per lane) and takes the ticket
+        const int t = opaque_tid();
+        if (t < kSumWords)
+            __hip_atomic_store(F.tile_rows + (size_t)b * kPartialWords + t, tot[t], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        wait_stores();
+        if (t == 0) {
+            const uint32_t prev = __hip_atomic_fetch_add(F.tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last = prev == (uint32_t)(nb - 1);
+        }
     }
     __syncthreads();
     if (!last) return;
-    // the last block acquires every block's row
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     Acc m;
     m.zero();
     for (int r0 = opaque_tid(); r0 < nb; r0 += 2 * kBlock) {
@@ -434,20 +462,23 @@ __device__ inline void grid_finish(const Acc &a, int b, int nb, const FinishSlot
     __syncthreads();
     if (threadIdx.x == 0) {
         Acc total;
-        acc_from_partial(tot, total);
+        acc_from_words(tot, total);
         __hip_atomic_store(F.tickets, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         finalize_result(total, rank_tol, n_rays, extra_flags, F.out);
         bool publish = true;
         if (F.finished) {
-            // system scope: every query's result reaches the host before the publication
-            const uint32_t prev = __hip_atomic_fetch_add(F.finished, 1u, __ATOMIC_ACQ_REL,
-                                                         __HIP_MEMORY_SCOPE_SYSTEM);
+            // every query's result has reached the host before the publication
+            wait_stores();
+            const uint32_t prev = __hip_atomic_fetch_add(F.finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             publish = prev == (uint32_t)(F.n_queries - 1);
             if (publish) __hip_atomic_store(F.finished, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // publish: the results are visible to the host before the sequence number (no word to
         // publish to: the result stays in device memory, ordered by the stream)
-        if (publish && F.done) __hip_atomic_store(F.done, F.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (publish && F.done) {
+            wait_stores();
+            __hip_atomic_store(F.done, F.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
 }
 
