@@ -88,8 +88,8 @@ typedef struct {
 
 /* Per-ray debug flags (rmpc_trace_debug). */
 #define RMPC_RAY_TIE 1u          /* two face crossings within 1e-5 voxel at a decision the
-                                    walk took (crossings inside 8^3 cells and 2^3 bricks it
-                                    skipped as free are not examined; every decision is exact
+                                    walk took (crossings inside the free boxes it crosses
+                                    whole are not examined; every decision is exact
                                     regardless) */
 #define RMPC_RAY_RANGE_TIE 2u    /* a face crossing within 1e-5 voxel of max_range */
 #define RMPC_RAY_START_FACE 4u   /* the start lies within 1e-5 voxel of a face */
@@ -108,8 +108,7 @@ typedef struct {
     uint32_t flags;             /* RMPC_Q_* */
     int32_t n_rays;             /* rays cast (or scan points read) */
     int64_t visits;             /* voxels the rays' walks entered, start voxel included (the
-                                   walk reads far fewer: it skips free 8^3 cells and 2^3
-                                   bricks whole) */
+                                   walk reads far fewer: it crosses free boxes whole) */
 } rmpc_result;
 
 /* Largest ray count per query (the Halton table length). */
@@ -139,9 +138,12 @@ rmpc_status rmpc_destroy(rmpc_ctx *ctx);
  *     voxels_on_device == 0, device memory of the context's GPU otherwise.  Only read during
  *     the call.
  *   map_id_out: receives an id >= 0.
- * The library keeps the grid as given (x-fastest) in the arena and adds one summary element
- * per whole 8 x 8 x 8 cell and one per whole 2 x 2 x 2 brick (occupied when any of its voxels
- * is), about 1/7 of the grid's size more.  Blocking.
+ * The library keeps in the arena a 16-bit entry per 2 x 2 x 2 brick (its voxels' occupancy, or
+ * the extents of a free box around it) and, for float maps, the grid as given (x-fastest);
+ * together as much as rmpc_map_footprint says, about 1/7 more than the grid.  While it runs it
+ * also uses about 1 byte of scratch per voxel: from the arena where there is room, else allocated
+ * on the device for the call; if that fails too, the boxes are single bricks (the same results,
+ * from slower walks).  Blocking.
  * Errors: RMPC_E_INVALID, RMPC_E_NOMEM (arena full), RMPC_E_HIP.
  */
 rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void *voxels,
@@ -194,8 +196,9 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
                                    int32_t *map_id_out);
 
 /*
- * rmpc_map_footprint -- arena bytes that rmpc_map_upload of this grid takes (the grid plus its
- * cell and brick summaries, before the arena's 256-byte rounding), for sizing an arena.  Makes
+ * rmpc_map_footprint -- arena bytes that rmpc_map_upload of this grid takes (room for the grid,
+ * one element per whole 8^3 cell and one per whole 2^3 brick, before the arena's 256-byte
+ * rounding and without the scratch of the upload itself), for sizing an arena.  Makes
  * no GPU call.  The same descriptor checks as rmpc_map_upload apply; in particular the grid
  * must hold fewer than 2^31 voxels (linear indices are int32).
  * Errors: RMPC_E_INVALID.
@@ -280,14 +283,15 @@ typedef struct {
 /* Launch configuration (rmpc_config_set, rmpc_tune_batch).  Hits, distances, visits and the
  * metric sums do not depend on lookahead, blocks_per_cu or use_graph; the segmentation
  * (lane_target_log2) changes only the summation order.  RMPC_RAY_TIE / n_tie may change with
- * the lookahead and the segmentation (they report near-ties at the decisions the walk takes). */
+ * the map's layout, the lookahead and the segmentation (they report near-ties at the decisions
+ * the walk takes). */
 #define RMPC_CONFIG_QUERY 0     /* rmpc_query and rmpc_trace_debug */
 #define RMPC_CONFIG_BATCH 1     /* rmpc_query_batch */
 #define RMPC_CONFIG_SPARSE 2    /* rmpc_query and rmpc_trace_debug on sparse maps (blocks_per_cu and
                                    use_graph unused) */
 typedef struct {
-    int32_t lookahead;          /* steps (voxels, free bricks or free cells) planned per
-                                   round: 4, 8 or 16 */
+    int32_t lookahead;          /* single queries on sparse maps: block steps planned per round; 4, 8
+                                   or 16 (walks on dense maps do not plan ahead) */
     int32_t lane_target_log2;   /* split rays into segments until a query has ~2^this lanes (10..22) */
     int32_t blocks_per_cu;      /* batches: resident blocks per CU of the persistent kernel (0 = max) */
     int32_t use_graph;          /* batches: 1 = replay the launch from a captured hipGraph */
@@ -317,8 +321,8 @@ rmpc_status rmpc_config_get(rmpc_ctx *ctx, int32_t which, rmpc_launch_config *cf
 
 /*
  * rmpc_tune_batch -- time rmpc_query_batch on this batch for a grid of configurations
- * (lookahead, segmentation target, resident blocks) and keep the fastest as the context's
- * RMPC_CONFIG_BATCH (use_graph is kept as set).
+ * (segmentation target, resident blocks) and keep the fastest as the context's
+ * RMPC_CONFIG_BATCH (lookahead and use_graph are kept as set).
  *   cache_path: optional JSON file; a configuration cached there under this GPU's
  *     architecture, the batch's storage types and its mean ray count bucket is used without
  *     timing, and a newly timed one is added.  NULL: no file.

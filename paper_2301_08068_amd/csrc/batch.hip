@@ -166,7 +166,7 @@ rmpc::BatchArgs slot_args(LaunchSlot &slot)
 
 int graph_blocks(rmpc_ctx *ctx, const rmpc_launch_config &cfg)
 {
-    const int per_cu = cfg.blocks_per_cu > 0 ? cfg.blocks_per_cu : rmpc::batch_blocks_per_cu(cfg.lookahead);
+    const int per_cu = cfg.blocks_per_cu > 0 ? cfg.blocks_per_cu : rmpc::batch_blocks_per_cu();
     return per_cu * ctx->cu_count;
 }
 
@@ -175,14 +175,14 @@ int graph_blocks(rmpc_ctx *ctx, const rmpc_launch_config &cfg)
 rmpc_status slot_graph(rmpc_ctx *ctx, LaunchSlot &slot, const rmpc_launch_config &cfg)
 {
     const int gblocks = graph_blocks(ctx, cfg);
-    if (slot.graph && slot.graph_blocks == gblocks && slot.graph_lookahead == cfg.lookahead) return RMPC_OK;
+    if (slot.graph && slot.graph_blocks == gblocks) return RMPC_OK;
     // the grid is fixed (resident blocks) and the per-batch data sit in device memory, so one
     // captured launch serves every batch of this slot
     if (slot.graph) { RMPC_HIP(hipGraphExecDestroy(slot.graph)); slot.graph = nullptr; }
     hipStream_t s = slot.stream;
     hipGraph_t g;
     RMPC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    const hipError_t le = rmpc::launch_batch(slot_args(slot), gblocks, cfg.lookahead, s);
+    const hipError_t le = rmpc::launch_batch(slot_args(slot), gblocks, s);
     const hipError_t ce = hipStreamEndCapture(s, &g);
     if (le != hipSuccess) return fail(RMPC_E_HIP, std::string("batch capture: ") + hipGetErrorString(le));
     if (ce != hipSuccess) return fail(RMPC_E_HIP, std::string("batch capture: ") + hipGetErrorString(ce));
@@ -190,7 +190,6 @@ rmpc_status slot_graph(rmpc_ctx *ctx, LaunchSlot &slot, const rmpc_launch_config
     (void)hipGraphDestroy(g);
     if (ie != hipSuccess) return fail(RMPC_E_HIP, std::string("graph instantiate: ") + hipGetErrorString(ie));
     slot.graph_blocks = gblocks;
-    slot.graph_lookahead = cfg.lookahead;
     return RMPC_OK;
 }
 
@@ -214,7 +213,7 @@ rmpc_status slot_launch(rmpc_ctx *ctx, LaunchSlot &slot, int nq, int n_tiles,
     if (cfg.use_graph) {
         RMPC_HIP(hipGraphLaunch(slot.graph, s));
     } else {
-        RMPC_HIP(rmpc::launch_batch(B, blocks, cfg.lookahead, s));
+        RMPC_HIP(rmpc::launch_batch(B, blocks, s));
     }
     *seq_out = seq;
     return RMPC_OK;
@@ -387,21 +386,22 @@ rmpc_status rmpc_tune_batch(rmpc_ctx *ctx, const rmpc_query_desc *q, int32_t n,
     if (!cache_lookup(cache_path, key, &chosen)) {
         std::vector<rmpc_result> res((size_t)n);
         double best_ms = 1e30;
-        const int max_per_cu = std::max(1, rmpc::batch_blocks_per_cu(8));
-        for (int la : {4, 8, 16})
-            for (int lt : {12, 14, 16, 18})
-                for (int bpc : {0, std::max(1, max_per_cu / 2)}) {
-                    rmpc_launch_config c{la, lt, bpc, 0};
+        const int max_per_cu = std::max(1, rmpc::batch_blocks_per_cu());
+        // (the batch kernel does not depend on the lookahead: it stays as set)
+        const int la = ctx->cfg[RMPC_CONFIG_BATCH].lookahead;
+        for (int lt : {12, 14, 16, 18})
+            for (int bpc : {0, std::max(1, max_per_cu / 2)}) {
+                rmpc_launch_config c{la, lt, bpc, 0};
+                if (rmpc_status st = run_batch(ctx, q, n, map_params, scan_params, user, c, res.data()))
+                    return st;                                   // warm-up (and validation)
+                const auto t0 = std::chrono::steady_clock::now();
+                for (int r = 0; r < 3; ++r)
                     if (rmpc_status st = run_batch(ctx, q, n, map_params, scan_params, user, c, res.data()))
-                        return st;                                   // warm-up (and validation)
-                    const auto t0 = std::chrono::steady_clock::now();
-                    for (int r = 0; r < 3; ++r)
-                        if (rmpc_status st = run_batch(ctx, q, n, map_params, scan_params, user, c, res.data()))
-                            return st;
-                    const double ms = std::chrono::duration<double, std::milli>(
-                                          std::chrono::steady_clock::now() - t0).count() / 3.0;
-                    if (ms < best_ms) { best_ms = ms; chosen = c; }
-                }
+                        return st;
+                const double ms = std::chrono::duration<double, std::milli>(
+                                      std::chrono::steady_clock::now() - t0).count() / 3.0;
+                if (ms < best_ms) { best_ms = ms; chosen = c; }
+            }
         cache_store(cache_path, key, chosen);
     }
     chosen.use_graph = ctx->cfg[RMPC_CONFIG_BATCH].use_graph;

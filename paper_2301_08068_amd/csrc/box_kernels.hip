@@ -1,0 +1,583 @@
+// box_kernels.hip -- the box entries of an uploaded map (rmpc_dense.h): per brick of 2 x 2 x 2
+// voxels a box of free bricks around it, or its occupancy and its widest free voxel layer.
+//
+// The extents come from Chebyshev distances between bricks, taken on bit sets (one bit per brick,
+// rows along x in 64-bit words), where a dilation step costs a few instructions per 64 bricks:
+//   layers  the square dilations by 1 .. 6 bricks, within the layers of bricks perpendicular to
+//           each axis, of the bricks' six voxel layers.  Counting the steps that do not reach a
+//           brick (in bit-sliced counters) gives its free layers' extents (1 .. 7); the union of
+//           an axis' two sides gives the extents of a slab one brick thick
+//   cube    the cubic dilations by 1 .. 6: the half extent d of the free cube around a brick
+//   slab    close to a surface (d <= kBoxThin) the slab of half thickness d, perpendicular to the
+//           axis that allows the widest one, takes the cube's place, so that rays that graze floors
+//           and walls cross long runs of free space too
+//   far     where the cubes of the 27 bricks 3 (6) away are free as well, half extent 10 (13)
+// (modelled on the paper-shaped map, the slowest of 64 neighbouring rays takes 24 boxes next to the
+// floor with cubes of up to 255 bricks alone, 10 with these; elsewhere 17-22 and 11-16).
+//
+// Bound by the copy: the grid is read once and written once (float32 and float16 maps).  A 400^3
+// float32 grid: 85 us for the copy (6.0 TB/s) with the occupancy, 13 us for the layer sets, 26 and 30
+// for the dilations, 21 for the choice, 43 to write the entries; a copy and one thread per 8^3 cell
+// and per 2^3 brick took 91 + 147 + 65 us.
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "rmpc_device.h"
+#include "rmpc_kernels.h"
+
+namespace rmpc {
+
+namespace {
+
+constexpr int kBoxThin = 3;
+constexpr int kSteps = 6;                         // dilation steps; extents 1 .. kSteps + 1 come from them
+constexpr uint32_t kUnitBox = box_extents(1, 1, 1);
+
+// Scratch: the occupancy of every brick's voxels (a byte, rows padded to whole words), then bit
+// sets of `words` 64-bit words each.
+struct Scratch {
+    uint8_t *mask;                                // 0: free
+    uint64_t *layer;                              // 6: voxel layers x low, x high, y low, ... z high
+    uint64_t *cz, *cy, *cx;                       // kSteps each: dilated slabs, perpendicular to the axis
+    uint64_t *yx;                                 // 2 kSteps: the x layers dilated along y
+    uint64_t *best;                               // 6: extent (3 bits), side and axis (2 bits) of the best layer
+    uint64_t *cube;                               // 3: bits of d
+    uint64_t *full;                               // 1: d = kSteps + 1
+    int64_t words;
+    int32_t pitch, w;                             // bytes, words of a row
+};
+constexpr int kSets = 6 + 3 * kSteps + 2 * kSteps + 6 + 3 + 1;
+
+__host__ __device__ inline int32_t row_words(const MapView &m) { return (m.nbx + 63) >> 6; }
+__host__ __device__ inline int64_t set_words(const MapView &m) { return (int64_t)row_words(m) * m.nby * m.nbz; }
+__host__ __device__ inline int64_t mask_bytes(const MapView &m)
+{
+    return ((int64_t)((m.nbx + 3) & ~3) * m.nby * m.nbz + 255) / 256 * 256;
+}
+
+Scratch scratch_at(const MapView &m, uint8_t *p)
+{
+    Scratch s;
+    s.mask = p;
+    s.words = set_words(m);
+    s.pitch = (m.nbx + 3) & ~3;
+    s.w = row_words(m);
+    s.layer = reinterpret_cast<uint64_t *>(p + mask_bytes(m));
+    s.cz = s.layer + 6 * s.words;
+    s.cy = s.cz + kSteps * s.words;
+    s.cx = s.cy + kSteps * s.words;
+    s.yx = s.cx + kSteps * s.words;
+    s.best = s.yx + 2 * kSteps * s.words;
+    s.cube = s.best + 6 * s.words;
+    s.full = s.cube + 3 * s.words;
+    return s;
+}
+
+__device__ __forceinline__ uint16_t unit_entry(uint32_t mask)
+{
+    return (uint16_t)(mask ? kBoxOccupied | kBoxNoLayer | mask : kUnitBox);
+}
+
+// Occupancy of every brick, copying the voxels to dst (null: no copy; every voxel of the grid is
+// copied, those outside the bricks of a partial map by copy_rest_kernel).  A thread takes W
+// consecutive bricks of a row: with W = 2 each of its four voxel rows is one load of four
+// elements (rows of a multiple of four elements, aligned), with W = 1 any grid.
+// unit: write entries of single-brick boxes instead of the mask plane.
+template <int DT, int W, bool UNIT>
+__global__ void __launch_bounds__(256) brick_kernel(MapView m, const typename Voxel<DT>::T *src,
+                                                    typename Voxel<DT>::T *dst, uint8_t *mask, int32_t pitch,
+                                                    uint16_t *box)
+{
+    using T = typename Voxel<DT>::T;
+    const uint32_t nw = ((uint32_t)m.nbx + W - 1) / W;
+    const uint64_t id = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (id >= (uint64_t)nw * m.nby * m.nbz) return;
+    const uint32_t row = (uint32_t)(id / nw), bx = (uint32_t)(id - (uint64_t)row * nw) * W;
+    const uint32_t bz = row / (uint32_t)m.nby, by = row - bz * (uint32_t)m.nby;
+    uint32_t occ[W] = {};
+    if constexpr (W == 2) {
+        struct alignas(4 * sizeof(T)) Quad { T v[4]; };
+        Quad q[4];
+        bool in[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t y = 2 * by + (k & 1), z = 2 * bz + (k >> 1);
+            in[k] = y < (uint32_t)m.ny && z < (uint32_t)m.nz;
+            const uint64_t at = 2 * bx + (uint64_t)m.nx * (in[k] ? y + (uint64_t)m.ny * z : 0u);
+            q[k] = *reinterpret_cast<const Quad *>(src + at);
+            if (dst && in[k]) *reinterpret_cast<Quad *>(dst + at) = q[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (in[k] && Voxel<DT>::occ(q[k].v[i])) occ[i >> 1] |= 1u << ((i & 1) + 2 * k);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t x = 2 * bx + (k & 1), y = 2 * by + ((k >> 1) & 1), z = 2 * bz + (k >> 2);
+            if (x >= (uint32_t)m.nx || y >= (uint32_t)m.ny || z >= (uint32_t)m.nz) continue;
+            const uint64_t at = x + (uint64_t)m.nx * (y + (uint64_t)m.ny * z);
+            const T v = src[at];
+            if (dst) dst[at] = v;
+            if (Voxel<DT>::occ(v)) occ[0] |= 1u << k;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        if (bx + i >= (uint32_t)m.nbx) break;
+        if constexpr (UNIT) box[(uint64_t)row * m.nbx + bx + i] = unit_entry(occ[i]);
+        else mask[(uint64_t)row * pitch + bx + i] = (uint8_t)occ[i];
+    }
+}
+
+// The voxels of a partial map that lie outside its bricks.
+template <int DT>
+__global__ void __launch_bounds__(256) copy_rest_kernel(MapView m, const typename Voxel<DT>::T *src,
+                                                        typename Voxel<DT>::T *dst)
+{
+    const uint64_t row = blockIdx.x;                      // y + ny z
+    const uint32_t z = (uint32_t)(row / (uint32_t)m.ny), y = (uint32_t)(row - (uint64_t)z * m.ny);
+    const bool whole = y >= 2u * m.nby || z >= 2u * m.nbz;
+    for (uint32_t x = (whole ? 0u : 2u * m.nbx) + threadIdx.x; x < (uint32_t)m.nx; x += 256) {
+        const uint64_t at = x + (uint64_t)m.nx * row;
+        dst[at] = src[at];
+    }
+}
+
+// The layer sets from the masks: a lane takes four bricks of a row, eight lanes join their bits to
+// 32-bit words.  Bricks past the row's end are free, or occupied on a partial axis (bricks there
+// have no entries, so a box must not cover them).
+__global__ void __launch_bounds__(256) layer_bits_kernel(MapView m, Scratch s)
+{
+    const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;        // four bricks
+    const int64_t row = id / (16 * s.w);
+    const int x = (int)(id - row * 16 * s.w) * 4;
+    const bool in = row < (int64_t)m.nby * m.nbz;
+    uint32_t v = 2 * m.nbx < m.nx ? ~0u : 0u;
+    if (in && x < m.nbx) {
+        const uint32_t last = m.nbx - x;                               // bricks of the row from here
+        const uint32_t past = last < 4 ? ~0u << (8 * last) : 0u;
+        v = (*reinterpret_cast<const uint32_t *>(s.mask + row * s.pitch + x) & ~past) | (v & past);
+    }
+    const uint32_t sel[6] = {0x55u, 0xaau, 0x33u, 0xccu, 0x0fu, 0xf0u};
+    const int shift = 4 * (threadIdx.x & 7);
+    uint32_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const uint32_t t = v & (sel[k] * 0x01010101u);
+        // the top bit of every non-zero byte, gathered into four bits
+        const uint32_t top = (((t & 0x7f7f7f7fu) + 0x7f7f7f7fu) | t) & 0x80808080u;
+        uint32_t b = ((((top >> 7) * 0x01020408u) >> 24) & 15u) << shift;
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) b |= __shfl_xor(b, o, 8);
+        mine = (threadIdx.x & 7) == k ? b : mine;
+    }
+    if (in && (threadIdx.x & 7) < 6)
+        reinterpret_cast<uint32_t *>(s.layer + (threadIdx.x & 7) * s.words)[id >> 3] = mine;
+}
+
+// One word of a set, its row and its place: rows along y are w words apart, along z w nby.
+struct Place {
+    int64_t at, sy, sz;
+    int wi, w, y, ny, z, nz;
+    bool wall_x, wall_y, wall_z, ok;
+};
+
+__device__ __forceinline__ Place place_of(const MapView &m, const Scratch &s, int64_t id)
+{
+    Place p;
+    p.ok = id < s.words;
+    p.at = p.ok ? id : 0;
+    p.w = s.w;
+    const int64_t row = p.at / s.w;
+    p.wi = (int)(p.at - row * s.w);
+    p.z = (int)(row / m.nby);
+    p.y = (int)(row - (int64_t)p.z * m.nby);
+    p.ny = m.nby;
+    p.nz = m.nbz;
+    p.sy = s.w;
+    p.sz = (int64_t)s.w * m.nby;
+    p.wall_x = 2 * m.nbx < m.nx;
+    p.wall_y = 2 * m.nby < m.ny;
+    p.wall_z = 2 * m.nbz < m.nz;
+    return p;
+}
+
+__device__ __forceinline__ uint64_t word_at(const uint64_t *set, int64_t at, int i, int n, bool wall)
+{
+    return (unsigned)i < (unsigned)n ? set[at] : (i >= n && wall ? ~0ull : 0ull);
+}
+
+// The word j rows away along y or z (out of the grid: free, or occupied past a partial axis).
+__device__ __forceinline__ uint64_t word_y(const uint64_t *set, const Place &p, int j)
+{
+    return word_at(set, p.at + j * p.sy, p.y + j, p.ny, p.wall_y);
+}
+__device__ __forceinline__ uint64_t word_z(const uint64_t *set, const Place &p, int j)
+{
+    return word_at(set, p.at + j * p.sz, p.z + j, p.nz, p.wall_z);
+}
+
+// A word with the 32 bits before and after it in its row, lowest first.
+struct Window {
+    uint32_t w[4];
+};
+
+__device__ __forceinline__ Window window_at(const uint64_t *set, const Place &p, int64_t at, bool in, bool ones)
+{
+    if (!in) {
+        const uint32_t v = ones ? ~0u : 0u;
+        return Window{{v, v, v, v}};
+    }
+    const uint64_t c = set[at];
+    const uint32_t before = p.wi > 0 ? (uint32_t)(set[at - 1] >> 32) : 0u;
+    const uint32_t after = p.wi + 1 < p.w ? (uint32_t)set[at + 1] : (p.wall_x ? ~0u : 0u);
+    return Window{{before, (uint32_t)c, (uint32_t)(c >> 32), after}};
+}
+
+__device__ __forceinline__ Window window_row(const uint64_t *set, const Place &p, bool along_z, int j)
+{
+    const int i = (along_z ? p.z : p.y) + j, n = along_z ? p.nz : p.ny;
+    return window_at(set, p, p.at + j * (along_z ? p.sz : p.sy), (unsigned)i < (unsigned)n,
+                     i >= n && (along_z ? p.wall_z : p.wall_y));
+}
+
+__device__ __forceinline__ void join(Window &a, const Window &b)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a.w[i] |= b.w[i];
+}
+
+// The window's word dilated by K along x: bits joined with those up to K above and below, by
+// shifts that double the reach.
+template <int K>
+__device__ __forceinline__ uint64_t smear(const Window &v)
+{
+    uint32_t r1 = v.w[1], r2 = v.w[2], r3 = v.w[3], l0 = v.w[0], l1 = v.w[1], l2 = v.w[2];
+    auto step = [&](int n) {
+        r1 |= __builtin_amdgcn_alignbit(r2, r1, n);
+        r2 |= __builtin_amdgcn_alignbit(r3, r2, n);
+        r3 |= r3 >> n;
+        l2 |= __builtin_amdgcn_alignbit(l2, l1, 32 - n);
+        l1 |= __builtin_amdgcn_alignbit(l1, l0, 32 - n);
+        l0 |= l0 << n;
+    };
+    step(1);
+    if constexpr (K == 2) step(1);
+    if constexpr (K >= 3) step(2);
+    if constexpr (K > 3) step(K - 3);
+    return (uint64_t)(r1 | l1) | ((uint64_t)(r2 | l2) << 32);
+}
+
+// 64 counters of three bits.
+struct Count {
+    uint64_t b0, b1, b2;
+    __device__ __forceinline__ void add(uint64_t x)
+    {
+        const uint64_t c = b0 & x, d = b1 & c;
+        b0 ^= x;
+        b1 ^= c;
+        b2 ^= d;
+    }
+};
+
+__device__ __forceinline__ uint64_t above(const Count &a, const Count &b)
+{
+    const uint64_t e2 = ~(a.b2 ^ b.b2), e1 = ~(a.b1 ^ b.b1);
+    return (a.b2 & ~b.b2) | (e2 & ((a.b1 & ~b.b1) | (e1 & a.b0 & ~b.b0)));
+}
+__device__ __forceinline__ uint64_t pick(uint64_t m, uint64_t a, uint64_t b) { return (m & a) | (~m & b); }
+__device__ __forceinline__ Count pick(uint64_t m, const Count &a, const Count &b)
+{
+    return Count{pick(m, a.b0, b.b0), pick(m, a.b1, b.b1), pick(m, a.b2, b.b2)};
+}
+
+// The widest free layer so far: its extent, its side and its axis (x 0, y 1, z 2; 3 with side 1:
+// none).
+struct Best {
+    Count q;
+    uint64_t side, a0, a1;
+    __device__ __forceinline__ void offer(const Count &c, bool high, int axis)
+    {
+        const uint64_t m = above(c, q);
+        q = pick(m, c, q);
+        side = pick(m, high ? ~0ull : 0ull, side);
+        a0 = pick(m, axis & 1 ? ~0ull : 0ull, a0);
+        a1 = pick(m, axis & 2 ? ~0ull : 0ull, a1);
+    }
+};
+
+// One step of the dilations of an axis' two voxel layers within the planes along x and the rows
+// (y or z): ta, tb hold the layers' rows up to K away.
+template <int K>
+__device__ __forceinline__ void plane_step(const uint64_t *a, const uint64_t *b, const Place &p, bool along_z, Window &ta,
+                                           Window &tb, Count &qa, Count &qb, uint64_t *out)
+{
+    join(ta, window_row(a, p, along_z, -K));
+    join(ta, window_row(a, p, along_z, K));
+    join(tb, window_row(b, p, along_z, -K));
+    join(tb, window_row(b, p, along_z, K));
+    const uint64_t ca = smear<K>(ta), cb = smear<K>(tb);
+    qa.add(~ca);
+    qb.add(~cb);
+    out[p.at] = ca | cb;
+}
+
+__device__ __forceinline__ void plane(const Scratch &s, const Place &p, int axis, uint64_t *out, Best &best)
+{
+    const bool along_z = axis == 1;
+    const uint64_t *a = s.layer + 2 * axis * s.words, *b = a + s.words;
+    Window ta = window_row(a, p, along_z, 0), tb = window_row(b, p, along_z, 0);
+    Count qa{~a[p.at], 0, 0}, qb{~b[p.at], 0, 0};
+    plane_step<1>(a, b, p, along_z, ta, tb, qa, qb, out);
+    plane_step<2>(a, b, p, along_z, ta, tb, qa, qb, out + s.words);
+    plane_step<3>(a, b, p, along_z, ta, tb, qa, qb, out + 2 * s.words);
+    plane_step<4>(a, b, p, along_z, ta, tb, qa, qb, out + 3 * s.words);
+    plane_step<5>(a, b, p, along_z, ta, tb, qa, qb, out + 4 * s.words);
+    plane_step<6>(a, b, p, along_z, ta, tb, qa, qb, out + 5 * s.words);
+    best.offer(qa, false, axis);
+    best.offer(qb, true, axis);
+}
+
+// Layers perpendicular to y and z, and the first half (along y) of those perpendicular to x.
+__global__ void __launch_bounds__(256) planes_kernel(MapView m, Scratch s)
+{
+    const Place p = place_of(m, s, (int64_t)blockIdx.x * 256 + threadIdx.x);
+    if (!p.ok) return;
+    Best best{Count{0, 0, 0}, ~0ull, ~0ull, ~0ull};
+    plane(s, p, 2, s.cz, best);
+    plane(s, p, 1, s.cy, best);
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+        const uint64_t *set = s.layer + side * s.words;
+        uint64_t t = set[p.at];
+#pragma unroll
+        for (int k = 1; k <= kSteps; ++k) {
+            t |= word_y(set, p, -k) | word_y(set, p, k);
+            s.yx[(side * kSteps + k - 1) * s.words + p.at] = t;
+        }
+    }
+    uint64_t *o = s.best + p.at;
+    o[0] = best.q.b0; o[s.words] = best.q.b1; o[2 * s.words] = best.q.b2;
+    o[3 * s.words] = best.side; o[4 * s.words] = best.a0; o[5 * s.words] = best.a1;
+}
+
+// Layers perpendicular to x (the second half, along z), and the cubes.
+__global__ void __launch_bounds__(256) cubes_kernel(MapView m, Scratch s)
+{
+    const Place p = place_of(m, s, (int64_t)blockIdx.x * 256 + threadIdx.x);
+    if (!p.ok) return;
+    uint64_t *o = s.best + p.at;
+    Best best{Count{o[0], o[s.words], o[2 * s.words]}, o[3 * s.words], o[4 * s.words], o[5 * s.words]};
+    Count q[2];
+#pragma unroll
+    for (int side = 0; side < 2; ++side) q[side] = Count{~s.layer[side * s.words + p.at], 0, 0};
+    Count d{~0ull, 0, 0};
+#pragma unroll
+    for (int k = 1; k <= kSteps; ++k) {
+        uint64_t all = 0;
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const uint64_t *set = s.yx + (side * kSteps + k - 1) * s.words;
+            uint64_t t = set[p.at];
+#pragma unroll
+            for (int j = 1; j <= k; ++j) t |= word_z(set, p, -j) | word_z(set, p, j);
+            q[side].add(~t);
+            all |= t;
+        }
+        s.cx[(k - 1) * s.words + p.at] = all;
+        const uint64_t *set = s.cz + (k - 1) * s.words;
+        uint64_t t = set[p.at];
+#pragma unroll
+        for (int j = 1; j <= k; ++j) t |= word_z(set, p, -j) | word_z(set, p, j);
+        d.add(~t);
+    }
+    best.offer(q[0], false, 0);
+    best.offer(q[1], true, 0);
+    o[0] = best.q.b0; o[s.words] = best.q.b1; o[2 * s.words] = best.q.b2;
+    o[3 * s.words] = best.side; o[4 * s.words] = best.a0; o[5 * s.words] = best.a1;
+    uint64_t *c = s.cube + p.at;
+    c[0] = d.b0; c[s.words] = d.b1; c[2 * s.words] = d.b2;
+    s.full[p.at] = d.b0 & d.b1 & d.b2;
+}
+
+// Extents (bit-sliced) of the slab of half thickness d (1 .. 3: masks t1, t2, t3) perpendicular to
+// an axis: the dilated slabs one and two bricks along it join in.
+struct Near5 {
+    uint64_t c, n1, n2;                               // the word itself, its neighbours 1 and 2 away
+};
+
+__device__ __forceinline__ Near5 near_rows(const uint64_t *set, const Place &p, bool along_z)
+{
+    // (no wall: a slab is at most as thick as the cube, which ends at it)
+    Near5 r;
+    r.c = set[p.at];
+    const int i = along_z ? p.z : p.y, n = along_z ? p.nz : p.ny;
+    const int64_t st = along_z ? p.sz : p.sy;
+    r.n1 = word_at(set, p.at - st, i - 1, n, false) | word_at(set, p.at + st, i + 1, n, false);
+    r.n2 = word_at(set, p.at - 2 * st, i - 2, n, false) | word_at(set, p.at + 2 * st, i + 2, n, false);
+    return r;
+}
+
+__device__ __forceinline__ Near5 near_bits(const uint64_t *set, const Place &p)
+{
+    const uint64_t c = set[p.at];
+    const uint64_t before = p.wi > 0 ? set[p.at - 1] : 0ull, after = p.wi + 1 < p.w ? set[p.at + 1] : 0ull;
+    Near5 r;
+    r.c = c;
+    r.n1 = (c << 1) | (before >> 63) | (c >> 1) | (after << 63);
+    r.n2 = (c << 2) | (before >> 62) | (c >> 2) | (after << 62);
+    return r;
+}
+
+__device__ __forceinline__ void slab_add(Count &q, const Near5 &v, uint64_t t1, uint64_t t2, uint64_t t3)
+{
+    const uint64_t s2 = v.c | v.n1, s3 = s2 | v.n2;
+    q.add(~((t1 & v.c) | (t2 & s2) | (t3 & s3)));
+}
+
+// The bricks whose 27 neighbours by steps of n bricks (themselves included) have full cubes.  The
+// grid's last row or brick stands for those past it (they are free, and of a cube there only the
+// part that reaches into the grid matters).
+template <int N>
+__device__ __forceinline__ uint64_t far_bits(const Scratch &s, const Place &p)
+{
+    uint64_t c = ~0ull, before = ~0ull, after = ~0ull;
+    const int db = p.wi > 0 ? -1 : 0, da = p.wi + 1 < p.w ? 1 : 0;
+#pragma unroll
+    for (int k = -N; k <= N; k += N)
+#pragma unroll
+        for (int j = -N; j <= N; j += N) {
+            const int y = min(max(p.y + j, 0), p.ny - 1), z = min(max(p.z + k, 0), p.nz - 1);
+            const uint64_t *v = s.full + p.wi + p.w * ((int64_t)y + (int64_t)p.ny * z);
+            c &= v[0];
+            before &= v[db];
+            after &= v[da];
+        }
+    if (db == 0) before = (c & 1ull) ? ~0ull : 0ull;
+    if (da == 0) after = (c >> 63) ? ~0ull : 0ull;
+    return c & ((c >> N) | (after << (64 - N))) & ((c << N) | (before >> (64 - N)));
+}
+
+// The entries' bit planes, one word of 64 bricks per thread, written over sets that only the same
+// thread still reads (the layers, then the best layers and the cubes).
+constexpr int kEntryPlanes = 14;
+
+__device__ __forceinline__ uint64_t *entry_plane(const Scratch &s, int k)
+{
+    return k < 6 ? s.layer + k * s.words : s.best + (k - 6) * s.words;
+}
+
+__global__ void __launch_bounds__(256) select_kernel(MapView m, Scratch s)
+{
+    const Place p = place_of(m, s, (int64_t)blockIdx.x * 256 + threadIdx.x);
+    if (!p.ok) return;
+    const uint64_t *c = s.cube + p.at;
+    const Count d{c[0], c[s.words], c[2 * s.words]};
+    const uint64_t t1 = d.b0 & ~d.b1 & ~d.b2, t2 = ~d.b0 & d.b1 & ~d.b2, t3 = d.b0 & d.b1 & ~d.b2;
+    Count qx{~0ull, 0, 0}, qy = qx, qz = qx;
+#pragma unroll
+    for (int k = 0; k < kSteps; ++k) {
+        slab_add(qx, near_bits(s.cx + k * s.words, p), t1, t2, t3);
+        slab_add(qy, near_rows(s.cy + k * s.words, p, false), t1, t2, t3);
+        slab_add(qz, near_rows(s.cz + k * s.words, p, true), t1, t2, t3);
+    }
+    // the widest slab, where it is wider than the cube
+    const uint64_t yz = above(qz, qy);
+    Count q = pick(yz, qz, qy);
+    const uint64_t px = ~above(q, qx);
+    q = pick(px, qx, q);
+    const uint64_t use = (t1 | t2 | t3) & above(q, d);
+    const uint64_t ax = use & px, ay = use & ~px & ~yz, az = use & ~px & yz;
+    const Count ex = pick(use & ~ax, q, d), ey = pick(use & ~ay, q, d), ez = pick(use & ~az, q, d);
+    const uint64_t occ = s.layer[4 * s.words + p.at] | s.layer[5 * s.words + p.at];
+    const uint64_t *h = s.best + p.at;
+    const uint64_t h0 = h[0], h1 = h[s.words], h2 = h[2 * s.words], side = h[3 * s.words], a0 = h[4 * s.words], a1 = h[5 * s.words];
+    const uint64_t far3 = far_bits<3>(s, p), far6 = far_bits<6>(s, p);
+    // bits 1-3, 6-8, 11-13 of a free brick's entry; bits 8, 9, 10, 11-13 of an occupied one's; bit 15;
+    // half extent 10, 13
+    const uint64_t o[kEntryPlanes] = {ex.b0 & ~occ, ex.b1 & ~occ, ex.b2 & ~occ, ey.b0 & ~occ, ey.b1 & ~occ,
+                                      pick(occ, side, ey.b2), occ & a0, occ & a1, pick(occ, h0, ez.b0),
+                                      pick(occ, h1, ez.b1), pick(occ, h2, ez.b2), occ, far3, far6};
+#pragma unroll
+    for (int k = 0; k < kEntryPlanes; ++k) entry_plane(s, k)[p.at] = o[k];
+}
+
+// The entries: a wave writes 64, each lane picking its bit of every plane.
+__global__ void __launch_bounds__(256) expand_kernel(MapView m, Scratch s, uint16_t *box)
+{
+    const int64_t word = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (word >= s.words) return;
+    const int64_t row = word / s.w;
+    const int x = (int)(word - row * s.w) * 64 + (threadIdx.x & 63);
+    const uint32_t bits[kEntryPlanes] = {1u << 1, 1u << 2, 1u << 3, 1u << 6, 1u << 7, 1u << 8, 1u << 9, 1u << 10,
+                                         1u << 11, 1u << 12, 1u << 13, kBoxOccupied, 0u, 0u};
+    uint32_t e = 0;
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+        e |= __builtin_amdgcn_inverse_ballot_w64(entry_plane(s, k)[word]) ? bits[k] : 0u;
+    e = __builtin_amdgcn_inverse_ballot_w64(entry_plane(s, 12)[word]) ? box_extents(10, 10, 10) : e;
+    e = __builtin_amdgcn_inverse_ballot_w64(entry_plane(s, 13)[word]) ? box_extents(13, 13, 13) : e;
+    if (x >= m.nbx) return;
+    const uint32_t mask = s.mask[row * s.pitch + x];             // 0 for a free brick
+    box[row * m.nbx + x] = (uint16_t)(e | mask);
+}
+
+unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
+
+template <int DT, int W, bool UNIT>
+void launch_bricks(const BoxArgs &a, uint8_t *mask, int32_t pitch, hipStream_t s)
+{
+    using T = typename Voxel<DT>::T;
+    const MapView &m = a.map;
+    T *dst = DT == RMPC_OCC_U8 || a.src == m.data ? nullptr : static_cast<T *>(const_cast<void *>(m.data));
+    const int64_t n = (int64_t)((m.nbx + W - 1) / W) * m.nby * m.nbz;
+    if (n > 0)
+        brick_kernel<DT, W, UNIT><<<blocks_for(n), 256, 0, s>>>(m, static_cast<const T *>(a.src), dst, mask, pitch,
+                                                               const_cast<uint16_t *>(m.box));
+    if (dst && m.partial)
+        copy_rest_kernel<DT><<<(unsigned)m.ny * (unsigned)m.nz, 256, 0, s>>>(m, static_cast<const T *>(a.src), dst);
+}
+
+template <int DT>
+void launch_boxes_dt(const BoxArgs &a, hipStream_t s)
+{
+    using T = typename Voxel<DT>::T;
+    const MapView &m = a.map;
+    const bool wide = m.nx % 4 == 0 && reinterpret_cast<uintptr_t>(a.src) % (4 * sizeof(T)) == 0;
+    if (!a.scratch) {
+        if (wide) launch_bricks<DT, 2, true>(a, nullptr, 0, s);
+        else launch_bricks<DT, 1, true>(a, nullptr, 0, s);
+        return;
+    }
+    const Scratch p = scratch_at(m, a.scratch);
+    if (wide) launch_bricks<DT, 2, false>(a, p.mask, p.pitch, s);
+    else launch_bricks<DT, 1, false>(a, p.mask, p.pitch, s);
+    if (p.words == 0) return;
+    layer_bits_kernel<<<blocks_for(16 * p.words), 256, 0, s>>>(m, p);
+    planes_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
+    cubes_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
+    select_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
+    expand_kernel<<<(unsigned)((p.words + 3) / 4), 256, 0, s>>>(m, p, const_cast<uint16_t *>(m.box));
+}
+
+}  // namespace
+
+size_t box_scratch_bytes(const MapView &m)
+{
+    return set_words(m) == 0 ? 0 : (size_t)(mask_bytes(m) + 8 * kSets * set_words(m));
+}
+
+hipError_t launch_map_boxes(const BoxArgs &a, hipStream_t s)
+{
+    switch (a.map.dtype) {
+    case RMPC_TSDF_F32: launch_boxes_dt<RMPC_TSDF_F32>(a, s); break;
+    case RMPC_TSDF_F16: launch_boxes_dt<RMPC_TSDF_F16>(a, s); break;
+    default: launch_boxes_dt<RMPC_OCC_U8>(a, s); break;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace rmpc

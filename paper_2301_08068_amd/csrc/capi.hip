@@ -315,11 +315,15 @@ rmpc_status account_profile(rmpc_ctx *ctx)
 }
 
 
-// Validates a dense map's descriptor and lays it out: the grid, then one summary element per
-// whole 8^3 cell and one per whole 2^3 brick, each at an offset rounded up to 256 elements.
+// Validates a dense map's descriptor and lays it out: n_all elements, the grid in the first
+// cell_base of them, then one per whole 8^3 cell and one per whole 2^3 brick, each part at an
+// offset rounded up to 256 elements.  The box entries (2 bytes per brick) of float maps take the
+// part after the grid: with an entry for the partial bricks at odd extents too where they fit,
+// else for whole bricks only; uint8 maps keep no grid, and their entries take its place (they
+// always fit: a brick has a byte per voxel, at least two).
 // Linear voxel indices must fit int32 (the per-ray debug output and the query's start index are
 // int32), and every element offset uint32.
-rmpc_status dense_layout(const rmpc_map_desc &d, rmpc::MapView &v, uint64_t &n_all)
+rmpc_status dense_layout(const rmpc_map_desc &d, rmpc::MapView &v, uint64_t &n_all, size_t &box_offset)
 {
     if (d.nx < 1 || d.ny < 1 || d.nz < 1 || d.nx > kMaxDim || d.ny > kMaxDim || d.nz > kMaxDim)
         return fail(RMPC_E_INVALID, "grid dimensions out of [1, 4096]");
@@ -331,19 +335,42 @@ rmpc_status dense_layout(const rmpc_map_desc &d, rmpc::MapView &v, uint64_t &n_a
     if (n_log >= (1ull << 31)) return fail(RMPC_E_INVALID, "grid has 2^31 voxels or more (linear indices are int32)");
     std::memset(&v, 0, sizeof v);
     v.nx = d.nx; v.ny = d.ny; v.nz = d.nz; v.dtype = d.dtype;
-    v.ncx = d.nx >> rmpc::kCellLog2;
-    v.ncy = d.ny >> rmpc::kCellLog2;
-    v.ncz = d.nz >> rmpc::kCellLog2;
-    v.nbx = d.nx >> rmpc::kBrickLog2;
-    v.nby = d.ny >> rmpc::kBrickLog2;
-    v.nbz = d.nz >> rmpc::kBrickLog2;
+    const uint64_t cells = (uint64_t)(d.nx >> rmpc::kCellLog2) * (d.ny >> rmpc::kCellLog2) * (d.nz >> rmpc::kCellLog2);
+    const uint64_t bricks = (uint64_t)(d.nx >> rmpc::kBrickLog2) * (d.ny >> rmpc::kBrickLog2) * (d.nz >> rmpc::kBrickLog2);
     const uint64_t cell_base = (n_log + 255) / 256 * 256;
-    const uint64_t brick_base = (cell_base + (uint64_t)v.ncx * v.ncy * v.ncz + 255) / 256 * 256;
-    n_all = brick_base + (uint64_t)v.nbx * v.nby * v.nbz;
+    n_all = (cell_base + cells + 255) / 256 * 256 + bricks;
     if (n_all >= (1ull << 32)) return fail(RMPC_E_INVALID, "grid too large for 32-bit voxel offsets");
-    v.cell_base = (uint32_t)cell_base;
-    v.brick_base = (uint32_t)brick_base;
+    v.nbx = (d.nx + 1) / 2;
+    v.nby = (d.ny + 1) / 2;
+    v.nbz = (d.nz + 1) / 2;
+    box_offset = 0;
+    if (d.dtype != RMPC_OCC_U8) {
+        const size_t eb = elem_bytes(d.dtype);
+        box_offset = (size_t)cell_base * eb;
+        if (2 * (uint64_t)v.nbx * v.nby * v.nbz > (n_all - cell_base) * eb) {
+            v.nbx = d.nx / 2;
+            v.nby = d.ny / 2;
+            v.nbz = d.nz / 2;
+            v.partial = 1;
+        }
+    }
     return RMPC_OK;
+}
+
+// The entries of a uint8 grid in host memory with single-brick boxes (used when there is no
+// memory for the scratch of the box kernels).
+std::vector<uint16_t> host_unit_boxes(const rmpc::MapView &m, const uint8_t *vox)
+{
+    std::vector<uint16_t> box((size_t)m.nbx * m.nby * m.nbz, 0);
+    for (int z = 0; z < m.nz; ++z)
+        for (int y = 0; y < m.ny; ++y)
+            for (int x = 0; x < m.nx; ++x)
+                if (vox[(size_t)x + (size_t)m.nx * (y + (size_t)m.ny * z)])
+                    box[(size_t)(x / 2) + (size_t)m.nbx * (y / 2 + (size_t)m.nby * (z / 2))] |=
+                        (uint16_t)(rmpc::kBoxOccupied | rmpc::kBoxNoLayer | (1u << ((x & 1) + 2 * (y & 1) + 4 * (z & 1))));
+    for (uint16_t &e : box)
+        if (!e) e = (uint16_t)rmpc::box_extents(1, 1, 1);
+    return box;
 }
 
 // Validates a scan query and fills everything of ScanArgs but its reduction slots.
@@ -504,7 +531,8 @@ rmpc_status rmpc_map_footprint(const rmpc_map_desc *desc, size_t *bytes)
     if (!desc || !bytes) return fail(RMPC_E_INVALID, "NULL argument");
     rmpc::MapView v;
     uint64_t n_all;
-    if (rmpc_status st = dense_layout(*desc, v, n_all)) return st;
+    size_t box_offset;
+    if (rmpc_status st = dense_layout(*desc, v, n_all, box_offset)) return st;
     *bytes = (size_t)(n_all * elem_bytes(desc->dtype));
     return RMPC_OK;
 }
@@ -516,21 +544,56 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
     if (ctx->server) return fail(RMPC_E_INVALID, "maps cannot change while the server runs");
     rmpc::MapView v;
     uint64_t n_all;
-    if (rmpc_status st = dense_layout(*desc, v, n_all)) return st;
+    size_t box_offset;
+    if (rmpc_status st = dense_layout(*desc, v, n_all, box_offset)) return st;
     DeviceGuard dg(ctx->device);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const uint64_t n_log = (uint64_t)desc->nx * desc->ny * desc->nz;
     const size_t eb = elem_bytes(desc->dtype);
+    const bool u8 = desc->dtype == RMPC_OCC_U8;
     size_t off;
     if (!ctx->alloc.alloc(n_all * eb, &off)) return fail(RMPC_E_NOMEM, "arena full (map)");
-    v.data = ctx->arena + off;
-    // the grid is stored as given (x-fastest); the cell and brick summaries follow it
-    hipError_t e = hipMemcpyAsync(ctx->arena + off, voxels, n_log * eb,
-                                  voxels_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = rmpc::launch_map_summaries(rmpc::SummaryArgs{v}, s);
+    uint8_t *base = ctx->arena + off;
+    v.data = u8 ? nullptr : base;
+    v.box = reinterpret_cast<uint16_t *>(base + box_offset);
+    // scratch of the box kernels for the duration of the call: from the arena, else from the
+    // device; without any, every free brick gets a box of itself (the same results, more steps)
+    const size_t scratch_bytes = rmpc::box_scratch_bytes(v);
+    rmpc::BoxArgs A{v, voxels, nullptr};
+    size_t scratch_off = 0;
+    void *scratch_dev = nullptr;
+    const bool in_arena = scratch_bytes > 0 && ctx->alloc.alloc(scratch_bytes, &scratch_off);
+    if (in_arena) A.scratch = ctx->arena + scratch_off;
+    else if (scratch_bytes > 0 && hipMalloc(&scratch_dev, scratch_bytes) == hipSuccess) A.scratch = static_cast<uint8_t *>(scratch_dev);
+    else (void)hipGetLastError();
+    // the kernels read the caller's buffer themselves when it is memory of this GPU; any other
+    // pointer is copied to the arena first
+    hipPointerAttribute_t attr;
+    const bool direct = voxels_on_device && hipPointerGetAttributes(&attr, voxels) == hipSuccess &&
+                        attr.type == hipMemoryTypeDevice && attr.device == ctx->device;
+    if (!direct) (void)hipGetLastError();
+    std::vector<uint16_t> host_boxes;
+    hipError_t e = hipSuccess;
+    if (!direct && !(u8 && !A.scratch)) {
+        e = hipMemcpyAsync(base, voxels, n_log * eb, voxels_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s);
+        A.src = base;
+    }
+    if (!direct && u8 && !A.scratch) {
+        // in place the entries would overwrite voxels still to be read
+        std::vector<uint8_t> vox((size_t)n_log);
+        e = hipMemcpyAsync(vox.data(), voxels, (size_t)n_log, hipMemcpyDefault, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        host_boxes = host_unit_boxes(v, vox.data());
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(base, host_boxes.data(), sizeof(uint16_t) * host_boxes.size(), hipMemcpyHostToDevice, s);
+    } else if (e == hipSuccess) {
+        e = rmpc::launch_map_boxes(A, s);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) (void)hipStreamSynchronize(s);
+    if (in_arena) ctx->alloc.release(scratch_off);
+    if (scratch_dev) (void)hipFree(scratch_dev);
     if (e != hipSuccess) {
-        (void)hipStreamSynchronize(s);
         ctx->alloc.release(off);
         return fail(RMPC_E_HIP, std::string("map upload: ") + hipGetErrorString(e));
     }

@@ -32,6 +32,10 @@ __global__ void __launch_bounds__(256) edt_rows_kernel(MapView m, int32_t *g)
     if (row >= (int64_t)m.ny * m.nz) return;             // the same for the whole wave
     using T = typename Voxel<DT>::T;
     const T *data = static_cast<const T *>(m.data);
+    // uint8 maps: the row's entries and the bits of its voxels in them
+    const uint32_t y = (uint32_t)(row % m.ny), z = (uint32_t)(row / m.ny);
+    const uint16_t *box = m.box + (size_t)m.nbx * ((y >> 1) + (size_t)m.nby * (z >> 1));
+    const uint32_t sub = 2u * (y & 1u) + 4u * (z & 1u);
     const int lane = threadIdx.x & 63;
     const int32_t nx = m.nx;
     const int nch = (nx + 63) >> 6;
@@ -42,7 +46,12 @@ __global__ void __launch_bounds__(256) edt_rows_kernel(MapView m, int32_t *g)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int32_t i = ((c0 + u) << 6) + lane;
-            o[u] = i < nx && Voxel<DT>::occ(data[base + i]);
+            if constexpr (DT == RMPC_OCC_U8) {
+                const uint32_t e = i < nx ? box[i >> 1] : 0u;
+                o[u] = (e & kBoxOccupied) != 0u && ((e >> (sub + (i & 1))) & 1u) != 0u;
+            } else {
+                o[u] = i < nx && Voxel<DT>::occ(data[base + i]);
+            }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {

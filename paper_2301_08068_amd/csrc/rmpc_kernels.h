@@ -8,8 +8,7 @@
 
 namespace rmpc {
 
-// Steps (voxels or free cells) planned per lane and round of a single query by default
-// (4, 8 or 16 are compiled; measured fastest for one 65536-ray query on gfx950).
+// The dense configurations' lookahead as reported by default (their walks do not plan ahead).
 constexpr int kLookahead = 8;
 
 // Threads per block of the query kernels (one tile = this many lanes).
@@ -26,22 +25,32 @@ constexpr int kPartialWords = 32;
 constexpr int kScanMaxBlocks = 128;
 constexpr int kScanBatch = 8;                // scan points a thread loads before it evaluates them
 
-// A resident map: the voxel grid x-fastest (element offset x + nx (y + ny z)), then, at
-// element offset cell_base, one summary element per cell of 8 x 8 x 8 voxels, also x-fastest:
-// "occupied" when any voxel of the cell is, "free" when none is.  Only whole cells inside the
-// grid have a summary (ncx = nx / 8 etc.); the walk skips free cells whole.
-struct MapView {
-    const void *data;
-    int32_t nx, ny, nz, dtype;
-    uint32_t cell_base;          // element offset of the cell summaries
-    int32_t ncx, ncy, ncz;       // whole cells along each axis
-    uint32_t brick_base;         // element offset of the brick summaries
-    int32_t nbx, nby, nbz;       // whole bricks along each axis
-};
-
-// log2 of the edge, in voxels, of a summary cell and of a summary brick.
+// log2 of the edge, in voxels, of a brick, and of the cells that the arena layout counts.
 constexpr int kCellLog2 = 3;
 constexpr int kBrickLog2 = 1;
+
+// Box entry of a brick (16 bits).
+//   Free brick: three 5-bit fields from bit 0 that hold twice the half extents (2 ex, 2 ey, 2 ez;
+//   1 <= e <= kBoxMax bricks): every brick within ex - 1, ey - 1 and ez - 1 of it along x, y and z
+//   is free (or outside the grid).
+//   Occupied brick: kBoxOccupied, the occupancy of its voxels in the low byte (bit (x & 1) + 2 (y
+//   & 1) + 4 (z & 1)), and one of its six voxel layers that is free: bit 8 the side, bits 9-10 the
+//   axis a (3: none, with side 1), bits 11-14 its half extent e: the voxel layer on that side of
+//   axis a is free in every brick within e - 1 of it along the other two axes.
+constexpr uint32_t kBoxOccupied = 0x8000u;
+constexpr uint32_t kBoxNoLayer = (1u << 8) | (3u << 9);
+constexpr int kBoxMax = 15;
+constexpr uint32_t box_extents(uint32_t ex, uint32_t ey, uint32_t ez) { return 2u * (ex | (ey << 5) | (ez << 10)); }
+
+// A resident map: float32 and float16 maps keep the voxel grid x-fastest (element offset x + nx
+// (y + ny z)); uint8 maps keep only the box entries, which hold every voxel's occupancy.
+struct MapView {
+    const void *data;            // the grid (uint8 maps: null)
+    const uint16_t *box;         // one entry per brick, x-fastest
+    int32_t nx, ny, nz, dtype;
+    int32_t nbx, nby, nbz;       // bricks with an entry along each axis
+    int32_t partial;             // non-zero: an odd last layer of voxels has no entries
+};
 
 // A sparse map: 8 x 8 x 8-voxel blocks stored where the world has content (every other voxel
 // is free), found through an open-addressed hash table from block coordinates to slots.
@@ -118,7 +127,7 @@ struct RayArgs {
     float tmax_lo, tmax_hi;      // float32 guard band around max_range / h
     double tmax_v;               // parameter span split into segments: min(max_range / h, grid diagonal)
     int32_t segments;            // segments per ray (1, 2, 4, 8 or 16): a tile holds kBlock / segments rays
-    int32_t lookahead;           // steps planned per round (4, 8 or 16)
+    int32_t lookahead;           // sparse maps: block steps planned per round (4, 8 or 16)
     double max_range, h;
     int32_t subvoxel;            // non-zero: refine hit distances on the interpolated TSDF
     double vel64[3];             // velocity, float64 (for the exact contribution count)
@@ -209,8 +218,11 @@ struct GatherArgs {
     RayRec *out;
 };
 
-struct SummaryArgs {
-    MapView map;                 // grid in place; summaries are written at cell_base
+// Build a map's box entries (and its grid) from the voxels at src.
+struct BoxArgs {
+    MapView map;                 // data and box already point into the arena
+    const void *src;             // device memory: the voxels, x-fastest (map.data: in place)
+    uint8_t *scratch;            // box_scratch_bytes, or null: every free brick gets a box of itself
 };
 
 int ray_grid_blocks(int n_rays);
@@ -222,7 +234,9 @@ hipError_t launch_raycast(const RayArgs &a, hipStream_t s, bool debug, hipEvent_
 hipError_t launch_scan(const ScanArgs &a, hipStream_t s, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr);
 hipError_t launch_directions(const DirsArgs &a, hipStream_t s);
-hipError_t launch_map_summaries(const SummaryArgs &a, hipStream_t s);
+hipError_t launch_map_boxes(const BoxArgs &a, hipStream_t s);
+// Scratch bytes of launch_map_boxes.
+size_t box_scratch_bytes(const MapView &m);
 hipError_t launch_compact(const CompactArgs &a, hipStream_t s);
 hipError_t launch_gather(const GatherArgs &a, hipStream_t s);
 // Exact squared Euclidean distance transform of the map's occupancy into out (x fastest).
@@ -245,8 +259,8 @@ hipError_t launch_sparse(const RayArgs &a, hipStream_t s, bool debug, hipEvent_t
 // Occupancy masks of n sparse blocks from their values, and the tables' occupied flags.
 hipError_t launch_sparse_masks(const SparseView &v, HashEntry *table, hipStream_t s);
 // Persistent fused batch: `blocks` resident blocks pull tiles from a counter.
-hipError_t launch_batch(const BatchArgs &a, int blocks, int lookahead, hipStream_t s);
-// Resident blocks per CU of the batch kernel for a lookahead.
-int batch_blocks_per_cu(int lookahead);
+hipError_t launch_batch(const BatchArgs &a, int blocks, hipStream_t s);
+// Resident blocks per CU of the batch kernel.
+int batch_blocks_per_cu();
 
 }  // namespace rmpc

@@ -1,5 +1,5 @@
-// rmpc_walk.h -- device-side pieces of the exact ray walk shared by the dense-grid kernels
-// (raycast.hip) and the sparse block-map kernels (sparse.hip): float32 crossing parameters with
+// rmpc_walk.h -- device-side pieces of the exact ray walk used by the sparse block-map kernels
+// (rmpc_sparse.h) and, in part, by the dense walk (rmpc_dense.h): float32 crossing parameters with
 // float64 decisions inside a guard band, segment boundaries, entry voxels of coarse elements,
 // the per-ray obstacle policy, and launch helpers.  gfx950 only.
 #pragma once

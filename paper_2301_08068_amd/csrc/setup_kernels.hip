@@ -1,5 +1,5 @@
-// setup_kernels.hip -- one-time device work: the Halton ray-direction table, the ordered ray
-// lists and the free-cell summaries of an uploaded voxel grid.
+// setup_kernels.hip -- one-time device work: the Halton ray-direction table and the ordered ray
+// lists.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -41,42 +41,6 @@ __global__ void directions_kernel(DirsArgs A)
     A.out[i] = (float)(rho * c);
     A.out[i + A.n] = (float)(rho * s);
     A.out[i + 2 * A.n] = (float)z;
-}
-
-// Summary of each whole block of (2^LG)^3 voxels: "occupied" if any voxel in it is, stored
-// at base + bx + nbx * (by + nby * bz).
-template <int DT, int LG>
-__global__ void summary_kernel(MapView m, uint32_t base, int nbx, int nby, int nbz, typename Voxel<DT>::T occ_val,
-                               typename Voxel<DT>::T free_val)
-{
-    using T = typename Voxel<DT>::T;
-    constexpr int E = 1 << LG;
-    const int n_blocks = nbx * nby * nbz;
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_blocks) return;
-    const int cx = c % nbx, cy = (c / nbx) % nby, cz = c / (nbx * nby);
-    T *data = static_cast<T *>(const_cast<void *>(m.data));
-    bool any = false;
-    for (int k = 0; k < E * E * E && !any; ++k) {
-        const int x = (cx << LG) + (k % E), y = (cy << LG) + ((k / E) % E), z = (cz << LG) + k / (E * E);
-        any = Voxel<DT>::occ(data[(uint32_t)x + (uint32_t)m.nx * ((uint32_t)y + (uint32_t)m.ny * (uint32_t)z)]);
-    }
-    data[base + (uint32_t)c] = any ? occ_val : free_val;
-}
-
-template <int DT, int LG>
-void launch_summary(const MapView &m, uint32_t base, int nbx, int nby, int nbz, typename Voxel<DT>::T occ_val,
-                    typename Voxel<DT>::T free_val, hipStream_t s)
-{
-    const int n = nbx * nby * nbz;
-    if (n > 0) summary_kernel<DT, LG><<<(n + 255) / 256, 256, 0, s>>>(m, base, nbx, nby, nbz, occ_val, free_val);
-}
-
-template <int DT>
-void launch_summaries(const MapView &m, typename Voxel<DT>::T occ_val, typename Voxel<DT>::T free_val, hipStream_t s)
-{
-    launch_summary<DT, kCellLog2>(m, m.cell_base, m.ncx, m.ncy, m.ncz, occ_val, free_val, s);
-    launch_summary<DT, kBrickLog2>(m, m.brick_base, m.nbx, m.nby, m.nbz, occ_val, free_val, s);
 }
 
 // Chunk-wise count of entries < n (one 1024-entry chunk per block).
@@ -145,16 +109,6 @@ hipError_t launch_compact(const CompactArgs &a, hipStream_t s)
 hipError_t launch_directions(const DirsArgs &a, hipStream_t s)
 {
     directions_kernel<<<(a.n + 255) / 256, 256, 0, s>>>(a);
-    return hipGetLastError();
-}
-
-hipError_t launch_map_summaries(const SummaryArgs &a, hipStream_t s)
-{
-    switch (a.map.dtype) {
-    case RMPC_TSDF_F32: launch_summaries<RMPC_TSDF_F32>(a.map, -1.0f, 1.0f, s); break;
-    case RMPC_TSDF_F16: launch_summaries<RMPC_TSDF_F16>(a.map, (uint16_t)0xbc00, (uint16_t)0x3c00, s); break;
-    default: launch_summaries<RMPC_OCC_U8>(a.map, (uint8_t)1, (uint8_t)0, s); break;
-    }
     return hipGetLastError();
 }
 
