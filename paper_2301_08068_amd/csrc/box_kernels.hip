@@ -8,7 +8,7 @@
 //           brick (in bit-sliced counters) gives its free layers' extents (1 .. 7); the union of
 //           an axis' two sides gives the extents of a slab one brick thick
 //   cube    the cubic dilations by 1 .. 6: the half extent d of the free cube around a brick
-//   slab    close to a surface (d <= kBoxThin) the slab of half thickness d, perpendicular to the
+//   slab    close to a surface (d <= 3) the slab of half thickness d, perpendicular to the
 //           axis that allows the widest one, takes the cube's place, so that rays that graze floors
 //           and walls cross long runs of free space too
 //   far     where the cubes of the 27 bricks 3 (6) away are free as well, half extent 10 (13)
@@ -30,7 +30,6 @@ namespace rmpc {
 
 namespace {
 
-constexpr int kBoxThin = 3;
 constexpr int kSteps = 6;                         // dilation steps; extents 1 .. kSteps + 1 come from them
 constexpr uint32_t kUnitBox = box_extents(1, 1, 1);
 

@@ -22,6 +22,8 @@ namespace rmpc_host {
 
 constexpr size_t kMinArena = 16u << 20;
 constexpr int kMaxDim = 4096;
+// 32-bit words of the context's pinned completion block (64 bytes; word 0 and 1: the sequence number)
+constexpr int kEdtFlagWord = 4;              // a distance transform needs its wide passes
 constexpr int32_t kMaxSparseBlocks = 1 << 22;   // slot * 512 + voxel fits int32
 
 thread_local std::string g_last_error;
@@ -836,8 +838,27 @@ rmpc_status rmpc_edt(rmpc_ctx *ctx, int32_t map_id, int32_t *sqdist_dev, void *h
     if (it->second.sparse) return fail(RMPC_E_INVALID, "the distance transform needs a dense map");
     DeviceGuard dg(ctx->device);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    RMPC_HIP(rmpc::launch_edt(it->second.view, sqdist_dev, s));
-    RMPC_HIP(hipStreamSynchronize(s));
+    // the narrow passes with scratch for the call (as much as the arena has room for); where a
+    // distance exceeds them, or without any room, the wide passes
+    const rmpc::MapView &v = it->second.view;
+    uint32_t *flag = reinterpret_cast<uint32_t *>(ctx->done_host) + kEdtFlagWord;
+    size_t off, bytes = rmpc::edt_scratch_bytes(v);
+    bool wide = !ctx->alloc.alloc(bytes, &off) && !ctx->alloc.alloc(bytes = rmpc::kEdtFlagBytes, &off);
+    hipError_t e = hipSuccess;
+    if (!wide) {
+        *flag = 0u;
+        e = rmpc::launch_edt(v, sqdist_dev, ctx->arena + off, bytes, flag, s);
+        const hipError_t se = hipStreamSynchronize(s);
+        ctx->alloc.release(off);
+        if (e == hipSuccess) e = se;
+        wide = __atomic_load_n(flag, __ATOMIC_ACQUIRE) != 0u;
+    }
+    if (e == hipSuccess && wide) {
+        e = rmpc::launch_edt_wide(v, sqdist_dev, s);
+        const hipError_t se = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = se;
+    }
+    if (e != hipSuccess) return fail(RMPC_E_HIP, std::string("distance transform: ") + hipGetErrorString(e));
     return RMPC_OK;
 }
 

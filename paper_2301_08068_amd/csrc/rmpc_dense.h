@@ -233,9 +233,9 @@ __device__ __forceinline__ void box_step(const RayArgs &A, const BoxRay &R, BoxW
         const uint32_t axis = (e >> 9) & 3u;
         const bool in = (((at >> axis) ^ (e >> 8)) & 1u) == 0u;
         const int reach = (int)((e >> 10) & 30u);
-        Fx = in & (axis != 0u) ? ex + reach : w.ux + 1;
-        Fy = in & (axis != 1u) ? ey + reach : w.uy + 1;
-        Fz = in & (axis != 2u) ? ez + reach : w.uz + 1;
+        Fx = (in & (axis != 0u)) ? ex + reach : w.ux + 1;
+        Fy = (in & (axis != 1u)) ? ey + reach : w.uy + 1;
+        Fz = (in & (axis != 2u)) ? ez + reach : w.uz + 1;
     }
     const float Tx = box_crossing(Fx, R.gsx, R.arx), Ty = box_crossing(Fy, R.gsy, R.ary), Tz = box_crossing(Fz, R.gsz, R.arz);
     const float t1 = __builtin_amdgcn_fmed3f(Tx, fminf(Ty, Tz), -kInf);

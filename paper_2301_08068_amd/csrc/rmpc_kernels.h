@@ -239,8 +239,16 @@ hipError_t launch_map_boxes(const BoxArgs &a, hipStream_t s);
 size_t box_scratch_bytes(const MapView &m);
 hipError_t launch_compact(const CompactArgs &a, hipStream_t s);
 hipError_t launch_gather(const GatherArgs &a, hipStream_t s);
-// Exact squared Euclidean distance transform of the map's occupancy into out (x fastest).
-hipError_t launch_edt(const MapView &m, int32_t *out, hipStream_t s);
+// Exact squared Euclidean distance transform of the map's occupancy into out (x fastest) where
+// every distance stays below 256 voxels; otherwise *flag_host (pinned, cleared by the caller) is
+// set and out is undefined.  scratch: edt_scratch_bytes, or at least kEdtFlagBytes (the row
+// distances then go through out), 256-byte aligned.
+constexpr size_t kEdtFlagBytes = 256;
+hipError_t launch_edt(const MapView &m, int32_t *out, void *scratch, size_t scratch_bytes, uint32_t *flag_host,
+                      hipStream_t s);
+// The same for any distance, without scratch.
+hipError_t launch_edt_wide(const MapView &m, int32_t *out, hipStream_t s);
+size_t edt_scratch_bytes(const MapView &m);
 
 // The single-lookup ESDF policy at one position.
 struct EsdfArgs {

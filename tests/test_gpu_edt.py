@@ -107,3 +107,57 @@ def test_esdf_policy_matches_oracle(ctx, tiny_map):
         assert e.value.status == B.RMPC_E_OUT_OF_BOUNDS
     finally:
         ctx.release(mid)
+
+
+@pytest.mark.parametrize("room", [True, False])
+@pytest.mark.parametrize("enc", ["f32", "f16", "u8"])
+@pytest.mark.parametrize("shape,p", [((64, 65, 33), 0.003), ((63, 128, 32), 0.0005), ((129, 66, 31), 0.002),
+                                     ((2, 257, 65), 0.002), ((300, 3, 40), 0.2)])
+def test_chunk_and_strip_edges(shape, p, enc, room):
+    """Lines of one element less, as many and one more than the passes' chunks of 64, strips of 32
+    lines with and without a rest, in an arena with room for the rows' words and in a full one (the
+    row distances then pass through the field)."""
+    from paper_2301_08068_amd import binding
+    rng = np.random.default_rng(sum(shape))
+    occ = rng.uniform(size=shape) < p
+    occ[-1, -1, -1] = True
+    t = np.where(occ, -0.05, 0.3).astype(np.float32)
+    data = {"f32": t, "f16": W.encode_f16(t), "u8": W.encode_u8(t)}[enc]
+    c = binding.Context(0, arena_bytes=24 << 20)
+    try:
+        mid = c.upload(data, 0.1, np.zeros(3), enc)
+        n = 0 if room else 1 << 15
+        while n:
+            try:
+                c.upload(np.zeros((n, 1, 256), np.uint8), 0.1, np.zeros(3), "u8") if n <= 4096 else \
+                    c.upload(np.zeros((4096, 1, n >> 4), np.uint8), 0.1, np.zeros(3), "u8")
+            except binding.RmpcError as e:
+                assert e.status == binding.RMPC_E_NOMEM
+                n >>= 1
+        g = c.edt(mid, shape).cpu().numpy()
+    finally:
+        c.close()
+    assert np.array_equal(g, oracle.edt(oracle.OracleMap(data, 0.1, np.zeros(3), enc)))
+
+
+# (one occupied voxel in a corner) the farthest voxel at 255, at 256 and beyond; strips without any
+# occupied voxel beside others; a single row, column and voxel
+@pytest.mark.parametrize("shape", [(1, 256, 1), (1, 257, 1), (256, 1, 3), (257, 2, 3), (3, 2, 256), (3, 2, 257),
+                                   (2, 300, 70), (5, 3, 600), (181, 181, 2), (182, 182, 2), (1, 1, 1), (3, 2, 1)])
+@pytest.mark.parametrize("at", [0, -1])
+def test_distances_around_the_narrow_limit(ctx, shape, at):
+    t = np.full(shape, 0.3, np.float32)
+    t.reshape(-1)[at] = -0.05
+    g = _gpu_edt(ctx, t, 0.1, "f32")
+    assert np.array_equal(g, oracle.edt(oracle.OracleMap(t, 0.1, np.zeros(3), "f32")))
+
+
+@pytest.mark.parametrize("n", [207, 208, 209, 831, 832, 833, 1665, 4000, 4001])
+def test_strip_widths(ctx, n):
+    """Lines of the lengths at which the strips narrow, along y and along z, with a rest of lines."""
+    rng = np.random.default_rng(n)
+    for shape in ((2, n, 35), (n, 2, 35)):
+        t = np.where(rng.uniform(size=shape) < 0.002, -0.05, 0.3).astype(np.float32)
+        t.reshape(-1)[n] = -0.05
+        g = _gpu_edt(ctx, t, 0.1, "f32")
+        assert np.array_equal(g, oracle.edt(oracle.OracleMap(t, 0.1, np.zeros(3), "f32")))
