@@ -181,8 +181,9 @@ __device__ __forceinline__ bool box_step64(const RayArgs &A, const BoxRay &R, Bo
     if (Y < t64) { a = 1; t64 = Y; }
     if (Z < t64) { a = 2; t64 = Z; }
     bool tie = (a != 0 && X - t64 < 1e-5) || (a != 1 && Y - t64 < 1e-5) || (a != 2 && Z - t64 < 1e-5);
-    const float ta = a == 0 ? box_crossing(Fx, R.gsx, R.arx)
-                            : (a == 1 ? box_crossing(Fy, R.gsy, R.ary) : box_crossing(Fz, R.gsz, R.arz));
+    // (a choice between values: one between R's fields would keep R in private memory)
+    const float Tx = box_crossing(Fx, R.gsx, R.arx), Ty = box_crossing(Fy, R.gsy, R.ary), Tz = box_crossing(Fz, R.gsz, R.arz);
+    const float ta = a == 0 ? Tx : (a == 1 ? Ty : Tz);
     if (ta > t_hi) return false;
     if (ta >= t_lo && t64 * A.h > A.max_range) return false;           // closed interval
     if (a == 0 ? Fx == ex : (a == 1 ? Fy == ey : Fz == ez)) return false;

@@ -145,34 +145,68 @@ __device__ __forceinline__ int opaque_tid()
     return t;
 }
 
-// The block total, written to out[] in partial layout (9 sums, 9 compensations, 4 counters).
-__device__ __forceinline__ void block_reduce_store(const Acc &a, float *lds, float *out)
+constexpr int kColRows = kBlock / kColLanes;       // rows a lane merges
+
+// A lane's share of a column: the pair sums of its kColRows rows and, in the counter lanes, their
+// sum of one counter.
+struct Column {
+    float s[kColRows], c[kColRows];
+    int32_t n;
+};
+
+// Take the kBlock rows in LDS: as they are (first) or merged after the rows taken before.
+__device__ __forceinline__ void column_rows(Column &o, const float *lds, int t, bool first)
 {
-    const int t = opaque_tid(), q = t % kColLanes;
-    row_store(lds + t * kRowWords, a);
-    __syncthreads();
+    const int q = t % kColLanes;
     if (t < kPairLanes) {
         const int col = t / kColLanes;
-        float vs[kBlock / kColLanes], vc[kBlock / kColLanes];
+        float s[kColRows], c[kColRows];
 #pragma unroll
-        for (int u = 0; u < kBlock / kColLanes; ++u) {
-            vs[u] = lds[(q + u * kColLanes) * kRowWords + col];
-            vc[u] = lds[(q + u * kColLanes) * kRowWords + 9 + col];
+        for (int u = 0; u < kColRows; ++u) {
+            s[u] = lds[(q + u * kColLanes) * kRowWords + col];
+            c[u] = lds[(q + u * kColLanes) * kRowWords + 9 + col];
         }
-        float s = vs[0], c = vc[0];
 #pragma unroll
-        for (int u = 1; u < kBlock / kColLanes; ++u) csum_merge(s, c, vs[u], vc[u]);
-        pair_butterfly(t, s, c);
-        if (q == 0) { out[col] = s; out[9 + col] = c; }
+        for (int u = 0; u < kColRows; ++u) {
+            if (first) { o.s[u] = s[u]; o.c[u] = c[u]; }
+            else csum_merge(o.s[u], o.c[u], s[u], c[u]);
+        }
     } else if (t >= kIntLane0) {
         const int col = (t - kIntLane0) / kColLanes;
         const int32_t *rows = reinterpret_cast<const int32_t *>(lds);
-        int32_t v = 0;
+        int32_t v = first ? 0 : o.n;
 #pragma unroll
-        for (int u = 0; u < kBlock / kColLanes; ++u) v += rows[(q + u * kColLanes) * kRowWords + 18 + col];
-        v = int_butterfly(v);
-        if (q == 0) reinterpret_cast<int32_t *>(out)[18 + col] = v;
+        for (int u = 0; u < kColRows; ++u) v += rows[(q + u * kColLanes) * kRowWords + 18 + col];
+        o.n = v;
     }
+}
+
+// The columns' totals, written to out[] in partial layout (9 sums, 9 compensations, 4 counters).
+__device__ __forceinline__ void column_store(const Column &o, int t, float *out)
+{
+    const int q = t % kColLanes;
+    if (t < kPairLanes) {
+        const int col = t / kColLanes;
+        float s = o.s[0], c = o.c[0];
+#pragma unroll
+        for (int u = 1; u < kColRows; ++u) csum_merge(s, c, o.s[u], o.c[u]);
+        pair_butterfly(t, s, c);
+        if (q == 0) { out[col] = s; out[9 + col] = c; }
+    } else if (t >= kIntLane0) {
+        const int32_t v = int_butterfly(o.n);
+        if (q == 0) reinterpret_cast<int32_t *>(out)[18 + (t - kIntLane0) / kColLanes] = v;
+    }
+}
+
+// The block total, written to out[].
+__device__ __forceinline__ void block_reduce_store(const Acc &a, float *lds, float *out)
+{
+    const int t = opaque_tid();
+    row_store(lds + t * kRowWords, a);
+    __syncthreads();
+    Column o;
+    column_rows(o, lds, t, true);
+    column_store(o, t, out);
 }
 
 // ------------------------------------------------------------------------------------
@@ -378,20 +412,6 @@ __device__ __forceinline__ void acc_from_words(const float *w, Acc &a)
     a.n_tie = __float_as_int(w[20]); a.visits = __float_as_int(w[21]);
 }
 
-// A row that another block has written to device memory, past this XCD's L2 (8 bytes a load).
-__device__ __forceinline__ void acc_from_partial(const float *p, Acc &a)
-{
-    uint64_t *q = reinterpret_cast<uint64_t *>(const_cast<float *>(p));
-    float w[22];
-#pragma unroll
-    for (int k = 0; k < 11; ++k) {
-        const uint64_t v = __hip_atomic_load(q + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        w[2 * k] = __uint_as_float((uint32_t)v);
-        w[2 * k + 1] = __uint_as_float((uint32_t)(v >> 32));
-    }
-    acc_from_words(w, a);
-}
-
 // Waits until this wave's earlier stores have been acknowledged.  Stores and atomics of agent
 // (system) scope are acknowledged by the memory that all XCDs (and the host) share, so an atomic
 // issued after the wait is seen by nobody before them, without the write-back of the whole L2
@@ -399,6 +419,38 @@ __device__ __forceinline__ void acc_from_partial(const float *p, Acc &a)
 __device__ __forceinline__ void wait_stores()
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// The total of n rows that other blocks have written to device memory, past this XCD's L2, written
+// to out[].  256 rows at a time: 16 lanes load a row (11 of them 8 bytes each) and put it into LDS
+// as a thread's row.  (A row per thread, 88 bytes at a stride of 128, made every load instruction
+// 64 requests: 512 rows took 4.9 us to arrive and be merged against 3.2, a
+// 65,536-ray query 33.6 us against 31.2.)
+__device__ __forceinline__ void rows_reduce_store(const float *rows, int n, float *lds, float *out)
+{
+    const int t = opaque_tid(), q = t & (kColLanes - 1), row = t / kColLanes;
+    const uint64_t *words = reinterpret_cast<const uint64_t *>(rows) + min(q, kSumWords / 2 - 1);
+    float *to = lds + row * kRowWords + 2 * q;
+    Column o;
+    for (int r0 = 0; r0 < n; r0 += kBlock) {
+        uint64_t w[kColRows];
+#pragma unroll
+        for (int k = 0; k < kColRows; ++k) {
+            const uint32_t r = (uint32_t)min(r0 + row + k * kColLanes, n - 1);
+            w[k] = __hip_atomic_load(words + r * (kPartialWords / 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (r0) __syncthreads();             // the rows before have been taken
+        if (q < kSumWords / 2)
+#pragma unroll
+            for (int k = 0; k < kColRows; ++k) {
+                const uint64_t v = r0 + row + k * kColLanes < n ? w[k] : 0ull;
+                to[k * kColLanes * kRowWords] = __uint_as_float((uint32_t)v);
+                to[k * kColLanes * kRowWords + 1] = __uint_as_float((uint32_t)(v >> 32));
+            }
+        __syncthreads();
+        column_rows(o, lds, t, r0 == 0);
+    }
+    column_store(o, t, out);
 }
 
 // Where one reduction keeps its state: tile rows (one per tile), a ticket, the result slot,
@@ -415,8 +467,8 @@ struct FinishSlots {
 };
 
 // Grid reduction: every block stores its total in its row and takes a ticket; the last block
-// merges all rows -- thread t takes rows t, t + 256, ... in that order, then the block tree
-// merges the threads -- so the result depends on the rows and their count only, never on the
+// merges all rows -- rows r, r + 256, ... in that order, then the block tree merges those 256
+// -- so the result depends on the rows and their count only, never on the
 // order in which blocks finish.  It resolves, writes the result and publishes.
 //
 // Rows, tickets and results go past the L2 with agent- and system-scope accesses, ordered by
@@ -445,20 +497,7 @@ __device__ inline void grid_finish(const Acc &a, int b, int nb, const FinishSlot
     }
     __syncthreads();
     if (!last) return;
-    Acc m;
-    m.zero();
-    for (int r0 = opaque_tid(); r0 < nb; r0 += 2 * kBlock) {
-        // two rows per pass, both loaded before either is merged
-        Acc r1, r2;
-        acc_from_partial(F.tile_rows + (size_t)r0 * kPartialWords, r1);
-        const int s2 = r0 + kBlock;
-        if (s2 < nb) acc_from_partial(F.tile_rows + (size_t)s2 * kPartialWords, r2);
-        else r2.zero();
-        m.merge(r1);
-        if (s2 < nb) m.merge(r2);
-    }
-    __syncthreads();                         // lds and tot are reused
-    block_reduce_store(m, lds, tot);
+    rows_reduce_store(F.tile_rows, nb, lds, tot);
     __syncthreads();
     if (threadIdx.x == 0) {
         Acc total;

@@ -384,3 +384,18 @@ def test_special_values_occupancy(ctx, enc):
             compare_trace(ctx.trace(mid, x, 4096, P), o, f"{enc} specials state {s}")
     finally:
         ctx.release(mid)
+
+
+@pytest.mark.parametrize("n,lanes_log2", [(16, 10), (60097, 16), (65536, 16), (60097, 17), (65536, 17), (65536, 18), (65536, 20)])
+def test_reduction_over_few_and_many_blocks(ctx, tiny, tiny_map, n, lanes_log2):
+    """1, 235, 256, 470, 512, 1,024 and 4,096 blocks: the last block's passes of 256 rows with and
+    without a rest."""
+    mid, om = tiny
+    x, v = W.free_state(tiny_map, 117)
+    before = ctx.config(0)
+    try:
+        ctx.config(0, lane_target_log2=lanes_log2)
+        g = ctx.query(mid, x, v, n, P_TINY)
+    finally:
+        ctx.config(0, **before)
+    compare_query(g, oracle.query(om, x, v, n, P_TINY, nthreads=8), f"n={n}")
