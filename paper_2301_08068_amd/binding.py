@@ -189,9 +189,34 @@ def params_struct(p: Dict[str, float]) -> Params:
 
 
 def result_dict(r: Result) -> Dict:
-    return dict(f=np.array(r.f[:]), S=np.array(r.A[:]).reshape(3, 3), b=np.array(r.b[:]),
-                lam=np.array(r.lam[:]), rank=r.rank, n_hit=r.n_hit, n_contrib=r.n_contrib,
+    a = np.frombuffer(r, np.float64, 18).copy()
+    return dict(f=a[:3], S=a[3:12].reshape(3, 3), b=a[12:15],
+                lam=a[15:], rank=r.rank, n_hit=r.n_hit, n_contrib=r.n_contrib,
                 n_tie=r.n_tie, flags=r.flags, n_rays=r.n_rays, visits=r.visits)
+
+
+_RESULT = np.dtype([("f", "f8", 3), ("A", "f8", (3, 3)), ("b", "f8", 3), ("lam", "f8", 3), ("rank", "i4"),
+                    ("n_hit", "i4"), ("n_contrib", "i4"), ("n_tie", "i4"), ("flags", "u4"), ("n_rays", "i4"),
+                    ("visits", "i8")])
+assert _RESULT.itemsize == RESULT_BYTES
+
+
+def result_dicts(out, n: int) -> list:
+    """result_dict of the first n of an array of results, whole columns at a time (0.8 us a result
+    instead of 3.1): 64 results share the memory of their arrays, so one that is kept keeps at most
+    that much."""
+    if n < 4:                                # (5 us to set up)
+        return [result_dict(out[k]) for k in range(n)]
+    rows = []
+    raw = np.frombuffer(out, _RESULT, n)
+    for k in range(0, n, 64):
+        part = raw[k:k + 64]
+        rows += [dict(f=f, S=S, b=b, lam=lam, rank=rank, n_hit=n_hit, n_contrib=n_contrib, n_tie=n_tie,
+                      flags=flags, n_rays=n_rays, visits=visits)
+                 for f, S, b, lam, rank, n_hit, n_contrib, n_tie, flags, n_rays, visits in
+                 zip(*(part[c].copy() for c in ("f", "A", "b", "lam")),
+                     *(part[c].tolist() for c in ("rank", "n_hit", "n_contrib", "n_tie", "flags", "n_rays", "visits")))]
+    return rows
 
 
 def _stream_ptr(stream) -> Optional[int]:
@@ -404,7 +429,7 @@ def rmpc_query_batch(ctx: int, descs, map_params: Optional[Dict[str, float]],
     sp = C.byref(params_struct(scan_params)) if scan_params else None
     _check(_lib.rmpc_query_batch(C.c_void_p(ctx), descs, n, mp, sp, C.c_void_p(_stream_ptr(stream)), out),
            "rmpc_query_batch")
-    return [result_dict(r) for r in out]
+    return result_dicts(out, n)
 
 
 def rmpc_config_set(ctx: int, which: int, lookahead: int, lane_target_log2: int,
@@ -485,7 +510,7 @@ def rmpc_poll_completed(ctx: int, max_n: int = 256, raw: bool = False):
            "rmpc_poll_completed")
     if raw:
         return tickets[:n.value], lat[:n.value], out, n.value
-    return [(tickets[i], result_dict(out[i]), lat[i]) for i in range(n.value)]
+    return list(zip(tickets[:n.value], result_dicts(out, n.value), lat[:n.value]))
 
 
 def rmpc_server_stats(ctx: int) -> Dict[str, int]:

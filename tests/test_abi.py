@@ -104,3 +104,22 @@ def test_sparse_workload_round_trip():
     k = int(np.argmax(np.any(sm.values <= 0, axis=(1, 2, 3))))
     bx, by, bz = sm.coords[k] - np.asarray((-5, 3, -2))
     assert np.array_equal(sm.values[k], m.tsdf[8 * bz:8 * bz + 8, 8 * by:8 * by + 8, 8 * bx:8 * bx + 8])
+
+
+@pytest.mark.parametrize("n", [0, 1, 3, 4, 63, 64, 65, 130])
+def test_result_columns_equal_single_results(lib_path, n):
+    """The conversion of an array of results equals that of each result alone, byte for byte."""
+    from paper_2301_08068_amd import binding as B
+    rng = np.random.default_rng(n)
+    out = (B.Result * max(n, 1)).from_buffer_copy(rng.bytes(B.RESULT_BYTES * max(n, 1)))
+    rows = B.result_dicts(out, n)
+    assert len(rows) == n
+    for r, d in zip(out, rows):
+        one = B.result_dict(r)
+        assert list(d) == list(one)
+        for k in one:
+            assert type(d[k]) is type(one[k]) and np.shape(d[k]) == np.shape(one[k])
+            assert np.asarray(d[k]).tobytes() == np.asarray(one[k]).tobytes()
+        for k, field in (("f", r.f), ("S", r.A), ("b", r.b), ("lam", r.lam)):
+            assert d[k].tobytes() == bytes(field) and d[k].flags.writeable
+        assert (d["rank"], d["flags"], d["visits"]) == (r.rank, r.flags, r.visits)
