@@ -393,9 +393,11 @@ __device__ __forceinline__ BoxResult box_finish(const RayArgs &A, const BoxRay &
         const float Tz = R.rz != 0.0f ? box_crossing(uz, R.gsz, R.arz) : -kInf;
         const float t1 = fmaxf(Tx, fmaxf(Ty, Tz)), t2 = __builtin_amdgcn_fmed3f(Tx, Ty, Tz);
         int a = Tx == t1 ? 0 : (Ty == t1 ? 1 : 2);
-        double t64 = a == 0 ? face64(R.rx > 0.0f ? ux : -ux, A.g[0], R.rx)
-                            : (a == 1 ? face64(R.ry > 0.0f ? uy : -uy, A.g[1], R.ry)
-                                      : face64(R.rz > 0.0f ? uz : -uz, A.g[2], R.rz));
+        // (one division for the lanes of all axes)
+        const float gx = A.g[0], gy = A.g[1], gz = A.g[2];
+        const float ra = a == 0 ? R.rx : (a == 1 ? R.ry : R.rz), ga = a == 0 ? gx : (a == 1 ? gy : gz);
+        const int ua = a == 0 ? ux : (a == 1 ? uy : uz);
+        double t64 = face64(ra > 0.0f ? ua : -ua, ga, ra);
         if (t1 - t2 <= 1e-5f + 1e-6f * t1) {
             const double huge = __builtin_huge_val();
             const double X = R.rx != 0.0f ? signed_face64(ux, A.g[0], R.rx) : -huge;

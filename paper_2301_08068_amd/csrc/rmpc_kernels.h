@@ -162,12 +162,18 @@ struct ScanArgs {
     uint64_t seq;
 };
 
-// One query of a batched launch.
-struct BatchQuery {
+// One query of a batched launch, and what every tile of it needs first.
+struct BatchQueryHead {
     int32_t kind;                // 0: map query (ray), 1: scan query (scan)
     int32_t tile_begin;          // first tile of this query in the batch
     int32_t n_tiles;             // 256-lane tiles of this query
     int32_t pad;
+};
+struct BatchQuery {
+    union {
+        BatchQueryHead head;
+        struct { int32_t kind, tile_begin, n_tiles, pad; };
+    };
     union {
         RayArgs ray;
         ScanArgs scan;

@@ -651,7 +651,7 @@ __device__ __forceinline__ void sparse_tile(const RayArgs &A, int tile, int n_ti
             acc.visits = 1;
             acc.n_hit = 1;
             acc.n_contrib = contributes(A, rr.x, rr.y, rr.z, 0.0);
-            policy_accumulate(A.pol, rr.x, rr.y, rr.z, 0.0f, acc);
+            policy_set(A.pol, rr.x, rr.y, rr.z, 0.0f, acc);
         }
     } else {
         const SOut o = sparse_trace<K>(A, valid, seg, S, rr.x, rr.y, rr.z, slot0, occ0, m0);
@@ -662,7 +662,7 @@ __device__ __forceinline__ void sparse_tile(const RayArgs &A, int tile, int n_ti
                 const double d = sparse_distance<SV>(A, rr.x, rr.y, rr.z, o.d);
                 acc.n_hit = 1;
                 acc.n_contrib = contributes(A, rr.x, rr.y, rr.z, d);
-                policy_accumulate(A.pol, rr.x, rr.y, rr.z, (float)d, acc);
+                policy_set(A.pol, rr.x, rr.y, rr.z, (float)d, acc);
             }
         }
     }

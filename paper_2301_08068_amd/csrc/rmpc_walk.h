@@ -187,12 +187,17 @@ __device__ __forceinline__ float4 load_ray(const RayRec *rays, int j)
 //   p = max(0, xdot . r)^2,  q = eta_damp p / (d/nu_damp + eps)        (|f_damp| / |r|)
 //   sigma = q / (q|r| + c log(1 + exp(-2 c q|r|)))                      (s(f_damp) = -sigma r)
 //   a = w_r(d) sigma^2,  phi = eta_rep exp(-d/nu_rep) + q,  w_r(d) = (1 - d/r)^2 on [0, r].
-__device__ __forceinline__ void policy_accumulate(const PolicyF &P, float rx, float ry, float rz,
-                                                  float d, Acc &acc)
+// Returns false when every term is zero: a ray along or away from which the robot does not move
+// (half of all, and of whole waves: neighbouring lanes hold neighbouring directions), or a hit
+// beyond the radius.  Nothing but zeros is left out: parameters and quotients that would make a
+// term NaN are computed.
+__device__ __forceinline__ bool policy_terms(const PolicyF &P, float rx, float ry, float rz, float d, float (&x)[9])
 {
     const float vr = P.vx * rx + P.vy * ry + P.vz * rz;
     const float pp = vr > 0.0f ? vr * vr : 0.0f;
     const float q = P.eta_damp * pp / (d * P.inv_nu_damp + P.eps);
+    const bool tame = P.c >= 1e-30f && P.eta_rep <= 1e30f;      // no quotient 0 / 0, no product 0 inf below
+    if (tame && (q == 0.0f || (d > P.radius && q < 1e30f))) return false;
     const float rn2 = rx * rx + ry * ry + rz * rz;
     const float mq = q * sqrtf(rn2);
     const float sigma = q / (mq + P.c * log1pf(expf(-2.0f * P.c * mq)));
@@ -201,15 +206,38 @@ __device__ __forceinline__ void policy_accumulate(const PolicyF &P, float rx, fl
     const float a = w * sigma * sigma;
     const float phi = P.eta_rep * expf(-d * P.inv_nu_rep) + q;
     const float bb = -a * rn2 * phi;
-    csum_add(acc.s[0], acc.c[0], a * rx * rx);
-    csum_add(acc.s[1], acc.c[1], a * rx * ry);
-    csum_add(acc.s[2], acc.c[2], a * rx * rz);
-    csum_add(acc.s[3], acc.c[3], a * ry * ry);
-    csum_add(acc.s[4], acc.c[4], a * ry * rz);
-    csum_add(acc.s[5], acc.c[5], a * rz * rz);
-    csum_add(acc.s[6], acc.c[6], bb * rx);
-    csum_add(acc.s[7], acc.c[7], bb * ry);
-    csum_add(acc.s[8], acc.c[8], bb * rz);
+    x[0] = a * rx * rx;
+    x[1] = a * rx * ry;
+    x[2] = a * rx * rz;
+    x[3] = a * ry * ry;
+    x[4] = a * ry * rz;
+    x[5] = a * rz * rz;
+    x[6] = bb * rx;
+    x[7] = bb * ry;
+    x[8] = bb * rz;
+    return true;
+}
+
+__device__ __forceinline__ void policy_accumulate(const PolicyF &P, float rx, float ry, float rz, float d, Acc &acc)
+{
+    float x[9];
+    if (!policy_terms(P, rx, ry, rz, d, x)) return;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) csum_add(acc.s[k], acc.c[k], x[k]);
+}
+
+// policy_accumulate into zero sums: what csum_add leaves there (x - x: a term that is not finite
+// makes the sum NaN).
+__device__ __forceinline__ void policy_set(const PolicyF &P, float rx, float ry, float rz, float d, Acc &acc)
+{
+    float x[9];
+    if (!policy_terms(P, rx, ry, rz, d, x)) return;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+#pragma clang fp contract(off)
+        acc.s[k] = 0.0f + x[k];
+        acc.c[k] = x[k] - x[k];
+    }
 }
 
 // Exact "non-zero metric" predicate in float64: d < radius and xdot . r > 0, with the dot
@@ -241,21 +269,6 @@ __device__ __forceinline__ FinishSlots single_slots(float *partials, uint32_t *t
     F.done = done;
     F.seq = seq;
     return F;
-}
-
-// A copy of *p made of wave-uniform words (readfirstlane), so that the compiler keeps it in
-// scalar registers; p must be the same for every lane.
-template <typename T>
-__device__ __forceinline__ T load_uniform(const T *p)
-{
-    static_assert(sizeof(T) % 4 == 0, "whole words");
-    uint32_t w[sizeof(T) / 4];
-    const uint32_t *src = reinterpret_cast<const uint32_t *>(p);
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = __builtin_amdgcn_readfirstlane(src[i]);
-    T out;
-    __builtin_memcpy(&out, w, sizeof(T));
-    return out;
 }
 
 // The continuous TSDF: trilinear interpolation of the stored values, which sit at the voxel

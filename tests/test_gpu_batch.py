@@ -187,3 +187,19 @@ def test_tuner_picks_and_caches(env, paper_map, tmp_path):
     o = oracle.query(oracle.OracleMap.from_voxelmap(paper_map), qs[0]["x"], qs[0]["v"], qs[0]["n"], P_PAPER,
                      nthreads=8)
     compare_query(res[0], o, "tuned batch")
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128, 129, 1000, 4096])
+def test_every_tile_finds_its_query(env, tiny_map, n):
+    """Batches around the multiples of 64 queries, of one, two and five tiles a query: each equals
+    the query alone, bit for bit (the same lanes per ray in both configurations)."""
+    ctx, maps = env
+    states = [W.free_state(tiny_map, 100 + k) for k in range(7)]
+    rays = [16, 1, 32, 80]
+    kinds = [(k % 7, rays[k % 4]) for k in range(n)]
+    got = ctx.query_batch([dict(kind="map", map_id=maps["tiny"], n=r, x=states[s][0], v=states[s][1])
+                           for s, r in kinds], P_TINY, None)
+    want = {(s, r): ctx.query(maps["tiny"], *states[s], r, P_TINY) for s, r in set(kinds)}
+    for k, (g, key) in enumerate(zip(got, kinds)):
+        for f in ("S", "b", "f", "n_hit", "visits"):
+            assert np.array_equal(g[f], want[key][f]), (k, key, f)
