@@ -176,9 +176,12 @@ typedef struct {
  *     voxel (i, j, l) (0..7 each) at k * 512 + i + 8 j + 64 l.  Host memory when
  *     values_on_device == 0, device memory otherwise.  Only read during the call.
  *   map_id_out: receives the map's id (the same id space as dense maps).
- * The library keeps the values, a 512-bit occupancy mask per block and an open-addressed hash
- * table (a power of two of at least 16 n_blocks entries of 16 bytes, at least 1024) from block
- * coordinates to slots: 16 capacity + 64 n_blocks + 512 elem_bytes n_blocks arena bytes.
+ * The library keeps the values, a 512-bit occupancy mask per block and, in 16 capacity bytes
+ * (capacity: a power of two, at least 16 n_blocks and 1024), an open-addressed hash table from block
+ * coordinates to slots: 16 capacity + 64 n_blocks + 512 elem_bytes n_blocks arena bytes.  Where the
+ * box around the stored blocks lies within 2^16 voxels of the origin and is small enough, a
+ * quarter of the capacity holds the table and the rest an index of the box (4 bytes per block of
+ * it, 128 bytes per stored block), which walks use.
  * More than 2^27 blocks: RMPC_E_INVALID.
  * rmpc_query and rmpc_trace_debug accept sparse maps (launch configuration
  * RMPC_CONFIG_SPARSE; the start may lie anywhere whose voxels within max_range keep
@@ -186,7 +189,7 @@ typedef struct {
  * free_value outside the stored blocks); rmpc_trace_debug then reports a hit as
  * slot * 512 + (i + 8 j + 64 l) of the hit voxel in its block.  Batched queries, the serving
  * loop and rollouts (single and batched) take sparse maps too: in a batch a sparse query uses
- * the batch's segmentation with block rounds of 4 steps.  The distance transform takes dense
+ * the batch's segmentation (and without an index block rounds of 4 steps).  The distance transform takes dense
  * maps only (RMPC_E_INVALID).  Blocking.
  * Errors: RMPC_E_INVALID (NULL, n_blocks, dtype, voxel size, free_value, coordinates, a
  * repeated block), RMPC_E_NOMEM (arena full), RMPC_E_HIP.
@@ -290,8 +293,8 @@ typedef struct {
 #define RMPC_CONFIG_SPARSE 2    /* rmpc_query and rmpc_trace_debug on sparse maps (blocks_per_cu and
                                    use_graph unused) */
 typedef struct {
-    int32_t lookahead;          /* single queries on sparse maps: block steps planned per round; 4, 8
-                                   or 16 (walks on dense maps do not plan ahead) */
+    int32_t lookahead;          /* single queries on sparse maps without an index: block steps planned
+                                   per round; 4, 8 or 16 (other walks do not plan ahead) */
     int32_t lane_target_log2;   /* split rays into segments until a query has ~2^this lanes (10..22) */
     int32_t blocks_per_cu;      /* batches: resident blocks per CU of the persistent kernel (0 = max) */
     int32_t use_graph;          /* batches: 1 = replay the launch from a captured hipGraph */

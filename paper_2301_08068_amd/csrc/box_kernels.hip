@@ -50,9 +50,9 @@ constexpr int kSets = 6 + 3 * kSteps + 2 * kSteps + 6 + 3 + 1;
 
 __host__ __device__ inline int32_t row_words(const MapView &m) { return (m.nbx + 63) >> 6; }
 __host__ __device__ inline int64_t set_words(const MapView &m) { return (int64_t)row_words(m) * m.nby * m.nbz; }
-__host__ __device__ inline int64_t mask_bytes(const MapView &m)
+inline int64_t mask_bytes(const MapView &m)
 {
-    return ((int64_t)((m.nbx + 3) & ~3) * m.nby * m.nbz + 255) / 256 * 256;
+    return ((int64_t)box_mask_pitch(m) * m.nby * m.nbz + 255) / 256 * 256;
 }
 
 Scratch scratch_at(const MapView &m, uint8_t *p)
@@ -60,7 +60,7 @@ Scratch scratch_at(const MapView &m, uint8_t *p)
     Scratch s;
     s.mask = p;
     s.words = set_words(m);
-    s.pitch = (m.nbx + 3) & ~3;
+    s.pitch = box_mask_pitch(m);
     s.w = row_words(m);
     s.layer = reinterpret_cast<uint64_t *>(p + mask_bytes(m));
     s.cz = s.layer + 6 * s.words;
@@ -540,6 +540,16 @@ void launch_bricks(const BoxArgs &a, uint8_t *mask, int32_t pitch, hipStream_t s
         copy_rest_kernel<DT><<<(unsigned)m.ny * (unsigned)m.nz, 256, 0, s>>>(m, static_cast<const T *>(a.src), dst);
 }
 
+void launch_extents(const MapView &m, const Scratch &p, hipStream_t s)
+{
+    if (p.words == 0) return;
+    layer_bits_kernel<<<blocks_for(16 * p.words), 256, 0, s>>>(m, p);
+    planes_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
+    cubes_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
+    select_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
+    expand_kernel<<<(unsigned)((p.words + 3) / 4), 256, 0, s>>>(m, p, const_cast<uint16_t *>(m.box));
+}
+
 template <int DT>
 void launch_boxes_dt(const BoxArgs &a, hipStream_t s)
 {
@@ -554,12 +564,7 @@ void launch_boxes_dt(const BoxArgs &a, hipStream_t s)
     const Scratch p = scratch_at(m, a.scratch);
     if (wide) launch_bricks<DT, 2, false>(a, p.mask, p.pitch, s);
     else launch_bricks<DT, 1, false>(a, p.mask, p.pitch, s);
-    if (p.words == 0) return;
-    layer_bits_kernel<<<blocks_for(16 * p.words), 256, 0, s>>>(m, p);
-    planes_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
-    cubes_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
-    select_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
-    expand_kernel<<<(unsigned)((p.words + 3) / 4), 256, 0, s>>>(m, p, const_cast<uint16_t *>(m.box));
+    launch_extents(m, p, s);
 }
 
 }  // namespace
@@ -568,6 +573,10 @@ size_t box_scratch_bytes(const MapView &m)
 {
     return set_words(m) == 0 ? 0 : (size_t)(mask_bytes(m) + 8 * kSets * set_words(m));
 }
+
+int32_t box_mask_pitch(const MapView &m) { return (m.nbx + 3) & ~3; }
+
+void launch_cell_boxes(const MapView &m, uint8_t *scratch, hipStream_t s) { launch_extents(m, scratch_at(m, scratch), s); }
 
 hipError_t launch_map_boxes(const BoxArgs &a, hipStream_t s)
 {

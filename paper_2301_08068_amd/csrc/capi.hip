@@ -201,6 +201,14 @@ rmpc_status setup_sparse_query(rmpc_ctx *ctx, const MapEntry &me, const double x
     ray_list(ctx, n_rays, &A.rays, &A.n_list);
     A.sparse = 1;
     A.sp = me.sview;
+    double span = tmax + 2.0;
+    for (int a = 0; a < 3; ++a) span = std::max(span, std::fabs((double)A.g[a]) + tmax + 2.0);
+    if (me.sview.index && span <= (double)rmpc::kIndexSpan) {
+        A.sparse = 2;
+        A.map.nx = A.map.ny = A.map.nz = rmpc::kFarVoxel;
+        A.map.lo = -rmpc::kFarVoxel;
+        A.map.span = (int32_t)span;
+    }
     A.subvoxel = params->subvoxel != 0;
     A.n_rays = n_rays;
     A.start_flags = start_flags;
@@ -337,6 +345,7 @@ rmpc_status dense_layout(const rmpc_map_desc &d, rmpc::MapView &v, uint64_t &n_a
     if (n_log >= (1ull << 31)) return fail(RMPC_E_INVALID, "grid has 2^31 voxels or more (linear indices are int32)");
     std::memset(&v, 0, sizeof v);
     v.nx = d.nx; v.ny = d.ny; v.nz = d.nz; v.dtype = d.dtype;
+    v.span = std::max(d.nx, std::max(d.ny, d.nz));
     const uint64_t cells = (uint64_t)(d.nx >> rmpc::kCellLog2) * (d.ny >> rmpc::kCellLog2) * (d.nz >> rmpc::kCellLog2);
     const uint64_t bricks = (uint64_t)(d.nx >> rmpc::kBrickLog2) * (d.ny >> rmpc::kBrickLog2) * (d.nz >> rmpc::kBrickLog2);
     const uint64_t cell_base = (n_log + 255) / 256 * 256;
@@ -611,6 +620,40 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
 
 constexpr uint64_t kTableSlack = 16;       // block-table entries per stored block, at least
 
+// The box of blocks around n blocks, if its coordinates stay within what a map's index may span.
+bool index_box(const int32_t *coords, int32_t n, int32_t lo[3], int32_t nb[3])
+{
+    const int32_t limit = rmpc::kIndexSpan >> rmpc::kBlockLog2;
+    int32_t hi[3];
+    for (int a = 0; a < 3; ++a) lo[a] = hi[a] = coords[a];
+    for (int32_t k = 1; k < n; ++k)
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = std::min(lo[a], coords[3 * (size_t)k + a]);
+            hi[a] = std::max(hi[a], coords[3 * (size_t)k + a]);
+        }
+    for (int a = 0; a < 3; ++a) {
+        if (lo[a] < -limit || hi[a] >= limit) return false;
+        nb[a] = hi[a] - lo[a] + 1;
+    }
+    return true;
+}
+
+// Device memory for the duration of a call.
+struct DeviceScratch {
+    uint8_t *p = nullptr;
+    bool get(size_t n)
+    {
+        if (hipMalloc(reinterpret_cast<void **>(&p), n) == hipSuccess) return true;
+        (void)hipGetLastError();
+        p = nullptr;
+        return false;
+    }
+    ~DeviceScratch()
+    {
+        if (p) (void)hipFree(p);
+    }
+};
+
 rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, const int32_t *block_coords_host,
                                    const void *values, int values_on_device, void *hip_stream, int32_t *map_id_out)
 {
@@ -631,10 +674,31 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
     // the table: a power of two of at least kTableSlack times the blocks, filled on the host by
     // linear probing.  Most lookups are of blocks that are not stored; at a load factor of 1/2
     // nearly half of them met another key at their first entry and probed on (a further
-    // dependent load, and the end of a block round), at 1/16 few do
+    // dependent load, and the end of a block round), at 1/16 few do.  A map that has an index walks by
+    // that and only falls back on the table (far from the origin; values of sub-voxel distances):
+    // its table has a quarter of the entries, and index and bricks take no more than the rest.
     uint64_t cap64 = 1024;
     while (cap64 < kTableSlack * (uint64_t)n) cap64 *= 2u;
     if (cap64 > (1ull << 31)) return fail(RMPC_E_INVALID, "too many blocks for the block table");
+    rmpc::SparseView v;
+    std::memset(&v, 0, sizeof v);
+    v.n_slots = n;
+    const size_t table_bytes = sizeof(rmpc::HashEntry) * (size_t)cap64;
+    size_t index_at = 0, bricks_at = 0, scratch_bytes = 0;
+    bool indexed = index_box(block_coords_host, n, v.lo, v.nb);
+    if (indexed) {
+        index_at = sizeof(rmpc::HashEntry) * (size_t)(cap64 / 4);
+        bricks_at = index_at + (sizeof(uint32_t) * (size_t)v.nb[0] * v.nb[1] * v.nb[2] + 255) / 256 * 256;
+        indexed = bricks_at + sizeof(uint16_t) * 64 * (size_t)n <= table_bytes;
+    }
+    DeviceGuard dg(ctx->device);
+    hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    DeviceScratch scratch;
+    if (indexed) {
+        scratch_bytes = rmpc::sparse_index_scratch_bytes(v);
+        indexed = scratch.get(scratch_bytes);
+    }
+    if (indexed) cap64 /= 4;
     const uint32_t cap = (uint32_t)cap64;
     std::vector<rmpc::HashEntry> table(cap, rmpc::HashEntry{rmpc::kEmptyKey, -1, 0u});
     const uint32_t mask = cap - 1u;
@@ -653,7 +717,7 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
     }
     const size_t eb = elem_bytes(desc->dtype);
     size_t o_table, o_occ, o_vals;
-    if (!ctx->alloc.alloc(sizeof(rmpc::HashEntry) * (size_t)cap, &o_table))
+    if (!ctx->alloc.alloc(table_bytes, &o_table))
         return fail(RMPC_E_NOMEM, "arena full (sparse map table)");
     if (!ctx->alloc.alloc(sizeof(uint64_t) * 8 * (size_t)n, &o_occ)) {
         ctx->alloc.release(o_table);
@@ -664,14 +728,13 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
         ctx->alloc.release(o_occ);
         return fail(RMPC_E_NOMEM, "arena full (sparse map values)");
     }
-    DeviceGuard dg(ctx->device);
-    hipStream_t s = static_cast<hipStream_t>(hip_stream);
     rmpc::HashEntry *table_dev = reinterpret_cast<rmpc::HashEntry *>(ctx->arena + o_table);
-    rmpc::SparseView v;
-    std::memset(&v, 0, sizeof v);
     v.table = table_dev;
     v.table_mask = mask;
-    v.n_slots = n;
+    if (indexed) {
+        v.index = reinterpret_cast<const uint32_t *>(ctx->arena + o_table + index_at);
+        v.bricks = reinterpret_cast<const uint16_t *>(ctx->arena + o_table + bricks_at);
+    }
     v.occ = reinterpret_cast<const uint64_t *>(ctx->arena + o_occ);
     v.values = ctx->arena + o_vals;
     v.dtype = desc->dtype;
@@ -682,6 +745,7 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
         e = hipMemcpyAsync(ctx->arena + o_vals, values, eb * rmpc::kBlockVoxels * (size_t)n,
                            values_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = rmpc::launch_sparse_masks(v, table_dev, s);
+    if (e == hipSuccess && indexed) e = rmpc::launch_sparse_index(v, scratch.p, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipStreamSynchronize(s);

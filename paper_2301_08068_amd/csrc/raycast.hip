@@ -25,13 +25,38 @@ namespace rmpc {
 
 namespace {
 
+// Slot of the block of voxel (vx, vy, vz) if it has an occupied voxel, else -1.
+__device__ __forceinline__ int indexed_slot(const SparseView &S, int vx, int vy, int vz)
+{
+    const uint32_t ix = (uint32_t)((vx >> kBlockLog2) - S.lo[0]), iy = (uint32_t)((vy >> kBlockLog2) - S.lo[1]),
+                   iz = (uint32_t)((vz >> kBlockLog2) - S.lo[2]);
+    if (ix >= (uint32_t)S.nb[0] || iy >= (uint32_t)S.nb[1] || iz >= (uint32_t)S.nb[2]) return -1;
+    const uint32_t e = S.index[ix + (uint32_t)S.nb[0] * (iy + __umul24(iz, (uint32_t)S.nb[1]))];
+    return e & kBlockOccupied ? (int)(e & ~kBlockOccupied) : -1;
+}
+
+// What a trace reports for an occupied voxel: its index in the grid, on a sparse map its slot and
+// its place in the block.
+template <int DT>
+__device__ __forceinline__ int hit_index(const RayArgs &A, int vx, int vy, int vz)
+{
+    if constexpr (is_indexed(DT))
+        return indexed_slot(A.sp, vx, vy, vz) * kBlockVoxels + (vx & 7) + 8 * (vy & 7) + 64 * (vz & 7);
+    return vx + A.map.nx * (vy + A.map.ny * vz);
+}
+
 // The start voxel is occupied: every ray hits at distance 0 (same address for all lanes).
 template <int DT>
 __device__ __forceinline__ bool start_occupied(const RayArgs &A)
 {
+    if constexpr (is_indexed(DT)) {
+        const SparseView &S = A.sp;
+        const int slot = indexed_slot(S, A.v0[0], A.v0[1], A.v0[2]);
+        return slot >= 0 && ((S.occ[(size_t)slot * kLayers + (A.v0[2] & 7)] >> ((A.v0[0] & 7) + 8 * (A.v0[1] & 7))) & 1ull) != 0;
+    }
     const MapView &m = A.map;
     const int bx = A.v0[0] >> kBrickLog2, by = A.v0[1] >> kBrickLog2, bz = A.v0[2] >> kBrickLog2;
-    if constexpr (DT != RMPC_OCC_U8) {
+    if constexpr (DT != RMPC_OCC_U8 && !is_indexed(DT)) {
         if (bx >= m.nbx || by >= m.nby || bz >= m.nbz)
             return Voxel<DT>::occ(static_cast<const typename Voxel<DT>::T *>(m.data)[(uint32_t)A.lin0]);
     }
@@ -47,7 +72,7 @@ struct RayOut {
     double d;
     uint32_t flags;
     int visits_lane;                  // the ray's visit count in one lane of its group, else 0
-    int hit_lin;                      // debug
+    int fx, fy, fz;                   // the hit voxel (debug)
 };
 
 // Walk one ray with the S lanes of its group; every lane of the wave must call this.
@@ -55,7 +80,7 @@ template <int DT, bool PART>
 __device__ __forceinline__ RayOut trace_group(const RayArgs &A, bool valid, int seg, int S,
                                               float rx, float ry, float rz)
 {
-    const BoxRay R = box_ray(A, rx, ry, rz);
+    const BoxRay R = box_ray<DT>(A, rx, ry, rz);
     BoxWalk w;
     bool last;
     float t_lo, t_hi, t_first;
@@ -92,9 +117,9 @@ __device__ __forceinline__ RayOut trace_group(const RayArgs &A, bool valid, int 
     const uint64_t rm = (__ballot(keep && e.rtie) >> base) & seg_bits;
     o.report = valid && seg == (h < S ? h : 0);
     o.hit = hit && seg == h;
+    o.fx = e.fx; o.fy = e.fy; o.fz = e.fz;
     o.d = o.hit ? e.d : __builtin_huge_val();
     o.flags = A.start_flags | (tm ? kRayTie : 0u) | (rm ? kRayRangeTie : 0u);
-    o.hit_lin = o.hit ? e.fx + A.map.nx * (e.fy + A.map.ny * e.fz) : -1;
     return o;
 }
 
@@ -118,8 +143,12 @@ struct DenseField {
 template <int DT>
 __device__ __forceinline__ double subvoxel_distance(const RayArgs &A, float rx, float ry, float rz, double d)
 {
-    const DenseField<DT> f{static_cast<const typename Voxel<DT>::T *>(A.map.data), A.map.nx, A.map.ny, A.map.nz};
-    return subvoxel_at(A, f, rx, ry, rz, d);
+    if constexpr (DT == kIndexedF32) return sparse_distance<kSvF32>(A, rx, ry, rz, d);
+    else if constexpr (DT == kIndexedF16) return sparse_distance<kSvF16>(A, rx, ry, rz, d);
+    else {
+        const DenseField<DT> f{static_cast<const typename Voxel<DT>::T *>(A.map.data), A.map.nx, A.map.ny, A.map.nz};
+        return subvoxel_at(A, f, rx, ry, rz, d);
+    }
 }
 
 // One 256-lane tile of a map query: lane -> (ray position, segment).  Waves stay whole (the
@@ -153,7 +182,7 @@ __device__ __forceinline__ void ray_tile(const RayArgs &A, int tile, int n_tiles
             acc.n_tie = (o.flags & kRayTie) != 0;
             if (o.hit) {
                 double d = o.d;
-                if constexpr (DT != RMPC_OCC_U8)
+                if constexpr (DT != RMPC_OCC_U8 && DT != kIndexed)
                     if (A.subvoxel) d = subvoxel_distance<DT>(A, rx, ry, rz, d);
                 acc.n_hit = 1;
                 acc.n_contrib = contributes(A, rx, ry, rz, d);
@@ -207,7 +236,7 @@ __device__ __forceinline__ void scan_tile(const ScanArgs &A, int tile, int n_til
 
 // One map query per launch; block b takes tile xcd_tile(b).
 template <int DT, bool PART>
-__global__ void __launch_bounds__(kBlock, 4) raycast_rmp_kernel(RayArgs A)
+__global__ void __launch_bounds__(kBlock, DT == kIndexedF32 || DT == kIndexedF16 ? 2 : 4) raycast_rmp_kernel(RayArgs A)
 {
     __shared__ float lds[kReduceLdsWords];
     ray_tile<DT, PART>(A, xcd_tile(blockIdx.x, gridDim.x), gridDim.x,
@@ -272,6 +301,10 @@ __global__ void __launch_bounds__(kBlock, 4) batch_kernel(BatchArgs B)
         const int t = tile - head.tile_begin;
         if (head.kind == 0) {
             const RayArgs &A = Q.ray;
+            if (A.sparse == 2) {
+                ray_tile<kIndexed, false>(A, t, head.n_tiles, F, lds);
+                continue;
+            }
             if (A.sparse) {
                 // block rounds of 4 steps on sparse maps (their best), no sub-voxel refinement
                 // (batches refuse it on sparse maps)
@@ -311,7 +344,7 @@ __global__ void __launch_bounds__(kBlock, 2) trace_debug_kernel(RayArgs A)
     const float rx = rr.x, ry = rr.y, rz = rr.z;
     if (start_occupied<DT>(A)) {
         if (valid && seg == 0) {
-            A.dbg_hit[i] = A.lin0;
+            A.dbg_hit[i] = hit_index<DT>(A, A.v0[0], A.v0[1], A.v0[2]);
             A.dbg_dist[i] = 0.0;
             A.dbg_flags[i] = (uint8_t)(A.start_flags | kRayInCollision);
             if (A.dbg_visits) A.dbg_visits[i] = 1;
@@ -323,9 +356,9 @@ __global__ void __launch_bounds__(kBlock, 2) trace_debug_kernel(RayArgs A)
     int v = o.visits_lane;
     for (int off = 1; off < S; off <<= 1) v += __shfl_xor(v, off, kWave);
     if (o.report) {
-        A.dbg_hit[i] = o.hit ? o.hit_lin : -1;
+        A.dbg_hit[i] = o.hit ? hit_index<DT>(A, o.fx, o.fy, o.fz) : -1;
         double d = o.d;
-        if constexpr (DT != RMPC_OCC_U8)
+        if constexpr (DT != RMPC_OCC_U8 && DT != kIndexed)
             if (A.subvoxel && o.hit) d = subvoxel_distance<DT>(A, rx, ry, rz, d);
         A.dbg_dist[i] = d;
         A.dbg_flags[i] = (uint8_t)o.flags;
@@ -397,6 +430,11 @@ hipError_t launch_raycast(const RayArgs &A, hipStream_t s, bool debug, hipEvent_
 {
     const int grid = ray_grid_blocks(A.n_list * A.segments);
     const bool part = A.map.partial != 0;
+    if (A.sparse) {
+        if (!A.subvoxel) return launch_dt<kIndexed, false>(A, grid, s, debug, e0, e1);
+        return A.sp.dtype == RMPC_TSDF_F32 ? launch_dt<kIndexedF32, false>(A, grid, s, debug, e0, e1)
+                                           : launch_dt<kIndexedF16, false>(A, grid, s, debug, e0, e1);
+    }
     switch (A.map.dtype) {
     case RMPC_TSDF_F32:
         return part ? launch_dt<RMPC_TSDF_F32, true>(A, grid, s, debug, e0, e1)

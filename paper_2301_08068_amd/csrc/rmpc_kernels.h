@@ -50,7 +50,10 @@ struct MapView {
     int32_t nx, ny, nz, dtype;
     int32_t nbx, nby, nbz;       // bricks with an entry along each axis
     int32_t partial;             // non-zero: an odd last layer of voxels has no entries
+    int32_t lo;                  // first voxel along every axis (0; a sparse map's box walk: -kFarVoxel)
+    int32_t span;                // bound of a walk's coordinates (for the float32 error)
 };
+constexpr int32_t kFarVoxel = 1 << 24;
 
 // A sparse map: 8 x 8 x 8-voxel blocks stored where the world has content (every other voxel
 // is free), found through an open-addressed hash table from block coordinates to slots.
@@ -88,6 +91,10 @@ __host__ __device__ inline uint32_t block_hash(uint64_t k, uint32_t mask)
     return (uint32_t)k & mask;
 }
 
+constexpr uint32_t kBlockOccupied = 1u << 31;
+// A map's index is built, and a query uses it, where no coordinate exceeds this (in float32 terms:
+// 1/60 of a voxel).
+constexpr int32_t kIndexSpan = 1 << 16;
 struct SparseView {
     const HashEntry *table;      // table_mask + 1 entries (a power of two, at least twice the blocks)
     uint32_t table_mask;
@@ -97,6 +104,11 @@ struct SparseView {
     int32_t dtype;
     int32_t pad;
     double free_value;           // TSDF maps: the field's value outside the stored blocks
+    // the box walk's index (null: the map has none), over the blocks of a box that holds all stored
+    // ones: block lo + (x, y, z) at x + nb[0] (y + nb[1] z)
+    const uint32_t *index;       // kBlockOccupied | slot, or a free block's box of free blocks: the bits of box_extents
+    const uint16_t *bricks;      // 64 brick entries per slot (as a dense map's; bricks of other slots count as well)
+    int32_t lo[3], nb[3];
 };
 
 // Policy constants in float32 (reciprocals precomputed on the host).
@@ -116,7 +128,7 @@ struct alignas(16) RayRec {
 struct RayArgs {
     MapView map;                 // dense maps
     SparseView sp;               // sparse maps
-    int32_t sparse;
+    int32_t sparse;              // 0: a dense map, 1: a sparse one by its table, 2: by its index
     const RayRec *rays;          // ordered ray list; entries with i >= n_rays are skipped
     int32_t n_list;              // length of `rays` (>= n_rays)
     int32_t n_rays;
@@ -272,6 +284,14 @@ hipError_t launch_sparse(const RayArgs &a, hipStream_t s, bool debug, hipEvent_t
                          hipEvent_t ev1 = nullptr);
 // Occupancy masks of n sparse blocks from their values, and the tables' occupied flags.
 hipError_t launch_sparse_masks(const SparseView &v, HashEntry *table, hipStream_t s);
+// The index and the brick entries of a sparse map whose masks and flags are written.  scratch:
+// sparse_index_scratch_bytes, 256-byte aligned.
+size_t sparse_index_scratch_bytes(const SparseView &v);
+hipError_t launch_sparse_index(const SparseView &v, uint8_t *scratch, hipStream_t s);
+// The boxes of a grid of nbx x nby x nbz cells from their occupancy, one byte a cell (0 or 255) at
+// the start of scratch (zeroed by the caller; rows of box_mask_pitch bytes), written to box.
+int32_t box_mask_pitch(const MapView &m);
+void launch_cell_boxes(const MapView &m, uint8_t *scratch, hipStream_t s);
 // Persistent fused batch: `blocks` resident blocks pull tiles from a counter.
 hipError_t launch_batch(const BatchArgs &a, int blocks, hipStream_t s);
 // Resident blocks per CU of the batch kernel.

@@ -1,6 +1,6 @@
 // sparse.hip -- the raycast-and-policy query on a sparse block map: the single-query and debug
 // kernels over the walk of rmpc_sparse.h, and the kernels that build a sparse map's occupancy
-// masks and table flags at upload.
+// masks, table flags, index and brick entries at upload.
 
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
@@ -85,6 +85,121 @@ __global__ void sparse_flag_kernel(SparseView v, HashEntry *table)
     e.occupied = any != 0 ? 1u : 0u;
 }
 
+// The index's occupied blocks, from the table: their slots, and 255 in the cells' occupancy.
+__global__ void __launch_bounds__(256) index_slots_kernel(SparseView v, uint32_t *index, uint8_t *mask, int32_t pitch)
+{
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i > v.table_mask) return;
+    const HashEntry e = v.table[i];
+    if (e.key == kEmptyKey || e.occupied == 0u) return;
+    const uint32_t bits = (1u << kBlockCoordBits) - 1u;
+    const int x = (int)((uint32_t)e.key & bits) - kBlockCoordBias - v.lo[0];
+    const int y = (int)((uint32_t)(e.key >> 21) & bits) - kBlockCoordBias - v.lo[1];
+    const int z = (int)((uint32_t)(e.key >> 42) & bits) - kBlockCoordBias - v.lo[2];
+    const int64_t row = y + (int64_t)v.nb[1] * z;
+    index[x + v.nb[0] * row] = kBlockOccupied | (uint32_t)e.slot;
+    mask[x + pitch * row] = 255u;
+}
+
+// The other blocks' boxes.
+__global__ void __launch_bounds__(256) index_boxes_kernel(uint32_t *index, const uint16_t *box, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n && index[i] == 0u) index[i] = box[i];
+}
+
+// A slot's 64 bricks (a wave): their voxels' occupancy, and one bit each in bits[slot].
+__global__ void __launch_bounds__(256) brick_masks_kernel(SparseView v, uint16_t *bricks, uint64_t *bits)
+{
+    const int slot = blockIdx.x * 4 + (threadIdx.x >> 6), b = threadIdx.x & 63;
+    if (slot >= v.n_slots) return;
+    const uint64_t *w = v.occ + (size_t)slot * kLayers + 2 * (b >> 4);
+    const int at = 2 * (b & 3) + 16 * ((b >> 2) & 3);
+    uint32_t mask = 0;
+#pragma unroll
+    for (int dz = 0; dz < 2; ++dz)
+        mask |= (uint32_t)(((w[dz] >> at) & 3u) | (((w[dz] >> (at + 8)) & 3u) << 2)) << (4 * dz);
+    const uint64_t any = __ballot(mask != 0u);
+    bricks[(size_t)slot * 64 + b] = (uint16_t)mask;
+    if (b == 0) bits[slot] = any;
+}
+
+// The brick entries of the occupied blocks (a wave each): an occupied brick's voxels, without a
+// free layer; around a free one the free cube, half extent 1 .. 5 (what the 27 blocks around tell),
+// or where it is narrow (below 3) the widest slab one brick thick.
+__global__ void __launch_bounds__(256) brick_boxes_kernel(SparseView v, uint16_t *bricks, const uint64_t *bits)
+{
+    __shared__ uint32_t rows[4][144];                     // 12 bricks along x, for y and z from 4 before the block on
+    const int64_t n = (int64_t)v.nb[0] * v.nb[1] * v.nb[2];
+    const int64_t at = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const uint32_t e = at < n ? v.index[at] : 0u;
+    const bool mine = (e & kBlockOccupied) != 0u;
+    uint32_t *row = rows[threadIdx.x >> 6];
+    if (mine) {
+        const int64_t yz = at / v.nb[0];
+        const int x = (int)(at - yz * v.nb[0]), z = (int)(yz / v.nb[1]), y = (int)(yz - (int64_t)z * v.nb[1]);
+        // lanes 0 .. 26: a neighbouring block's bricks
+        uint64_t near = 0;
+        if (lane < 27) {
+            const int px = x + lane % 3 - 1, py = y + lane / 3 % 3 - 1, pz = z + lane / 9 - 1;
+            if ((unsigned)px < (unsigned)v.nb[0] && (unsigned)py < (unsigned)v.nb[1] && (unsigned)pz < (unsigned)v.nb[2]) {
+                const uint32_t q = v.index[px + v.nb[0] * (py + (int64_t)v.nb[1] * pz)];
+                if (q & kBlockOccupied) near = bits[q & ~kBlockOccupied];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int r = lane + 64 * k, ry = r % 12, rz = min(r / 12, 11), from = 3 * (ry >> 2) + 9 * (rz >> 2);
+            const int s = 4 * (ry & 3) + 16 * (rz & 3);
+            uint32_t w = 0;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const uint64_t m = __shfl((unsigned long long)near, from + i, 64);
+                w |= (uint32_t)((m >> s) & 15u) << (4 * i);
+            }
+            if (r < 144) row[r] = w;
+        }
+    }
+    __syncthreads();
+    if (!mine) return;
+    uint16_t *out = bricks + ((size_t)(e & ~kBlockOccupied) * 64 + lane);
+    const uint32_t mask = *out;
+    if (mask) {
+        *out = (uint16_t)(kBoxOccupied | kBoxNoLayer | mask);
+        return;
+    }
+    // nearest occupied brick, in bricks, at most 5: at all, and within the layer of bricks
+    // perpendicular to each axis
+    const int i = 4 + (lane & 3), j = 4 + ((lane >> 2) & 3), k = 4 + (lane >> 4);
+    int d = 5, dx = 5, dy = 5, dz = 5;
+    for (int c = -4; c <= 4; ++c)
+        for (int b = -4; b <= 4; ++b) {
+            const uint32_t w = row[(j + b) + 12 * (k + c)];
+            const uint32_t right = w >> i, left = w << (31 - i);
+            const int ring = max(abs(b), abs(c));
+            const int r = max(ring, min(right ? __builtin_ctz(right) : 5, left ? __builtin_clz(left) : 5));
+            d = min(d, r);
+            dz = c == 0 ? min(dz, r) : dz;
+            dy = b == 0 ? min(dy, r) : dy;
+            dx = right & 1u ? min(dx, ring) : dx;
+        }
+    uint32_t o = box_extents(d, d, d);
+    if (d < 3 && max(dx, max(dy, dz)) > d)
+        o = dz >= dx && dz >= dy ? box_extents(dz, dz, 1) : (dy >= dx ? box_extents(dy, 1, dy) : box_extents(1, dx, dx));
+    *out = (uint16_t)o;
+}
+
+MapView index_cells(const SparseView &v)
+{
+    MapView m{};
+    m.nbx = v.nb[0]; m.nby = v.nb[1]; m.nbz = v.nb[2];
+    m.nx = 2 * m.nbx; m.ny = 2 * m.nby; m.nz = 2 * m.nbz;
+    return m;
+}
+
+size_t round256(size_t n) { return (n + 255) / 256 * 256; }
+
 template <int K, int SV>
 hipError_t launch_sparse_k(const RayArgs &A, hipStream_t s, bool debug, hipEvent_t e0, hipEvent_t e1)
 {
@@ -111,11 +226,39 @@ hipError_t launch_sparse_sv(const RayArgs &A, hipStream_t s, bool debug, hipEven
 
 hipError_t launch_sparse(const RayArgs &A, hipStream_t s, bool debug, hipEvent_t e0, hipEvent_t e1)
 {
+    if (A.sparse == 2) return launch_raycast(A, s, debug, e0, e1);
     switch (A.lookahead) {
     case 4: return launch_sparse_sv<4>(A, s, debug, e0, e1);
     case 16: return launch_sparse_sv<16>(A, s, debug, e0, e1);
     default: return launch_sparse_sv<8>(A, s, debug, e0, e1);
     }
+}
+
+// Scratch: the occupancy and bit sets of the index's boxes, their entries, the bricks' bits.
+size_t sparse_index_scratch_bytes(const SparseView &v)
+{
+    const size_t cells = (size_t)v.nb[0] * v.nb[1] * v.nb[2];
+    return round256(box_scratch_bytes(index_cells(v))) + round256(sizeof(uint16_t) * cells) + sizeof(uint64_t) * (size_t)v.n_slots;
+}
+
+hipError_t launch_sparse_index(const SparseView &v, uint8_t *scratch, hipStream_t s)
+{
+    MapView m = index_cells(v);
+    const int64_t cells = (int64_t)v.nb[0] * v.nb[1] * v.nb[2];
+    uint16_t *box = reinterpret_cast<uint16_t *>(scratch + round256(box_scratch_bytes(m)));
+    uint64_t *bits = reinterpret_cast<uint64_t *>(reinterpret_cast<uint8_t *>(box) + round256(sizeof(uint16_t) * (size_t)cells));
+    uint32_t *index = const_cast<uint32_t *>(v.index);
+    uint16_t *bricks = const_cast<uint16_t *>(v.bricks);
+    m.box = box;
+    const int32_t pitch = box_mask_pitch(m);
+    if (hipError_t e = hipMemsetAsync(scratch, 0, (size_t)pitch * m.nby * m.nbz, s)) return e;
+    if (hipError_t e = hipMemsetAsync(index, 0, sizeof(uint32_t) * (size_t)cells, s)) return e;
+    index_slots_kernel<<<(v.table_mask + 256) / 256, 256, 0, s>>>(v, index, scratch, pitch);
+    launch_cell_boxes(m, scratch, s);
+    index_boxes_kernel<<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(index, box, cells);
+    brick_masks_kernel<<<(unsigned)((v.n_slots + 3) / 4), 256, 0, s>>>(v, bricks, bits);
+    brick_boxes_kernel<<<(unsigned)((cells + 3) / 4), 256, 0, s>>>(v, bricks, bits);
+    return hipGetLastError();
 }
 
 hipError_t launch_sparse_masks(const SparseView &v, HashEntry *table, hipStream_t s)

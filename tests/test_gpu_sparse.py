@@ -358,3 +358,44 @@ def test_sparse_subvoxel_distances(ctx, tiny_map, enc):
     finally:
         ctx.release(mid)
     assert moved > 1000
+
+
+@pytest.mark.parametrize("enc", ["f32", "u8"])
+@pytest.mark.parametrize("shift,far", [((-3, 2, -8), False), ((-3, 2, -8), True), ((8120, -8150, 8100), False),
+                                       ((8184, -8192, 0), False)])
+def test_sparse_walk_by_index_and_by_table(ctx, tiny_map, shift, far, enc):
+    """Starts inside, above and beside the box of the stored blocks; an index (near the origin and
+    a few blocks from the largest coordinates it may have), none (one block far away: the box would
+    be too large), and one that a query so far out may not use.  Grid coordinates are multiples
+    of 1/64, exact in float32 in both frames."""
+    base = W.sparse_from_dense(tiny_map, keep_free=0.1, seed=3)
+    coords = base.coords + np.asarray(shift, np.int32)
+    more = np.array([[-200000, 1, 2]], np.int32) if far else coords[:0]
+    sm = W.SparseMap("s", np.concatenate([coords, more]), np.concatenate([base.values, base.values[:len(more)]]), 0.125,
+                     np.zeros(3), [], base.trunc_m)
+    data = sm.values if enc == "f32" else W.encode_u8(sm.values)
+    mid = ctx.upload_sparse(sm.coords, data, sm.voxel_m, sm.origin_m, enc, sm.trunc_m)
+    lo, hi = (np.asarray(shift) - 12) * 8, (np.asarray(shift) + 20) * 8
+    dense = W.SparseMap("d", coords, base.values, 0.125, np.zeros(3), [], base.trunc_m).dense_crop(lo, hi)[0]
+    om = oracle.OracleMap(dense, sm.voxel_m, np.zeros(3), "f32")
+    dirs = oracle.directions(2048)
+    rng = np.random.default_rng(abs(shift[0]))
+    try:
+        for k in range(24):
+            gd = rng.integers(64 * 56, 64 * 200, 3) / 64.0
+            if k % 3 == 0:
+                gd = np.floor(gd)
+            v0 = gd.astype(int)
+            if dense[v0[2], v0[1], v0[0]] <= 0:
+                continue
+            x = (gd + lo) * sm.voxel_m
+            g = ctx.trace(mid, x, 2048, P_TINY)
+            o = oracle.trace(om, gd.astype(np.float32), dirs, P_TINY["max_range"], nthreads=8)
+            _compare(g, o, sm, lo, dense.shape[::-1], f"{shift} {far} {enc} start {gd}")
+            v = rng.normal(0.0, 1.0, 3)
+            oq = oracle.combine(P_TINY, dirs, o["d"], o["hit"], v)
+            oq["visits"] = int(o["visits"].sum())
+            oq["n_tie"] = int(np.count_nonzero(o["flags"] & oracle.TIE))
+            compare_query(ctx.query(mid, x, v, 2048, P_TINY), oq, f"query {gd}")
+    finally:
+        ctx.release(mid)
