@@ -16,8 +16,8 @@
 // floor with cubes of up to 255 bricks alone, 10 with these; elsewhere 17-22 and 11-16).
 //
 // Bound by the copy: the grid is read once and written once (float32 and float16 maps).  A 400^3
-// float32 grid: 85 us for the copy (6.0 TB/s) with the occupancy, 13 us for the layer sets, 26 and 30
-// for the dilations, 21 for the choice, 43 to write the entries; a copy and one thread per 8^3 cell
+// float32 grid: 85 us for the copy (6.0 TB/s) with the occupancy, 13 us for the layer sets, 22 and 19
+// for the dilations, 20 for the choice, 22 to write the entries; a copy and one thread per 8^3 cell
 // and per 2^3 brick took 91 + 147 + 65 us.
 
 #include <hip/hip_runtime.h>
@@ -41,12 +41,13 @@ struct Scratch {
     uint64_t *cz, *cy, *cx;                       // kSteps each: dilated slabs, perpendicular to the axis
     uint64_t *yx;                                 // 2 kSteps: the x layers dilated along y
     uint64_t *best;                               // 6: extent (3 bits), side and axis (2 bits) of the best layer
+    uint64_t *best_y;                             // 6: of the best perpendicular to y alone
     uint64_t *cube;                               // 3: bits of d
     uint64_t *full;                               // 1: d = kSteps + 1
     int64_t words;
     int32_t pitch, w;                             // bytes, words of a row
 };
-constexpr int kSets = 6 + 3 * kSteps + 2 * kSteps + 6 + 3 + 1;
+constexpr int kSets = 6 + 3 * kSteps + 2 * kSteps + 6 + 3 + 1 + 6;
 
 __host__ __device__ inline int32_t row_words(const MapView &m) { return (m.nbx + 63) >> 6; }
 __host__ __device__ inline int64_t set_words(const MapView &m) { return (int64_t)row_words(m) * m.nby * m.nbz; }
@@ -70,6 +71,7 @@ Scratch scratch_at(const MapView &m, uint8_t *p)
     s.best = s.yx + 2 * kSteps * s.words;
     s.cube = s.best + 6 * s.words;
     s.full = s.cube + 3 * s.words;
+    s.best_y = s.full + s.words;
     return s;
 }
 
@@ -150,7 +152,7 @@ __global__ void __launch_bounds__(256) copy_rest_kernel(MapView m, const typenam
 // have no entries, so a box must not cover them).
 __global__ void __launch_bounds__(256) layer_bits_kernel(MapView m, Scratch s)
 {
-    const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;        // four bricks
+    const int64_t id = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x;   // four bricks
     const int64_t row = id / (16 * s.w);
     const int x = (int)(id - row * 16 * s.w) * 4;
     const bool in = row < (int64_t)m.nby * m.nbz;
@@ -306,6 +308,28 @@ struct Best {
         a0 = pick(m, axis & 1 ? ~0ull : 0ull, a0);
         a1 = pick(m, axis & 2 ? ~0ull : 0ull, a1);
     }
+    __device__ __forceinline__ void offer(const Best &o)
+    {
+        const uint64_t m = above(o.q, q);
+        q = pick(m, o.q, q);
+        side = pick(m, o.side, side);
+        a0 = pick(m, o.a0, a0);
+        a1 = pick(m, o.a1, a1);
+    }
+    __device__ __forceinline__ void load(const uint64_t *set, int64_t words, int64_t at)
+    {
+        const uint64_t *o = set + at;
+        q = Count{o[0], o[words], o[2 * words]};
+        side = o[3 * words];
+        a0 = o[4 * words];
+        a1 = o[5 * words];
+    }
+    __device__ __forceinline__ void store(uint64_t *set, int64_t words, int64_t at) const
+    {
+        uint64_t *o = set + at;
+        o[0] = q.b0; o[words] = q.b1; o[2 * words] = q.b2;
+        o[3 * words] = side; o[4 * words] = a0; o[5 * words] = a1;
+    }
 };
 
 // One step of the dilations of an axis' two voxel layers within the planes along x and the rows
@@ -340,14 +364,26 @@ __device__ __forceinline__ void plane(const Scratch &s, const Place &p, int axis
     best.offer(qb, true, axis);
 }
 
-// Layers perpendicular to y and z, and the first half (along y) of those perpendicular to x.
+// Layers perpendicular to z (blockIdx.y 0) and y (1), and the first half (along y) of those
+// perpendicular to x (2).  A thread per word leaves a SIMD two waves on a 400^3 map, waiting for
+// loads: three kinds of blocks instead of one thread doing all of it, and two in the next kernel,
+// 26 + 30 us -> 22 + 19 (with the blocks of
+// neighbouring words on one XCD; 22 + 26 without).
 __global__ void __launch_bounds__(256) planes_kernel(MapView m, Scratch s)
 {
-    const Place p = place_of(m, s, (int64_t)blockIdx.x * 256 + threadIdx.x);
+    const Place p = place_of(m, s, (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
     if (!p.ok) return;
-    Best best{Count{0, 0, 0}, ~0ull, ~0ull, ~0ull};
-    plane(s, p, 2, s.cz, best);
-    plane(s, p, 1, s.cy, best);
+    if (blockIdx.y < 2) {
+        Best best{Count{0, 0, 0}, ~0ull, ~0ull, ~0ull};
+        if (blockIdx.y == 0) {
+            plane(s, p, 2, s.cz, best);
+            best.store(s.best, s.words, p.at);
+        } else {
+            plane(s, p, 1, s.cy, best);
+            best.store(s.best_y, s.words, p.at);
+        }
+        return;
+    }
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
         const uint64_t *set = s.layer + side * s.words;
@@ -358,22 +394,35 @@ __global__ void __launch_bounds__(256) planes_kernel(MapView m, Scratch s)
             s.yx[(side * kSteps + k - 1) * s.words + p.at] = t;
         }
     }
-    uint64_t *o = s.best + p.at;
-    o[0] = best.q.b0; o[s.words] = best.q.b1; o[2 * s.words] = best.q.b2;
-    o[3 * s.words] = best.side; o[4 * s.words] = best.a0; o[5 * s.words] = best.a1;
 }
 
-// Layers perpendicular to x (the second half, along z), and the cubes.
+// Layers perpendicular to x (the second half, along z; blockIdx.y 0), and the cubes (1).
 __global__ void __launch_bounds__(256) cubes_kernel(MapView m, Scratch s)
 {
-    const Place p = place_of(m, s, (int64_t)blockIdx.x * 256 + threadIdx.x);
+    const Place p = place_of(m, s, (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
     if (!p.ok) return;
-    uint64_t *o = s.best + p.at;
-    Best best{Count{o[0], o[s.words], o[2 * s.words]}, o[3 * s.words], o[4 * s.words], o[5 * s.words]};
+    if (blockIdx.y == 1) {
+        Count d{~0ull, 0, 0};
+#pragma unroll
+        for (int k = 1; k <= kSteps; ++k) {
+            const uint64_t *set = s.cz + (k - 1) * s.words;
+            uint64_t t = set[p.at];
+#pragma unroll
+            for (int j = 1; j <= k; ++j) t |= word_z(set, p, -j) | word_z(set, p, j);
+            d.add(~t);
+        }
+        uint64_t *c = s.cube + p.at;
+        c[0] = d.b0; c[s.words] = d.b1; c[2 * s.words] = d.b2;
+        s.full[p.at] = d.b0 & d.b1 & d.b2;
+        return;
+    }
+    Best best, best_y;
+    best.load(s.best, s.words, p.at);
+    best_y.load(s.best_y, s.words, p.at);
+    best.offer(best_y);
     Count q[2];
 #pragma unroll
     for (int side = 0; side < 2; ++side) q[side] = Count{~s.layer[side * s.words + p.at], 0, 0};
-    Count d{~0ull, 0, 0};
 #pragma unroll
     for (int k = 1; k <= kSteps; ++k) {
         uint64_t all = 0;
@@ -387,19 +436,10 @@ __global__ void __launch_bounds__(256) cubes_kernel(MapView m, Scratch s)
             all |= t;
         }
         s.cx[(k - 1) * s.words + p.at] = all;
-        const uint64_t *set = s.cz + (k - 1) * s.words;
-        uint64_t t = set[p.at];
-#pragma unroll
-        for (int j = 1; j <= k; ++j) t |= word_z(set, p, -j) | word_z(set, p, j);
-        d.add(~t);
     }
     best.offer(q[0], false, 0);
     best.offer(q[1], true, 0);
-    o[0] = best.q.b0; o[s.words] = best.q.b1; o[2 * s.words] = best.q.b2;
-    o[3 * s.words] = best.side; o[4 * s.words] = best.a0; o[5 * s.words] = best.a1;
-    uint64_t *c = s.cube + p.at;
-    c[0] = d.b0; c[s.words] = d.b1; c[2 * s.words] = d.b2;
-    s.full[p.at] = d.b0 & d.b1 & d.b2;
+    best.store(s.best, s.words, p.at);
 }
 
 // Extents (bit-sliced) of the slab of half thickness d (1 .. 3: masks t1, t2, t3) perpendicular to
@@ -471,7 +511,7 @@ __device__ __forceinline__ uint64_t *entry_plane(const Scratch &s, int k)
 
 __global__ void __launch_bounds__(256) select_kernel(MapView m, Scratch s)
 {
-    const Place p = place_of(m, s, (int64_t)blockIdx.x * 256 + threadIdx.x);
+    const Place p = place_of(m, s, (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
     if (!p.ok) return;
     const uint64_t *c = s.cube + p.at;
     const Count d{c[0], c[s.words], c[2 * s.words]};
@@ -504,24 +544,47 @@ __global__ void __launch_bounds__(256) select_kernel(MapView m, Scratch s)
     for (int k = 0; k < kEntryPlanes; ++k) entry_plane(s, k)[p.at] = o[k];
 }
 
-// The entries: a wave writes 64, each lane picking its bit of every plane.
+// The entries: a wave writes those of kExpandWords consecutive words (64 each), each lane picking its
+// bit of every plane.  The planes' words come by scalar loads of several words at once: a word at a
+// time, 14 loads of 8 bytes for 128 bytes of entries left the kernel waiting for them (43 us
+// on a 400^3 map against 22;
+// four words spill scalar registers: 33).
+constexpr int kExpandWords = 2;
+
 __global__ void __launch_bounds__(256) expand_kernel(MapView m, Scratch s, uint16_t *box)
 {
-    const int64_t word = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    if (word >= s.words) return;
-    const int64_t row = word / s.w;
-    const int x = (int)(word - row * s.w) * 64 + (threadIdx.x & 63);
+    const uint32_t word0 = __builtin_amdgcn_readfirstlane((xcd_tile(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6)) * kExpandWords);
+    if (word0 >= (uint32_t)s.words) return;
     const uint32_t bits[kEntryPlanes] = {1u << 1, 1u << 2, 1u << 3, 1u << 6, 1u << 7, 1u << 8, 1u << 9, 1u << 10,
                                          1u << 11, 1u << 12, 1u << 13, kBoxOccupied, 0u, 0u};
-    uint32_t e = 0;
+    // (reads past the last word stay within the scratch: sets follow the planes)
+    typedef const __attribute__((address_space(4))) uint64_t *ConstPtr;
+    uint64_t v[kEntryPlanes][kExpandWords];
 #pragma unroll
-    for (int k = 0; k < 12; ++k)
-        e |= __builtin_amdgcn_inverse_ballot_w64(entry_plane(s, k)[word]) ? bits[k] : 0u;
-    e = __builtin_amdgcn_inverse_ballot_w64(entry_plane(s, 12)[word]) ? box_extents(10, 10, 10) : e;
-    e = __builtin_amdgcn_inverse_ballot_w64(entry_plane(s, 13)[word]) ? box_extents(13, 13, 13) : e;
-    if (x >= m.nbx) return;
-    const uint32_t mask = s.mask[row * s.pitch + x];             // 0 for a free brick
-    box[row * m.nbx + x] = (uint16_t)(e | mask);
+    for (int k = 0; k < kEntryPlanes; ++k) {
+        const ConstPtr plane = (ConstPtr)(uintptr_t)(entry_plane(s, k) + word0);
+#pragma unroll
+        for (int i = 0; i < kExpandWords; ++i) v[k][i] = plane[i];
+    }
+    uint32_t row = word0 / (uint32_t)s.w, wi = word0 - row * (uint32_t)s.w;
+#pragma unroll
+    for (int i = 0; i < kExpandWords; ++i) {
+        if (word0 + i >= (uint32_t)s.words) return;
+        uint32_t e = 0;
+#pragma unroll
+        for (int k = 0; k < 12; ++k) e |= __builtin_amdgcn_inverse_ballot_w64(v[k][i]) ? bits[k] : 0u;
+        e = __builtin_amdgcn_inverse_ballot_w64(v[12][i]) ? box_extents(10, 10, 10) : e;
+        e = __builtin_amdgcn_inverse_ballot_w64(v[13][i]) ? box_extents(13, 13, 13) : e;
+        const int x = (int)wi * 64 + (int)(threadIdx.x & 63);
+        if (x < m.nbx) {
+            const uint32_t mask = s.mask[(uint64_t)row * s.pitch + x];     // 0 for a free brick
+            box[(uint64_t)row * m.nbx + x] = (uint16_t)(e | mask);
+        }
+        if (++wi == (uint32_t)s.w) {
+            wi = 0;
+            ++row;
+        }
+    }
 }
 
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -543,11 +606,14 @@ void launch_bricks(const BoxArgs &a, uint8_t *mask, int32_t pitch, hipStream_t s
 void launch_extents(const MapView &m, const Scratch &p, hipStream_t s)
 {
     if (p.words == 0) return;
-    layer_bits_kernel<<<blocks_for(16 * p.words), 256, 0, s>>>(m, p);
-    planes_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
-    cubes_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
-    select_kernel<<<blocks_for(p.words), 256, 0, s>>>(m, p);
-    expand_kernel<<<(unsigned)((p.words + 3) / 4), 256, 0, s>>>(m, p, const_cast<uint16_t *>(m.box));
+    // every launch's blocks in eight equal runs of words, one per XCD: a kernel's reads of the set
+    // before and of rows above and below find most of them in their own L2
+    auto blocks = [](int64_t n) { return blocks_for((n + 2047) / 2048 * 2048); };
+    layer_bits_kernel<<<blocks(16 * p.words), 256, 0, s>>>(m, p);
+    planes_kernel<<<dim3(blocks(p.words), 3), 256, 0, s>>>(m, p);
+    cubes_kernel<<<dim3(blocks(p.words), 2), 256, 0, s>>>(m, p);
+    select_kernel<<<blocks(p.words), 256, 0, s>>>(m, p);
+    expand_kernel<<<blocks((p.words + kExpandWords - 1) / kExpandWords * 64), 256, 0, s>>>(m, p, const_cast<uint16_t *>(m.box));
 }
 
 template <int DT>

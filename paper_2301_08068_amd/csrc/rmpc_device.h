@@ -41,6 +41,15 @@ template <> struct Voxel<RMPC_OCC_U8> {
     static __device__ __forceinline__ bool occ(uint8_t v) { return v != 0; }
 };
 
+// Blocks are dispatched round-robin over the 8 XCDs (block b runs on XCD b % 8).  Give each
+// XCD a contiguous run of tiles so that its L2 sees one compact cone of ray directions (or run of
+// bricks).
+__device__ __forceinline__ int xcd_tile(int b, int nb)
+{
+    const int q = nb >> 3, r = nb & 7, x = b & 7;
+    return x * q + (x < r ? x : r) + (b >> 3);
+}
+
 // ------------------------------------------------------------------------------------
 // compensated float32 sums (error-free TwoSum; the compensations are kept to the end)
 // ------------------------------------------------------------------------------------

@@ -249,14 +249,6 @@ __device__ __forceinline__ int contributes(const RayArgs &A, float rx, float ry,
     return d < A.radius64 && vn > 0.0;
 }
 
-// Blocks are dispatched round-robin over the 8 XCDs (block b runs on XCD b % 8).  Give each
-// XCD a contiguous run of tiles so that its L2 sees one compact cone of ray directions.
-__device__ __forceinline__ int xcd_tile(int b, int nb)
-{
-    const int q = nb >> 3, r = nb & 7, x = b & 7;
-    return x * q + (x < r ? x : r) + (b >> 3);
-}
-
 __device__ __forceinline__ FinishSlots single_slots(float *partials, uint32_t *ticket, rmpc_result *out,
                                                     uint64_t *done, uint64_t seq)
 {
