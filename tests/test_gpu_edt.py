@@ -161,3 +161,28 @@ def test_strip_widths(ctx, n):
         t.reshape(-1)[n] = -0.05
         g = _gpu_edt(ctx, t, 0.1, "f32")
         assert np.array_equal(g, oracle.edt(oracle.OracleMap(t, 0.1, np.zeros(3), "f32")))
+
+
+@pytest.mark.parametrize("shape", [(4, 5, 6), (1, 5, 6), (4, 1, 1), (1, 1, 1)])
+def test_esdf_neighbours_at_the_grid_edges(ctx, shape):
+    """Every voxel of a tiny grid, its neighbours clamped at the edges; alternating with a map
+    without an occupied voxel (zero sums).  Tolerance as above."""
+    rng = np.random.default_rng(sum(shape))
+    p = W.params("static")
+    for occupied in (True, False):
+        t = np.full(shape, 0.3, np.float32)
+        if occupied:
+            t.reshape(-1)[rng.integers(t.size)] = -0.1
+        om = oracle.OracleMap(t, 0.5, np.zeros(3), "f32")
+        mid = ctx.upload(t, 0.5, np.zeros(3), "f32")
+        try:
+            sq, osq = ctx.edt(mid, shape), oracle.edt(om)
+            for z, y, x in np.ndindex(shape):
+                at, v = (np.array([x, y, z]) + 0.5) * 0.5, rng.normal(0.0, 1.0, 3)
+                g, o = ctx.esdf_query(mid, sq, at, v, p), oracle.esdf_query(om, osq, at, v, p)
+                for k in ("n_hit", "n_contrib", "flags", "rank", "n_rays", "n_tie", "visits"):
+                    assert g[k] == o[k], (x, y, z, k, g[k], o[k])
+                for k in ("S", "b", "f"):
+                    assert np.abs(g[k] - o[k]).max() <= 1e-9 * max(np.abs(o[k]).max(), 1e-300), (x, y, z, k)
+        finally:
+            ctx.release(mid)
