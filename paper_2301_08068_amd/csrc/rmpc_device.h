@@ -121,27 +121,45 @@ __device__ __forceinline__ void row_store(float *row, const Acc &a)
     q[0] = a.n_hit; q[1] = a.n_contrib; q[2] = a.n_tie; q[3] = a.visits;
 }
 
+// The value of the lane across the given step of a butterfly over 16 lanes, in one instruction: lane
+// ^ 1, ^ 2, and, where 4 (8) lanes hold the same value already, any of the other 4 (8), which
+// mirroring the 8 (16) lanes reaches.  (Through LDS, __shfl_xor, the four steps waited some 400
+// cycles.)
+template <int OFF>
+__device__ __forceinline__ int32_t across(int32_t v)
+{
+    constexpr int ctrl = OFF == 1 ? 0xB1 : OFF == 2 ? 0x4E : OFF == 4 ? 0x141 : 0x140;
+    return __builtin_amdgcn_update_dpp(0, v, ctrl, 0xf, 0xf, true);
+}
+
+template <int OFF>
+__device__ __forceinline__ void pair_step(int t, float &s, float &c)
+{
+    const float s2 = __int_as_float(across<OFF>(__float_as_int(s)));
+    const float c2 = __int_as_float(across<OFF>(__float_as_int(c)));
+    const bool upper = (t & OFF) != 0;
+    float ls = upper ? s2 : s, lc = upper ? c2 : c;
+    csum_merge(ls, lc, upper ? s : s2, upper ? c : c2);
+    s = ls;
+    c = lc;
+}
+
 // Butterfly over the 16 lanes of a pair group; the lower lane's value is always the left
 // operand of the merge.
 __device__ __forceinline__ void pair_butterfly(int t, float &s, float &c)
 {
-#pragma unroll
-    for (int off = 1; off < kColLanes; off <<= 1) {
-        const float s2 = __shfl_xor(s, off, kWave);
-        const float c2 = __shfl_xor(c, off, kWave);
-        const bool upper = (t & off) != 0;
-        float ls = upper ? s2 : s, lc = upper ? c2 : c;
-        csum_merge(ls, lc, upper ? s : s2, upper ? c : c2);
-        s = ls;
-        c = lc;
-    }
+    pair_step<1>(t, s, c);
+    pair_step<2>(t, s, c);
+    pair_step<4>(t, s, c);
+    pair_step<8>(t, s, c);
 }
 
 __device__ __forceinline__ int32_t int_butterfly(int32_t v)
 {
-#pragma unroll
-    for (int off = 1; off < kColLanes; off <<= 1) v += __shfl_xor(v, off, kWave);
-    return v;
+    v += across<1>(v);
+    v += across<2>(v);
+    v += across<4>(v);
+    return v + across<8>(v);
 }
 
 // The thread index through an empty asm statement.  The reductions' LDS addresses and lane
