@@ -403,12 +403,26 @@ __device__ __forceinline__ bool box_range_tie(const RayArgs &A, const BoxRay &R,
     return tie;
 }
 
+// Put the walk into a voxel a little before parameter t_first.  Where a face may lie on either side
+// of the float32 position the voxel is the one behind it, which the ray need not pass: the walk
+// leaves it at a crossing before t_first, and from there on is the ray's own.  (The voxel ahead of a
+// face that is still to be crossed would leave out the voxels until then: an error of 0.004 voxel
+// across a face is 0.1 along a ray that crosses it at 0.04.)  Returns false past the grid.
+__device__ __forceinline__ bool box_start(const RayArgs &A, const BoxRay &R, float t_first, BoxWalk &w)
+{
+    const MapView &m = A.map;
+    const float t = t_first - fmaxf(kSegOverlap, 2.0f * R.tol);
+    w.ux = max(w.ux, min((int)floorf(fmaf(t, fabsf(R.rx), R.gsx) - R.tol), signed_edge(m, R.rx, m.nx) - 1));
+    w.uy = max(w.uy, min((int)floorf(fmaf(t, fabsf(R.ry), R.gsy) - R.tol), signed_edge(m, R.ry, m.ny) - 1));
+    w.uz = max(w.uz, min((int)floorf(fmaf(t, fabsf(R.rz), R.gsz) - R.tol), signed_edge(m, R.rz, m.nz) - 1));
+    return t < R.t_exit;
+}
+
 // Start walking segment seg of S of a ray: its start voxel and its end.  Returns false for a
 // segment that starts past the grid.
 __device__ __forceinline__ bool box_segment(const RayArgs &A, const BoxRay &R, int seg, int S, BoxWalk &w, bool &last,
                                             float &t_lo, float &t_hi, float &t_first)
 {
-    const MapView &m = A.map;
     const float len = (float)A.tmax_v / (float)S;
     w.ux = signed_voxel(R.rx, A.v0[0]);
     w.uy = signed_voxel(R.ry, A.v0[1]);
@@ -421,12 +435,7 @@ __device__ __forceinline__ bool box_segment(const RayArgs &A, const BoxRay &R, i
     t_hi = last ? A.tmax_hi : len * (float)(seg + 1);
     t_first = len * (float)seg;       // (segment 0 starts in a free voxel)
     if (seg == 0) return true;
-    // inexact near a face: a crossing there is walked by the segment before as well
-    const float t = t_first - fmaxf(kSegOverlap, 2.0f * R.tol);
-    w.ux = max(w.ux, min((int)floorf(fmaf(t, fabsf(R.rx), R.gsx)), signed_edge(m, R.rx, m.nx) - 1));
-    w.uy = max(w.uy, min((int)floorf(fmaf(t, fabsf(R.ry), R.gsy)), signed_edge(m, R.ry, m.ny) - 1));
-    w.uz = max(w.uz, min((int)floorf(fmaf(t, fabsf(R.rz), R.gsz)), signed_edge(m, R.rz, m.nz) - 1));
-    return t < R.t_exit;
+    return box_start(A, R, t_first, w);
 }
 
 // A segment's result once its walk has stopped.

@@ -399,3 +399,35 @@ def test_sparse_walk_by_index_and_by_table(ctx, tiny_map, shift, far, enc):
             compare_query(ctx.query(mid, x, v, 2048, P_TINY), oq, f"query {gd}")
     finally:
         ctx.release(mid)
+
+
+@pytest.mark.parametrize("lane_target", [18, 19])
+@pytest.mark.parametrize("seed", [3, 14, 59, 70])
+def test_segments_that_start_beside_a_face_far_out(ctx, seed, lane_target):
+    """65,000 voxels from the origin a float32 position is off by up to 1/128 voxel, which along a
+    ray nearly parallel to a face is far: a segment must not start beyond a face that the ray has
+    yet to cross (in each of these worlds some ray of 65,536 did, and missed its hit)."""
+    rng = np.random.default_rng(seed)
+    n, shift = 160, np.array([8000, -8100, 8050])
+    occ = np.zeros((n, n, n), bool)
+    occ[40:120, 40:120, 40:120] = rng.uniform(size=(80, 80, 80)) < 0.002
+    g = rng.integers(64 * 64, 64 * 96, 3) / 64
+    v0 = np.floor(g).astype(int)
+    occ[v0[2], v0[1], v0[0]] = False
+    t = np.where(occ, -0.1, 0.3).astype(np.float32)
+    blocks = t.reshape(n // 8, 8, n // 8, 8, n // 8, 8).transpose(0, 2, 4, 1, 3, 5)
+    at = np.argwhere((blocks <= 0).any(axis=(3, 4, 5)))
+    coords = (at[:, ::-1] + shift).astype(np.int32)
+    sm = W.SparseMap("far", coords, np.ascontiguousarray(blocks[tuple(at.T)]), 0.125, np.zeros(3), [], 0.3)
+    params = W.params("static", max_range=38.0 * 0.125)
+    before = ctx.config(2)
+    mid = ctx.upload_sparse(sm.coords, sm.values, sm.voxel_m, sm.origin_m, "f32", 0.3)
+    try:
+        ctx.config(2, lane_target_log2=lane_target)
+        got = ctx.trace(mid, (g + 8 * shift) * 0.125, 65536, params)
+    finally:
+        ctx.config(2, **before)
+        ctx.release(mid)
+    o = oracle.trace(oracle.OracleMap(t, 0.125, np.zeros(3), "f32"), g.astype(np.float32), oracle.directions(65536),
+                     params["max_range"], nthreads=8)
+    _compare(got, o, sm, 8 * shift, (n, n, n), f"seed {seed}")
