@@ -431,10 +431,11 @@ rmpc_status rmpc_create(int device, void *arena_dev, size_t arena_bytes, rmpc_ct
     c->next_map_id = 0;
     c->cfg[RMPC_CONFIG_QUERY] = rmpc_launch_config{rmpc::kLookahead, 17, 0, 0};
     c->cfg[RMPC_CONFIG_BATCH] = rmpc_launch_config{8, 14, 0, 0};
-    // sparse walks have no brick level and each block step probes the hash table, so slow rays
-    // are longer and more lanes per ray pay; block rounds of 4 steps waste fewer table loads and
-    // registers (a 160 m world at 65,536 rays, 4 lanes per ray: lookahead 4 134 us, 8 182 us,
-    // 16 236 us; lookahead 8: 8 lanes per ray 186 us, 16 lanes 242 us)
+    // each block step of a walk by the table probes it, so slow rays are long and more lanes per
+    // ray pay; block rounds of 4 steps waste fewer table loads and registers (a 160 m world at 65,536
+    // rays, 4 lanes per ray: lookahead 4 134 us, 8 182 us, 16 236 us; lookahead 8: 8 lanes per ray
+    // 186 us, 16 lanes 242 us).  Walks by an index take 1, 2 or 4 lanes per ray in about the same
+    // time (42-45 us at 65,536 rays in a 96 m world).
     c->cfg[RMPC_CONFIG_SPARSE] = rmpc_launch_config{4, 18, 0, 0};
     c->ev_dep = nullptr;
     c->server = nullptr;

@@ -587,23 +587,25 @@ __global__ void esdf_policy_kernel(EsdfArgs A)
         n_contrib = d < A.radius && (A.vel[0] * rh[0] + A.vel[1] * rh[1] + A.vel[2] * rh[2]) > 0.0;
         resolve3(S, b, A.rank_tol, f, lam, rank, flags);
     }
-    if (lane != 0) return;
-    rmpc_result *out = A.out;
-    for (int i = 0; i < 3; ++i) {
-        store_system(&out->f[i], f[i]);
-        store_system(&out->b[i], b[i]);
-        store_system(&out->lambda[i], lam[i]);
-        for (int j = 0; j < 3; ++j) store_system(&out->A[3 * i + j], S[i][j]);
+    __shared__ rmpc_result res;
+    if (lane == 0) {
+        for (int i = 0; i < 3; ++i) {
+            res.f[i] = f[i];
+            res.b[i] = b[i];
+            res.lambda[i] = lam[i];
+            for (int j = 0; j < 3; ++j) res.A[3 * i + j] = S[i][j];
+        }
+        res.rank = rank;
+        res.n_hit = n_hit;
+        res.n_contrib = n_contrib;
+        res.n_tie = 0;
+        res.flags = flags;
+        res.n_rays = 1;
+        res.visits = 0;
     }
-    store_system(&out->rank, rank);
-    store_system(&out->n_hit, n_hit);
-    store_system(&out->n_contrib, n_contrib);
-    store_system(&out->n_tie, 0);
-    store_system(&out->flags, flags);
-    store_system(&out->n_rays, 1);
-    store_system(&out->visits, (int64_t)0);
+    store_result(&res, A.out);
     wait_stores();
-    store_system(A.done, A.seq);
+    if (lane == 0) store_system(A.done, A.seq);
 }
 
 }  // namespace

@@ -238,7 +238,7 @@ __device__ __forceinline__ void scan_tile(const ScanArgs &A, int tile, int n_til
 template <int DT, bool PART>
 __global__ void __launch_bounds__(kBlock, DT == kIndexedF32 || DT == kIndexedF16 ? 2 : 4) raycast_rmp_kernel(RayArgs A)
 {
-    __shared__ float lds[kReduceLdsWords];
+    __shared__ __align__(16) float lds[kReduceLdsWords];
     ray_tile<DT, PART>(A, xcd_tile(blockIdx.x, gridDim.x), gridDim.x,
                        single_slots(A.partials, A.ticket, A.result, A.done, A.seq), lds);
 }
@@ -269,7 +269,7 @@ __device__ __forceinline__ const T &constant_ref(const T &v)
 // waves per SIMD: 4 % less for the large batch, 2 % more for the served ones.)
 __global__ void __launch_bounds__(kBlock, 4) batch_kernel(BatchArgs B)
 {
-    __shared__ float lds[kReduceLdsWords];
+    __shared__ __align__(16) float lds[kReduceLdsWords];
     __shared__ int s_tile;
     const int n_tiles = B.hdr->n_tiles;
     const int n_queries = B.hdr->n_queries;
@@ -369,7 +369,7 @@ __global__ void __launch_bounds__(kBlock, 2) trace_debug_kernel(RayArgs A)
 // One scan query per launch.
 __global__ void __launch_bounds__(kBlock) scan_rmp_kernel(ScanArgs A)
 {
-    __shared__ float lds[kReduceLdsWords];
+    __shared__ __align__(16) float lds[kReduceLdsWords];
     scan_tile(A, blockIdx.x, gridDim.x, single_slots(A.partials, A.ticket, A.result, A.done, A.seq), lds);
 }
 
@@ -396,9 +396,9 @@ int ray_grid_blocks(int lanes)
     return b < 1 ? 1 : (b > kMaxBlocks ? kMaxBlocks : b);
 }
 
-// At most 128 blocks: every block pays a ticket with an agent-scope release and acquire at the
-// end, which costs more than looping over a few more points per thread (measured: 262,144
-// points take 19.5 us with 128 blocks against 43 us with 1024; 65,536 points 13.6 against 17.6).
+// At most 128 blocks: what every block pays at its end (its reduction, its row, its ticket, the
+// merge of its row) costs more than a few more points per thread: 65,536 points take 19.1 us with 128
+// blocks and 20.4 with 256, 262,144 points 21.3 and 21.4 (1,048,576 points 32.4 and 26.2).
 int scan_grid_blocks(int n_points)
 {
     int b = (n_points + kBlock - 1) / kBlock;

@@ -20,8 +20,7 @@ constexpr int kMaxPartialSlots = 4096;
 // Words of one block partial in device memory: 18 floats + 4 integers, padded.
 constexpr int kPartialWords = 32;
 
-// Blocks of one scan query (each block's ticket costs a release/acquire, so the points are
-// looped over instead of adding blocks).
+// Blocks of one scan query (at the end each costs more than a loop over a few more points).
 constexpr int kScanMaxBlocks = 128;
 constexpr int kScanBatch = 8;                // scan points a thread loads before it evaluates them
 

@@ -19,7 +19,7 @@ namespace {
 template <int K, int SV>
 __global__ void __launch_bounds__(kBlock, 2) sparse_rmp_kernel(RayArgs A)
 {
-    __shared__ float lds[kReduceLdsWords];
+    __shared__ __align__(16) float lds[kReduceLdsWords];
     sparse_tile<K, SV>(A, xcd_tile(blockIdx.x, gridDim.x), gridDim.x,
                    single_slots(A.partials, A.ticket, A.result, A.done, A.seq), lds);
 }
