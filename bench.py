@@ -24,7 +24,8 @@ if ROOT not in sys.path:
 
 METRIC = "rays/sec (raycast+RMP+resolve) at 65536 rays/query; served p50/p99 query latency"
 HBM_PEAK_GBS = 8000.0
-KERNEL_SOURCES = ["paper_2301_08068_amd/csrc/raycast.hip", "paper_2301_08068_amd/csrc/rmpc_device.h",
+KERNEL_SOURCES = ["paper_2301_08068_amd/csrc/raycast.hip", "paper_2301_08068_amd/csrc/rmpc_dense.h",
+                  "paper_2301_08068_amd/csrc/rmpc_device.h",
                   "paper_2301_08068_amd/csrc/rmpc_kernels.h", "paper_2301_08068_amd/csrc/rmpc_walk.h"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "raycast_rmp_paper400_f32_traffic.txt")
 L2_FILE = os.path.join(ROOT, "profiles", "raycast_rmp_paper400_f32_instmix_l2.txt")
@@ -646,7 +647,7 @@ def main():
                     help="rollout config: comma-separated rays per query")
     ap.add_argument("--serve-requests", type=int, default=20000)
     ap.add_argument("--serve-slots", type=int, default=3)
-    ap.add_argument("--lookahead", type=int, default=0, help="query launch: steps planned per round (4, 8, 16)")
+    ap.add_argument("--lookahead", type=int, default=0, help="query launch: steps planned per round (4, 8, 16; sparse maps without an index)")
     ap.add_argument("--lane-target", type=int, default=0, help="query launch: log2 of the lanes a query aims for")
     ap.add_argument("--cpu-seconds", type=float, default=10.0)
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -759,7 +760,7 @@ def main():
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic, "kernel": "raycast_rmp_kernel",
                 "algorithmic_bytes_per_launch": alg_bytes,
-                "limiter": "latency: the dependent round chain of the slowest waves, then the reduction tail"}
+                "limiter": "latency: the dependent step chain of the slowest waves, then the reduction tail"}
     if l2 is not None:
         req, hit_rate = l2
         roofline["l2_bytes_per_launch"] = int(req * L2_LINE_BYTES)
