@@ -179,3 +179,26 @@ def _brick_axes(dropped):
         out.append(pos)
         pos += 1 if i == dropped else 2
     return out
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("dims", [(63, 65, 67), (255, 8, 9), (1, 7, 5), (6, 301, 2), (64, 64, 65), (258, 3, 300)])
+def test_the_whole_grid_is_copied(dims, dtype):
+    """The resident grid equals the uploaded one, byte for byte, where bricks end at odd extents (the
+    last layers of partial maps are copied apart from them)."""
+    import torch
+    from paper_2301_08068_amd import binding as B
+    nx, ny, nz = dims
+    rng = np.random.default_rng(nx + ny + nz)
+    val = rng.uniform(-0.3, 0.3, (nz, ny, nx)).astype(np.float32)
+    grid = val if dtype == "f32" else val.astype(np.float16).view(np.uint16)
+    arena = torch.zeros(ARENA, dtype=torch.uint8, device="cuda:0")
+    ctx = B.rmpc_create(0, arena.data_ptr(), ARENA)
+    try:
+        dev = torch.from_numpy(np.ascontiguousarray(grid).view(np.uint8).reshape(-1)).to("cuda:0")
+        before = arena.clone()
+        B.rmpc_map_upload(ctx, nx, ny, nz, dtype, 0.1, (0.0, 0.0, 0.0), dev.data_ptr(), True)
+        base = int(torch.nonzero(arena != before)[0]) // 256 * 256
+        assert torch.equal(arena[base:base + dev.numel()], dev)
+    finally:
+        B.rmpc_destroy(ctx)
