@@ -22,7 +22,7 @@
 // segment per ray), the slowest of all 30-45.  Planning voxel, brick and 8^3-cell steps eight at a
 // time instead (33 VALU instructions a step, 240 a round) took 15-18 rounds of 2.2 us in the
 // slowest waves: that query's kernel 42-44 us against 24, a batch of 512 queries 2.23 ms against
-// 1.13.
+// 1.13 (20 us and 0.76 ms with the reductions and the batch kernel as they are now).
 #pragma once
 
 #include <hip/hip_runtime.h>
