@@ -227,8 +227,15 @@ __global__ void __launch_bounds__(256) edt_strip_kernel(int32_t *g, const RowWor
     extern __shared__ Quad strip_mem[];                   // [len + 2 kPad][lines / 4]
     Quad *strip = strip_mem;
     constexpr int kLanes = 1 << (CLOG - 2), kRows = 256 / kLanes;
-    // the last pass of a transform that another block has given up does nothing
-    if (flag && load_flag(flag) != 0u) return;
+    // the last pass of a transform that another block has given up does nothing (one load decides for
+    // the block: other blocks raise the flag at any time, and threads that read it one by one could
+    // part before the barriers below)
+    if (flag) {
+        __shared__ uint32_t given_up;
+        if (threadIdx.x == 0) given_up = load_flag(flag);
+        __syncthreads();
+        if (given_up != 0u) return;
+    }
     const int64_t q = blockIdx.x / strips;                // z (y pass) or y (z pass)
     const int32_t x0 = (int32_t)(blockIdx.x % strips) << CLOG;
     const int64_t base = x0 + outer * q;

@@ -187,3 +187,23 @@ def test_esdf_neighbours_at_the_grid_edges(ctx, shape):
                     assert np.abs(g[k] - o[k]).max() <= 1e-9 * max(np.abs(o[k]).max(), 1e-300), (x, y, z, k)
         finally:
             ctx.release(mid)
+
+
+# more strips than the GPU holds at once (the last pass has 15,040 and 24,000 blocks), so that blocks
+# start, load and search while others give the narrow passes up
+@pytest.mark.parametrize("shape,at", [((300, 160, 1500), [(0, 0, 0)]), ((1000, 48, 4000), [(0, 0, 0), (999, 47, 2000)])])
+def test_given_up_while_other_blocks_run(ctx, shape, at):
+    """Too far for the narrow passes: the distance to a few voxels, from its definition."""
+    occ = np.zeros(shape, np.uint8)
+    axes = [torch.arange(n, dtype=torch.int32, device="cuda:0") for n in shape]
+    want = None
+    for c in at:
+        occ[c] = 1
+        z, y, x = ((a - i) ** 2 for a, i in zip(axes, c))
+        d = z[:, None, None] + y[None, :, None] + x[None, None, :]
+        want = d if want is None else torch.minimum(want, d)
+    mid = ctx.upload(occ, 0.1, np.zeros(3), "u8")
+    try:
+        assert torch.equal(ctx.edt(mid, shape), want)
+    finally:
+        ctx.release(mid)
