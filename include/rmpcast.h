@@ -141,9 +141,10 @@ rmpc_status rmpc_destroy(rmpc_ctx *ctx);
  * The library keeps in the arena a 16-bit entry per 2 x 2 x 2 brick (its voxels' occupancy, or
  * the extents of a free box around it) and, for float maps, the grid as given (x-fastest);
  * together as much as rmpc_map_footprint says, about 1/7 more than the grid.  While it runs it
- * also uses about 1 byte of scratch per voxel: from the arena where there is room, else allocated
- * on the device for the call; if that fails too, the boxes are single bricks (the same results,
- * from slower walks).  Blocking.
+ * also uses scratch, a byte and 52 bits per brick, rows of bits padded to 64 bricks along the axis
+ * where that costs least (about 1 byte per voxel, below 14 per brick and 2 MiB): from the arena
+ * where there is room, else allocated on the device for the call; if that fails too, the boxes are
+ * single bricks (the same results, from slower walks).  Blocking.
  * Errors: RMPC_E_INVALID, RMPC_E_NOMEM (arena full), RMPC_E_HIP.
  */
 rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void *voxels,

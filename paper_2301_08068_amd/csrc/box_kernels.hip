@@ -23,6 +23,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "rmpc_device.h"
 #include "rmpc_kernels.h"
 
@@ -33,37 +35,56 @@ namespace {
 constexpr int kSteps = 6;                         // dilation steps; extents 1 .. kSteps + 1 come from them
 constexpr uint32_t kUnitBox = box_extents(1, 1, 1);
 
-// Scratch: the occupancy of every brick's voxels (a byte, rows padded to whole words), then bit
-// sets of `words` 64-bit words each.
+// Scratch: the occupancy of every brick's voxels (a byte), then bit sets of `words` 64-bit words each.
+// A set's words lie along one of the grid's axes (`axis`), its rows along the next, its planes along
+// the third: x, y, z, or with x and y, or x and z, changed over (`axis` 1, 2).  A grid a few bricks
+// wide in x has most of a word's 64 bits past its end: with words along x always, one of 2 x 2,048 x
+// 2,048 float32 voxels took 436 MB of scratch and 1,037 us to upload (now 7.9 MB, 68 us), one of
+// 1 x 4,096 x 4,096 bytes 1.8 GB and 5.4 ms (31 MB, 87 us).
 struct Scratch {
-    uint8_t *mask;                                // 0: free
-    uint64_t *layer;                              // 6: voxel layers x low, x high, y low, ... z high
-    uint64_t *cz, *cy, *cx;                       // kSteps each: dilated slabs, perpendicular to the axis
-    uint64_t *yx;                                 // 2 kSteps: the x layers dilated along y
+    BoxMask mask;                                 // 0: free
+    uint64_t *layer;                              // 6: voxel layers axis 0 low, high, axis 1 low, ...
+    uint64_t *cz, *cy, *cx;                       // kSteps each: dilated slabs, perpendicular to axis 2, 1, 0
+    uint64_t *yx;                                 // 2 kSteps: the layers of axis 0 dilated along axis 1
     uint64_t *best;                               // 6: extent (3 bits), side and axis (2 bits) of the best layer
-    uint64_t *best_y;                             // 6: of the best perpendicular to y alone
+    uint64_t *best_y;                             // 6: of the best perpendicular to axis 1 alone
     uint64_t *cube;                               // 3: bits of d
     uint64_t *full;                               // 1: d = kSteps + 1
     int64_t words;
-    int32_t pitch, w;                             // bytes, words of a row
+    int32_t axis;
+    int32_t n0, n1, n2, w;                        // bricks along the axes in this order; words of a row
+    bool wall0, wall1, wall2;                     // an odd last voxel layer without entries
 };
 constexpr int kSets = 6 + 3 * kSteps + 2 * kSteps + 6 + 3 + 1 + 6;
 
-__host__ __device__ inline int32_t row_words(const MapView &m) { return (m.nbx + 63) >> 6; }
-__host__ __device__ inline int64_t set_words(const MapView &m) { return (int64_t)row_words(m) * m.nby * m.nbz; }
-inline int64_t mask_bytes(const MapView &m)
+inline int64_t set_words(const MapView &m, int axis)
 {
-    return ((int64_t)box_mask_pitch(m) * m.nby * m.nbz + 255) / 256 * 256;
+    const int64_t n[3] = {m.nbx, m.nby, m.nbz};
+    return (n[axis] + 63) / 64 * (n[0] * n[1] * n[2] / std::max<int64_t>(n[axis], 1));
+}
+
+// The axis that words lie along: x, whose neighbours are neighbours in memory, unless another takes
+// less than three quarters of its words (48 x 400 x 400, along y half of them: 66 -> 63 us; 70 x 300 x
+// 300, 0.7 of them: 65 and 66 us).
+inline int word_axis(const MapView &m)
+{
+    const int other = set_words(m, 2) < set_words(m, 1) ? 2 : 1;
+    return 4 * set_words(m, other) < 3 * set_words(m, 0) ? other : 0;
 }
 
 Scratch scratch_at(const MapView &m, uint8_t *p)
 {
     Scratch s;
-    s.mask = p;
-    s.words = set_words(m);
-    s.pitch = box_mask_pitch(m);
-    s.w = row_words(m);
-    s.layer = reinterpret_cast<uint64_t *>(p + mask_bytes(m));
+    s.axis = word_axis(m);
+    const int32_t n[3] = {m.nbx, m.nby, m.nbz};
+    const bool wall[3] = {2 * m.nbx < m.nx, 2 * m.nby < m.ny, 2 * m.nbz < m.nz};
+    const int a1 = s.axis == 1 ? 0 : 1, a2 = s.axis == 2 ? 0 : 2;
+    s.n0 = n[s.axis]; s.n1 = n[a1]; s.n2 = n[a2];
+    s.wall0 = wall[s.axis]; s.wall1 = wall[a1]; s.wall2 = wall[a2];
+    s.w = (s.n0 + 63) >> 6;
+    s.words = set_words(m, s.axis);
+    s.mask = box_mask(m, p);
+    s.layer = reinterpret_cast<uint64_t *>(p + s.mask.bytes);
     s.cz = s.layer + 6 * s.words;
     s.cy = s.cz + kSteps * s.words;
     s.cx = s.cy + kSteps * s.words;
@@ -84,11 +105,10 @@ __device__ __forceinline__ uint16_t unit_entry(uint32_t mask)
 // copied, those outside the bricks of a partial map by copy_rest_kernel).  A thread takes W
 // consecutive bricks of a row: with W = 2 each of its four voxel rows is one load of four
 // elements (rows of a multiple of four elements, aligned), with W = 1 any grid.
-// unit: write entries of single-brick boxes instead of the mask plane.
+// UNIT: write entries of single-brick boxes instead of the masks.
 template <int DT, int W, bool UNIT>
 __global__ void __launch_bounds__(256) brick_kernel(MapView m, const typename Voxel<DT>::T *src,
-                                                    typename Voxel<DT>::T *dst, uint8_t *mask, int32_t pitch,
-                                                    uint16_t *box)
+                                                    typename Voxel<DT>::T *dst, BoxMask mask, uint16_t *box)
 {
     using T = typename Voxel<DT>::T;
     const uint32_t nw = ((uint32_t)m.nbx + W - 1) / W;
@@ -129,7 +149,7 @@ __global__ void __launch_bounds__(256) brick_kernel(MapView m, const typename Vo
     for (int i = 0; i < W; ++i) {
         if (bx + i >= (uint32_t)m.nbx) break;
         if constexpr (UNIT) box[(uint64_t)row * m.nbx + bx + i] = unit_entry(occ[i]);
-        else mask[(uint64_t)row * pitch + bx + i] = (uint8_t)occ[i];
+        else mask.at[(bx + i) * mask.sx + by * mask.sy + bz * mask.sz] = (uint8_t)occ[i];
     }
 }
 
@@ -155,21 +175,25 @@ __global__ void __launch_bounds__(256) copy_rest_kernel(MapView m, const typenam
 
 // The layer sets from the masks: a lane takes four bricks of a row, eight lanes join their bits to
 // 32-bit words.  Bricks past the row's end are free, or occupied on a partial axis (bricks there
-// have no entries, so a box must not cover them).
-__global__ void __launch_bounds__(256) layer_bits_kernel(MapView m, Scratch s)
+// have no entries, so a box must not cover them).  id: the four bricks, neighbouring lanes' one after
+// the other.
+__device__ __forceinline__ void layer_bits(const Scratch &s, int64_t id)
 {
-    const int64_t id = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x;   // four bricks
     const int64_t row = id / (16 * s.w);
     const int x = (int)(id - row * 16 * s.w) * 4;
-    const bool in = row < (int64_t)m.nby * m.nbz;
-    uint32_t v = 2 * m.nbx < m.nx ? ~0u : 0u;
-    if (in && x < m.nbx) {
-        const uint32_t last = m.nbx - x;                               // bricks of the row from here
+    const bool in = row < (int64_t)s.n1 * s.n2;
+    uint32_t v = s.wall0 ? ~0u : 0u;
+    if (in && x < s.n0) {
+        const uint32_t last = s.n0 - x;                                // bricks of the row from here
         const uint32_t past = last < 4 ? ~0u << (8 * last) : 0u;
-        v = (*reinterpret_cast<const uint32_t *>(s.mask + row * s.pitch + x) & ~past) | (v & past);
+        v = (*reinterpret_cast<const uint32_t *>(s.mask.at + row * (int64_t)s.mask.pitch + x) & ~past) | (v & past);
     }
-    const uint32_t sel[6] = {0x55u, 0xaau, 0x33u, 0xccu, 0x0fu, 0xf0u};
-    const int shift = 4 * (threadIdx.x & 7);
+    // the voxels of a layer, by the layer's axis in the sets' order
+    const uint32_t selx = 0x55u, sely = 0x33u, selz = 0x0fu;
+    const uint32_t sel0 = s.axis == 0 ? selx : (s.axis == 1 ? sely : selz), sel1 = s.axis == 1 ? selx : sely,
+                   sel2 = s.axis == 2 ? selx : selz;
+    const uint32_t sel[6] = {sel0, ~sel0 & 0xffu, sel1, ~sel1 & 0xffu, sel2, ~sel2 & 0xffu};
+    const int lane = (int)(id & 7), shift = 4 * lane;
     uint32_t mine = 0;
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
@@ -179,20 +203,25 @@ __global__ void __launch_bounds__(256) layer_bits_kernel(MapView m, Scratch s)
         uint32_t b = ((((top >> 7) * 0x01020408u) >> 24) & 15u) << shift;
 #pragma unroll
         for (int o = 1; o < 8; o <<= 1) b |= __shfl_xor(b, o, 8);
-        mine = (threadIdx.x & 7) == k ? b : mine;
+        mine = lane == k ? b : mine;
     }
-    if (in && (threadIdx.x & 7) < 6)
-        reinterpret_cast<uint32_t *>(s.layer + (threadIdx.x & 7) * s.words)[id >> 3] = mine;
+    if (in && lane < 6) reinterpret_cast<uint32_t *>(s.layer + lane * s.words)[id >> 3] = mine;
 }
 
-// One word of a set, its row and its place: rows along y are w words apart, along z w nby.
+__global__ void __launch_bounds__(256) layer_bits_kernel(Scratch s)
+{
+    layer_bits(s, (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
+}
+
+// One word of a set, its row and its place: rows are w words apart, planes w n1 (x, y and z below
+// stand for the sets' axes in their order).
 struct Place {
     int64_t at, sy, sz;
     int wi, w, y, ny, z, nz;
     bool wall_x, wall_y, wall_z, ok;
 };
 
-__device__ __forceinline__ Place place_of(const MapView &m, const Scratch &s, int64_t id)
+__device__ __forceinline__ Place place_of(const Scratch &s, int64_t id)
 {
     Place p;
     p.ok = id < s.words;
@@ -200,15 +229,15 @@ __device__ __forceinline__ Place place_of(const MapView &m, const Scratch &s, in
     p.w = s.w;
     const int64_t row = p.at / s.w;
     p.wi = (int)(p.at - row * s.w);
-    p.z = (int)(row / m.nby);
-    p.y = (int)(row - (int64_t)p.z * m.nby);
-    p.ny = m.nby;
-    p.nz = m.nbz;
+    p.z = (int)(row / s.n1);
+    p.y = (int)(row - (int64_t)p.z * s.n1);
+    p.ny = s.n1;
+    p.nz = s.n2;
     p.sy = s.w;
-    p.sz = (int64_t)s.w * m.nby;
-    p.wall_x = 2 * m.nbx < m.nx;
-    p.wall_y = 2 * m.nby < m.ny;
-    p.wall_z = 2 * m.nbz < m.nz;
+    p.sz = (int64_t)s.w * s.n1;
+    p.wall_x = s.wall0;
+    p.wall_y = s.wall1;
+    p.wall_z = s.wall2;
     return p;
 }
 
@@ -370,18 +399,16 @@ __device__ __forceinline__ void plane(const Scratch &s, const Place &p, int axis
     best.offer(qb, true, axis);
 }
 
-// Layers perpendicular to z (blockIdx.y 0) and y (1), and the first half (along y) of those
+// Layers perpendicular to z (kind, blockIdx.y, 0) and y (1), and the first half (along y) of those
 // perpendicular to x (2).  A thread per word leaves a SIMD two waves on a 400^3 map, waiting for
 // loads: three kinds of blocks instead of one thread doing all of it, and two in the next kernel,
 // 26 + 30 us -> 22 + 19 (with the blocks of
 // neighbouring words on one XCD; 22 + 26 without).
-__global__ void __launch_bounds__(256) planes_kernel(MapView m, Scratch s)
+__device__ __forceinline__ void planes(const Scratch &s, const Place &p, int kind)
 {
-    const Place p = place_of(m, s, (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
-    if (!p.ok) return;
-    if (blockIdx.y < 2) {
+    if (kind < 2) {
         Best best{Count{0, 0, 0}, ~0ull, ~0ull, ~0ull};
-        if (blockIdx.y == 0) {
+        if (kind == 0) {
             plane(s, p, 2, s.cz, best);
             best.store(s.best, s.words, p.at);
         } else {
@@ -402,12 +429,16 @@ __global__ void __launch_bounds__(256) planes_kernel(MapView m, Scratch s)
     }
 }
 
-// Layers perpendicular to x (the second half, along z; blockIdx.y 0), and the cubes (1).
-__global__ void __launch_bounds__(256) cubes_kernel(MapView m, Scratch s)
+__global__ void __launch_bounds__(256) planes_kernel(Scratch s)
 {
-    const Place p = place_of(m, s, (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
-    if (!p.ok) return;
-    if (blockIdx.y == 1) {
+    const Place p = place_of(s, (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
+    if (p.ok) planes(s, p, blockIdx.y);
+}
+
+// Layers perpendicular to x (the second half, along z; kind 0), and the cubes (1).
+__device__ __forceinline__ void cubes(const Scratch &s, const Place &p, int kind)
+{
+    if (kind == 1) {
         Count d{~0ull, 0, 0};
 #pragma unroll
         for (int k = 1; k <= kSteps; ++k) {
@@ -446,6 +477,12 @@ __global__ void __launch_bounds__(256) cubes_kernel(MapView m, Scratch s)
     best.offer(q[0], false, 0);
     best.offer(q[1], true, 0);
     best.store(s.best, s.words, p.at);
+}
+
+__global__ void __launch_bounds__(256) cubes_kernel(Scratch s)
+{
+    const Place p = place_of(s, (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
+    if (p.ok) cubes(s, p, blockIdx.y);
 }
 
 // Extents (bit-sliced) of the slab of half thickness d (1 .. 3: masks t1, t2, t3) perpendicular to
@@ -515,10 +552,8 @@ __device__ __forceinline__ uint64_t *entry_plane(const Scratch &s, int k)
     return k < 6 ? s.layer + k * s.words : s.best + (k - 6) * s.words;
 }
 
-__global__ void __launch_bounds__(256) select_kernel(MapView m, Scratch s)
+__device__ __forceinline__ void select(const Scratch &s, const Place &p)
 {
-    const Place p = place_of(m, s, (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
-    if (!p.ok) return;
     const uint64_t *c = s.cube + p.at;
     const Count d{c[0], c[s.words], c[2 * s.words]};
     const uint64_t t1 = d.b0 & ~d.b1 & ~d.b2, t2 = ~d.b0 & d.b1 & ~d.b2, t3 = d.b0 & d.b1 & ~d.b2;
@@ -536,10 +571,23 @@ __global__ void __launch_bounds__(256) select_kernel(MapView m, Scratch s)
     q = pick(px, qx, q);
     const uint64_t use = (t1 | t2 | t3) & above(q, d);
     const uint64_t ax = use & px, ay = use & ~px & ~yz, az = use & ~px & yz;
-    const Count ex = pick(use & ~ax, q, d), ey = pick(use & ~ay, q, d), ez = pick(use & ~az, q, d);
+    Count ex = pick(use & ~ax, q, d), ey = pick(use & ~ay, q, d), ez = pick(use & ~az, q, d);
     const uint64_t occ = s.layer[4 * s.words + p.at] | s.layer[5 * s.words + p.at];
     const uint64_t *h = s.best + p.at;
-    const uint64_t h0 = h[0], h1 = h[s.words], h2 = h[2 * s.words], side = h[3 * s.words], a0 = h[4 * s.words], a1 = h[5 * s.words];
+    const uint64_t h0 = h[0], h1 = h[s.words], h2 = h[2 * s.words], side = h[3 * s.words];
+    uint64_t a0 = h[4 * s.words], a1 = h[5 * s.words];
+    // from the sets' axes back to the grid's
+    if (s.axis == 1) {
+        const Count e = ex;
+        ex = ey;
+        ey = e;
+        a0 ^= ~a1;                                    // 0 <-> 1
+    } else if (s.axis == 2) {
+        const Count e = ex;
+        ex = ez;
+        ez = e;
+        a1 ^= ~a0;                                    // 0 <-> 2
+    }
     const uint64_t far3 = far_bits<3>(s, p), far6 = far_bits<6>(s, p);
     // bits 1-3, 6-8, 11-13 of a free brick's entry; bits 8, 9, 10, 11-13 of an occupied one's; bit 15;
     // half extent 10, 13
@@ -550,6 +598,12 @@ __global__ void __launch_bounds__(256) select_kernel(MapView m, Scratch s)
     for (int k = 0; k < kEntryPlanes; ++k) entry_plane(s, k)[p.at] = o[k];
 }
 
+__global__ void __launch_bounds__(256) select_kernel(Scratch s)
+{
+    const Place p = place_of(s, (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
+    if (p.ok) select(s, p);
+}
+
 // The entries: a wave writes those of kExpandWords consecutive words (64 each), each lane picking its
 // bit of every plane.  The planes' words come by scalar loads of several words at once: a word at a
 // time, 14 loads of 8 bytes for 128 bytes of entries left the kernel waiting for them (43 us
@@ -557,7 +611,13 @@ __global__ void __launch_bounds__(256) select_kernel(MapView m, Scratch s)
 // four words spill scalar registers: 33).
 constexpr int kExpandWords = 2;
 
-__global__ void __launch_bounds__(256) expand_kernel(MapView m, Scratch s, uint16_t *box)
+// Where the entry of the sets' brick (0, 0, 0) lies, and those one on along each axis.
+struct BoxOut {
+    uint16_t *box;
+    uint32_t s0, s1, s2;
+};
+
+__global__ void __launch_bounds__(256) expand_kernel(Scratch s, BoxOut out)
 {
     const uint32_t word0 = __builtin_amdgcn_readfirstlane((xcd_tile(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6)) * kExpandWords);
     if (word0 >= (uint32_t)s.words) return;
@@ -582,9 +642,11 @@ __global__ void __launch_bounds__(256) expand_kernel(MapView m, Scratch s, uint1
         e = __builtin_amdgcn_inverse_ballot_w64(v[12][i]) ? box_extents(10, 10, 10) : e;
         e = __builtin_amdgcn_inverse_ballot_w64(v[13][i]) ? box_extents(13, 13, 13) : e;
         const int x = (int)wi * 64 + (int)(threadIdx.x & 63);
-        if (x < m.nbx) {
-            const uint32_t mask = s.mask[(uint64_t)row * s.pitch + x];     // 0 for a free brick
-            box[(uint64_t)row * m.nbx + x] = (uint16_t)(e | mask);
+        if (x < s.n0) {
+            // (words along x: the planes' rows follow one another)
+            const uint32_t z = s.axis ? row / (uint32_t)s.n1 : 0u, y = row - z * (uint32_t)s.n1;
+            const uint32_t mask = s.mask.at[row * s.mask.pitch + x];              // 0 for a free brick
+            out.box[x * out.s0 + y * out.s1 + z * out.s2] = (uint16_t)(e | mask);
         }
         if (++wi == (uint32_t)s.w) {
             wi = 0;
@@ -596,14 +658,14 @@ __global__ void __launch_bounds__(256) expand_kernel(MapView m, Scratch s, uint1
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 template <int DT, int W, bool UNIT>
-void launch_bricks(const BoxArgs &a, uint8_t *mask, int32_t pitch, hipStream_t s)
+void launch_bricks(const BoxArgs &a, const BoxMask &mask, hipStream_t s)
 {
     using T = typename Voxel<DT>::T;
     const MapView &m = a.map;
     T *dst = DT == RMPC_OCC_U8 || a.src == m.data ? nullptr : static_cast<T *>(const_cast<void *>(m.data));
     const int64_t n = (int64_t)((m.nbx + W - 1) / W) * m.nby * m.nbz;
     if (n > 0)
-        brick_kernel<DT, W, UNIT><<<blocks_for(n), 256, 0, s>>>(m, static_cast<const T *>(a.src), dst, mask, pitch,
+        brick_kernel<DT, W, UNIT><<<blocks_for(n), 256, 0, s>>>(m, static_cast<const T *>(a.src), dst, mask,
                                                                const_cast<uint16_t *>(m.box));
     if (dst && m.partial) {
         const uint32_t row_blocks = 2 * m.nbx < m.nx ? blocks_for((int64_t)m.ny * m.nz) : 0u;
@@ -620,11 +682,13 @@ void launch_extents(const MapView &m, const Scratch &p, hipStream_t s)
     // every launch's blocks in eight equal runs of words, one per XCD: a kernel's reads of the set
     // before and of rows above and below find most of them in their own L2
     auto blocks = [](int64_t n) { return blocks_for((n + 2047) / 2048 * 2048); };
-    layer_bits_kernel<<<blocks(16 * p.words), 256, 0, s>>>(m, p);
-    planes_kernel<<<dim3(blocks(p.words), 3), 256, 0, s>>>(m, p);
-    cubes_kernel<<<dim3(blocks(p.words), 2), 256, 0, s>>>(m, p);
-    select_kernel<<<blocks(p.words), 256, 0, s>>>(m, p);
-    expand_kernel<<<blocks((p.words + kExpandWords - 1) / kExpandWords * 64), 256, 0, s>>>(m, p, const_cast<uint16_t *>(m.box));
+    const uint32_t st[3] = {1u, (uint32_t)m.nbx, (uint32_t)m.nbx * (uint32_t)m.nby};
+    const BoxOut out{const_cast<uint16_t *>(m.box), st[p.axis], st[p.axis == 1 ? 0 : 1], st[p.axis == 2 ? 0 : 2]};
+    layer_bits_kernel<<<blocks(16 * p.words), 256, 0, s>>>(p);
+    planes_kernel<<<dim3(blocks(p.words), 3), 256, 0, s>>>(p);
+    cubes_kernel<<<dim3(blocks(p.words), 2), 256, 0, s>>>(p);
+    select_kernel<<<blocks(p.words), 256, 0, s>>>(p);
+    expand_kernel<<<blocks((p.words + kExpandWords - 1) / kExpandWords * 64), 256, 0, s>>>(p, out);
 }
 
 template <int DT>
@@ -634,24 +698,35 @@ void launch_boxes_dt(const BoxArgs &a, hipStream_t s)
     const MapView &m = a.map;
     const bool wide = m.nx % 4 == 0 && reinterpret_cast<uintptr_t>(a.src) % (4 * sizeof(T)) == 0;
     if (!a.scratch) {
-        if (wide) launch_bricks<DT, 2, true>(a, nullptr, 0, s);
-        else launch_bricks<DT, 1, true>(a, nullptr, 0, s);
+        if (wide) launch_bricks<DT, 2, true>(a, BoxMask{}, s);
+        else launch_bricks<DT, 1, true>(a, BoxMask{}, s);
         return;
     }
     const Scratch p = scratch_at(m, a.scratch);
-    if (wide) launch_bricks<DT, 2, false>(a, p.mask, p.pitch, s);
-    else launch_bricks<DT, 1, false>(a, p.mask, p.pitch, s);
+    if (wide) launch_bricks<DT, 2, false>(a, p.mask, s);
+    else launch_bricks<DT, 1, false>(a, p.mask, s);
     launch_extents(m, p, s);
 }
 
 }  // namespace
 
-size_t box_scratch_bytes(const MapView &m)
+BoxMask box_mask(const MapView &m, uint8_t *scratch)
 {
-    return set_words(m) == 0 ? 0 : (size_t)(mask_bytes(m) + 8 * kSets * set_words(m));
+    const int axis = word_axis(m);
+    const uint32_t n[3] = {(uint32_t)m.nbx, (uint32_t)m.nby, (uint32_t)m.nbz}, pitch = (n[axis] + 3u) & ~3u;
+    const int a1 = axis == 1 ? 0 : 1, a2 = axis == 2 ? 0 : 2;
+    uint32_t st[3];
+    st[axis] = 1;
+    st[a1] = pitch;
+    st[a2] = pitch * n[a1];
+    return BoxMask{scratch, st[0], st[1], st[2], pitch, ((size_t)st[a2] * n[a2] + 255) / 256 * 256};
 }
 
-int32_t box_mask_pitch(const MapView &m) { return (m.nbx + 3) & ~3; }
+size_t box_scratch_bytes(const MapView &m)
+{
+    const int64_t words = set_words(m, word_axis(m));
+    return words == 0 ? 0 : box_mask(m, nullptr).bytes + (size_t)(8 * kSets * words);
+}
 
 void launch_cell_boxes(const MapView &m, uint8_t *scratch, hipStream_t s) { launch_extents(m, scratch_at(m, scratch), s); }
 

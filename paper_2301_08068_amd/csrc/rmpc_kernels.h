@@ -289,9 +289,16 @@ hipError_t launch_sparse_masks(const SparseView &v, HashEntry *table, hipStream_
 // sparse_index_scratch_bytes, 256-byte aligned.
 size_t sparse_index_scratch_bytes(const SparseView &v);
 hipError_t launch_sparse_index(const SparseView &v, uint8_t *scratch, hipStream_t s);
-// The boxes of a grid of nbx x nby x nbz cells from their occupancy, one byte a cell (0 or 255) at
-// the start of scratch (zeroed by the caller; rows of box_mask_pitch bytes), written to box.
-int32_t box_mask_pitch(const MapView &m);
+// Where launch_cell_boxes reads a cell's occupancy in its scratch: one byte (0 or 255) each, cell
+// (x, y, z) at x sx + y sy + z sz (at most 2^28 cells); rows of `pitch` bytes, in all `bytes`.
+struct BoxMask {
+    uint8_t *at;
+    uint32_t sx, sy, sz, pitch;
+    size_t bytes;
+};
+BoxMask box_mask(const MapView &m, uint8_t *scratch);
+// The boxes of a grid of nbx x nby x nbz cells from their occupancy at the start of scratch
+// (box_scratch_bytes; the occupancy zeroed and set by the caller), written to box.
 void launch_cell_boxes(const MapView &m, uint8_t *scratch, hipStream_t s);
 // Persistent fused batch: `blocks` resident blocks pull tiles from a counter.
 hipError_t launch_batch(const BatchArgs &a, int blocks, hipStream_t s);

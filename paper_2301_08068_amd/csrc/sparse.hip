@@ -86,7 +86,7 @@ __global__ void sparse_flag_kernel(SparseView v, HashEntry *table)
 }
 
 // The index's occupied blocks, from the table: their slots, and 255 in the cells' occupancy.
-__global__ void __launch_bounds__(256) index_slots_kernel(SparseView v, uint32_t *index, uint8_t *mask, int32_t pitch)
+__global__ void __launch_bounds__(256) index_slots_kernel(SparseView v, uint32_t *index, BoxMask mask)
 {
     const uint32_t i = blockIdx.x * 256 + threadIdx.x;
     if (i > v.table_mask) return;
@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(256) index_slots_kernel(SparseView v, uint32_t
     const int z = (int)((uint32_t)(e.key >> 42) & bits) - kBlockCoordBias - v.lo[2];
     const int64_t row = y + (int64_t)v.nb[1] * z;
     index[x + v.nb[0] * row] = kBlockOccupied | (uint32_t)e.slot;
-    mask[x + pitch * row] = 255u;
+    mask.at[x * mask.sx + y * mask.sy + z * mask.sz] = 255u;
 }
 
 // The other blocks' boxes.
@@ -250,10 +250,10 @@ hipError_t launch_sparse_index(const SparseView &v, uint8_t *scratch, hipStream_
     uint32_t *index = const_cast<uint32_t *>(v.index);
     uint16_t *bricks = const_cast<uint16_t *>(v.bricks);
     m.box = box;
-    const int32_t pitch = box_mask_pitch(m);
-    if (hipError_t e = hipMemsetAsync(scratch, 0, (size_t)pitch * m.nby * m.nbz, s)) return e;
+    const BoxMask mask = box_mask(m, scratch);
+    if (hipError_t e = hipMemsetAsync(scratch, 0, mask.bytes, s)) return e;
     if (hipError_t e = hipMemsetAsync(index, 0, sizeof(uint32_t) * (size_t)cells, s)) return e;
-    index_slots_kernel<<<(v.table_mask + 256) / 256, 256, 0, s>>>(v, index, scratch, pitch);
+    index_slots_kernel<<<(v.table_mask + 256) / 256, 256, 0, s>>>(v, index, mask);
     launch_cell_boxes(m, scratch, s);
     index_boxes_kernel<<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(index, box, cells);
     brick_masks_kernel<<<(unsigned)((v.n_slots + 3) / 4), 256, 0, s>>>(v, bricks, bits);

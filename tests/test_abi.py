@@ -123,3 +123,21 @@ def test_result_columns_equal_single_results(lib_path, n):
         for k, field in (("f", r.f), ("S", r.A), ("b", r.b), ("lam", r.lam)):
             assert d[k].tobytes() == bytes(field) and d[k].flags.writeable
         assert (d["rank"], d["flags"], d["visits"]) == (r.rank, r.flags, r.visits)
+
+
+@pytest.mark.parametrize("dims", [(400, 400, 400), (64, 64, 64), (130, 130, 130), (8, 4096, 4096), (1, 4096, 4096),
+                                  (2, 2048, 2048), (16, 2000, 2000), (6, 7, 4096), (4096, 1, 4096), (8, 8, 8), (1, 1, 1)])
+def test_upload_scratch_is_bounded(lib_path, dims):
+    """The scratch of an upload: a byte and 52 bits a brick of 2^3 voxels, rows of bits padded to 64
+    bricks along the axis where that costs least: below 14 bytes a brick, and 2 MiB."""
+    import ctypes as C
+
+    class MapView(C.Structure):
+        _fields_ = [("data", C.c_void_p), ("box", C.c_void_p)] + \
+            [(k, C.c_int32) for k in ("nx", "ny", "nz", "dtype", "nbx", "nby", "nbz", "partial", "lo", "span")]
+
+    scratch = C.CDLL(lib_path)._ZN4rmpc17box_scratch_bytesERKNS_7MapViewE
+    scratch.restype = C.c_size_t
+    nb = [-(-n // 2) for n in dims]
+    m = MapView(nx=dims[0], ny=dims[1], nz=dims[2], nbx=nb[0], nby=nb[1], nbz=nb[2])
+    assert scratch(C.byref(m)) < 14 * nb[0] * nb[1] * nb[2] + (2 << 20)

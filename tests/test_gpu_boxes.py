@@ -202,3 +202,13 @@ def test_the_whole_grid_is_copied(dims, dtype):
         assert torch.equal(arena[base:base + dev.numel()], dev)
     finally:
         B.rmpc_destroy(ctx)
+
+
+# words along y and along z: a few bricks wide in x, up to and past words of 64 bricks, odd extents
+@pytest.mark.parametrize("dtype", ["f32", "f16", "u8"])
+@pytest.mark.parametrize("dims,density", [((2, 128, 60), 0.002), ((1, 257, 9), 0.02), ((7, 131, 33), 0.003), ((3, 300, 258), 0.0005),
+                                          ((6, 4, 150), 0.01), ((5, 3, 259), 0.01), ((1, 1, 384), 0.02), ((9, 34, 129), 0.0005),
+                                          ((40, 300, 40), 0.0)])
+def test_boxes_of_narrow_grids(dims, density, dtype):
+    """As above, where the bit sets' words lie along another axis than x."""
+    test_boxes_are_free_and_layers_exact(dims, density, dtype)
