@@ -440,6 +440,7 @@ rmpc_status rmpc_create(int device, void *arena_dev, size_t arena_bytes, rmpc_ct
     c->ev_dep = nullptr;
     c->server = nullptr;
     c->cu_count = 0;
+    c->scratch_limit = SIZE_MAX;
     c->profiling = false;
     c->ev0 = c->ev1 = nullptr;
     c->prof_ms = 0.0;
@@ -574,9 +575,10 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
     rmpc::BoxArgs A{v, voxels, nullptr};
     size_t scratch_off = 0;
     void *scratch_dev = nullptr;
-    const bool in_arena = scratch_bytes > 0 && ctx->alloc.alloc(scratch_bytes, &scratch_off);
+    const bool wanted = scratch_bytes > 0 && scratch_bytes <= ctx->scratch_limit;
+    const bool in_arena = wanted && ctx->alloc.alloc(scratch_bytes, &scratch_off);
     if (in_arena) A.scratch = ctx->arena + scratch_off;
-    else if (scratch_bytes > 0 && hipMalloc(&scratch_dev, scratch_bytes) == hipSuccess) A.scratch = static_cast<uint8_t *>(scratch_dev);
+    else if (wanted && hipMalloc(&scratch_dev, scratch_bytes) == hipSuccess) A.scratch = static_cast<uint8_t *>(scratch_dev);
     else (void)hipGetLastError();
     // the kernels read the caller's buffer themselves when it is memory of this GPU; any other
     // pointer is copied to the arena first
@@ -697,7 +699,7 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
     DeviceScratch scratch;
     if (indexed) {
         scratch_bytes = rmpc::sparse_index_scratch_bytes(v);
-        indexed = scratch.get(scratch_bytes);
+        indexed = scratch_bytes <= ctx->scratch_limit && scratch.get(scratch_bytes);
     }
     if (indexed) cap64 /= 4;
     const uint32_t cap = (uint32_t)cap64;
@@ -770,6 +772,8 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
     *map_id_out = id;
     return RMPC_OK;
 }
+
+void rmpc_internal_scratch_limit(rmpc_ctx *ctx, size_t bytes) { ctx->scratch_limit = bytes; }
 
 rmpc_status rmpc_map_release(rmpc_ctx *ctx, int32_t map_id)
 {

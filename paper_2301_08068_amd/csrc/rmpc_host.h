@@ -94,6 +94,7 @@ struct rmpc_ctx {
     int32_t next_map_id;
     rmpc_launch_config cfg[3];  // RMPC_CONFIG_QUERY, RMPC_CONFIG_BATCH, RMPC_CONFIG_SPARSE
     int cu_count;
+    size_t scratch_limit;       // most scratch a map upload takes (rmpc_internal_scratch_limit)
     rmpc_host::LaunchSlot batch;          // rmpc_query_batch (allocated on first use)
     // streams of destroyed launch slots, kept for the next slots: a server that is stopped and
     // started again reuses them (creating streams again and again made a later server's first
@@ -107,6 +108,10 @@ struct rmpc_ctx {
     double prof_ms;
     int64_t prof_n;
 };
+
+// Not part of the C ABI: uploads into this context take no more scratch than this (SIZE_MAX: as much
+// as they need), for tests of the paths that a full device leaves.
+extern "C" void rmpc_internal_scratch_limit(rmpc_ctx *ctx, size_t bytes);
 
 namespace rmpc_host {
 

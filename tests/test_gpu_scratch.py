@@ -1,0 +1,96 @@
+"""Uploads that get no scratch (a full arena on a full device): maps walked by narrower boxes, or by
+the block table, give the same hits, distances, visits and sums."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import oracle  # noqa: E402
+from gpu_common import compare_trace  # noqa: E402
+from paper_2301_08068_amd import workloads as W  # noqa: E402
+
+P = W.params("static", max_range=5.0)
+
+
+@pytest.fixture()
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2301_08068_amd import binding
+    c = binding.Context(0, arena_bytes=64 << 20)
+    yield c
+    c.close()
+
+
+def _limit(c, n):
+    from paper_2301_08068_amd import binding
+    binding._lib.rmpc_internal_scratch_limit(C.c_void_p(c.ptr), C.c_size_t(n))
+
+
+def _same_query(a, b):
+    for k in ("f", "S", "b", "lam"):
+        assert np.array_equal(a[k], b[k]), k
+    for k in ("rank", "n_hit", "n_contrib", "visits"):
+        assert a[k] == b[k], k
+
+
+# even extents, odd ones (an odd last layer without entries for some types), walls of bricks at the
+# edges, a single layer, fewer bricks than a box reaches
+@pytest.mark.parametrize("on_device", [True, False])
+@pytest.mark.parametrize("enc", ["f32", "f16", "u8"])
+@pytest.mark.parametrize("dims,p", [((64, 48, 40), 0.003), ((61, 47, 33), 0.003), ((63, 1, 65), 0.01), ((5, 3, 4), 0.05),
+                                    ((1, 1, 1), 0.0), ((40, 41, 39), 0.0)])
+def test_dense_without_scratch(ctx, dims, p, enc, on_device):
+    nx, ny, nz = dims
+    rng = np.random.default_rng(sum(dims))
+    t = np.where(rng.uniform(size=(nz, ny, nx)) < p, -0.05, 0.3).astype(np.float32)
+    data = {"f32": t, "f16": W.encode_f16(t), "u8": W.encode_u8(t)}[enc]
+    om = oracle.OracleMap(data, 0.1, np.zeros(3), enc)
+    full = ctx.upload(data, 0.1, np.zeros(3), enc, on_device=on_device)
+    _limit(ctx, 0)
+    mid = ctx.upload(data, 0.1, np.zeros(3), enc, on_device=on_device)
+    free = np.argwhere(t > 0)
+    for at in free[rng.integers(len(free), size=4)]:
+        x = (at[::-1] + rng.uniform(0.1, 0.9, 3)) * 0.1
+        o = oracle.trace(om, oracle.grid_start(om, x), oracle.directions(4096), P["max_range"])
+        compare_trace(ctx.trace(mid, x, 4096, P), o, f"{dims} {enc}")
+        v = rng.normal(size=3)
+        _same_query(ctx.query(mid, x, v, 1000, P), ctx.query(full, x, v, 1000, P))
+    assert torch.equal(ctx.edt(mid, t.shape), ctx.edt(full, t.shape))
+
+
+@pytest.mark.parametrize("enc,subvoxel", [("f32", 0), ("f16", 1), ("u8", 0)])
+def test_sparse_without_scratch(ctx, tiny_map, enc, subvoxel):
+    """Walked by the table instead of the index."""
+    sm = W.sparse_from_dense(tiny_map, offset_blocks=(-3, 2, 5), keep_free=0.3, seed=4)
+    data = {"f32": sm.values, "f16": W.encode_f16(sm.values), "u8": W.encode_u8(sm.values)}[enc]
+    full = ctx.upload_sparse(sm.coords, data, sm.voxel_m, sm.origin_m, enc)
+    _limit(ctx, 0)
+    mid = ctx.upload_sparse(sm.coords, data, sm.voxel_m, sm.origin_m, enc)
+    p = dict(P, subvoxel=subvoxel)
+    for seed in range(6):
+        x, v = W.free_state(tiny_map, seed)
+        x = x + np.array([-3, 2, 5]) * 8 * sm.voxel_m + (sm.origin_m - tiny_map.origin_m)
+        a, b = ctx.trace(mid, x, 4096, p), ctx.trace(full, x, 4096, p)
+        for k in ("hit", "d", "visits"):
+            assert np.array_equal(a[k], b[k]), (seed, k)
+        _same_query(ctx.query(mid, x, v, 4096, p), ctx.query(full, x, v, 4096, p))
+        if not subvoxel:
+            q = [dict(kind="map", map_id=m, n=700, x=x, v=v) for m in (mid, full)]
+            _same_query(*ctx.query_batch(q, p, None))
+
+
+@pytest.mark.parametrize("short", [0, 1])
+def test_scratch_is_all_or_nothing(ctx, short):
+    """A limit of exactly the need, and one byte less."""
+    t = np.full((40, 40, 40), 0.3, np.float32)
+    t[30] = -0.1
+    need = 20 * 20 * 20 // 256 * 256 + 256 + 8 * 52 * 20 * 20          # masks (20 bytes a row), 52 bit sets of a word a row
+    _limit(ctx, need - short)
+    mid = ctx.upload(t, 0.1, np.zeros(3), "f32")
+    om = oracle.OracleMap(t, 0.1, np.zeros(3), "f32")
+    x = np.array([2.03, 1.97, 1.01])
+    compare_trace(ctx.trace(mid, x, 4096, P), oracle.trace(om, oracle.grid_start(om, x), oracle.directions(4096), P["max_range"]))
