@@ -144,7 +144,7 @@ rmpc_status rmpc_destroy(rmpc_ctx *ctx);
  * also uses scratch, a byte and 52 bits per brick, rows of bits padded to 64 bricks along the axis
  * where that costs least (about 1 byte per voxel, below 14 per brick and 2 MiB): from the arena
  * where there is room, else allocated on the device for the call; if that fails too, the boxes are
- * single bricks (the same results, from slower walks).  Blocking.
+ * narrower (the same results, from slower walks).  Blocking.
  * Errors: RMPC_E_INVALID, RMPC_E_NOMEM (arena full), RMPC_E_HIP.
  */
 rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void *voxels,

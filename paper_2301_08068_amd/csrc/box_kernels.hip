@@ -655,6 +655,47 @@ __global__ void __launch_bounds__(256) expand_kernel(Scratch s, BoxOut out)
     }
 }
 
+// Without scratch, after the single-brick entries: free cubes, in place and doubling.  The first step
+// gives half extent 2 to the free bricks whose 26 neighbours are free; a later one gives half
+// extent `to` to those whose eight neighbours `step` bricks away along every axis have at least
+// `from` (their cubes cover the wider one).  An entry only grows, and stays free or occupied, so it does
+// not matter whether a neighbour is read before or after it has grown in the same step.
+// (65,536 rays from the middle of 400^3 voxels, 1 in 10,000 occupied: 64 us by single-brick boxes, 29
+// with these, 27 with the extents.  The upload without scratch takes 576 us, of which 115 are not
+// these; 208 with scratch.)
+struct Widen {
+    int32_t from, step, to;
+};
+constexpr Widen kWiden[] = {{1, 1, 2}, {2, 1, 3}, {3, 2, 5}, {5, 4, 9}};
+
+__global__ void __launch_bounds__(256) widen_kernel(MapView m, uint16_t *box, Widen g)
+{
+    const uint64_t id = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (id >= (uint64_t)m.nbx * m.nby * m.nbz) return;
+    auto entry = [&](uint64_t at) { return (uint32_t)__hip_atomic_load(box + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); };
+    const uint32_t own = entry(id);
+    // (all three extents of an entry are the same here)
+    if (own >= kBoxOccupied || (own & 31u) < 2u * (uint32_t)g.from) return;
+    const uint32_t row = (uint32_t)(id / (uint32_t)m.nbx);
+    const int x = (int)(id - (uint64_t)row * m.nbx), z = (int)(row / (uint32_t)m.nby), y = (int)(row - (uint32_t)z * m.nby);
+    // past a partial axis lie voxels without entries; past the others, where everything is free, the
+    // last brick stands for those beyond it (of a cube there only the part in the grid matters)
+    if ((2 * m.nbx < m.nx && x + g.step >= m.nbx) || (2 * m.nby < m.ny && y + g.step >= m.nby) ||
+        (2 * m.nbz < m.nz && z + g.step >= m.nbz))
+        return;
+    const int by = g.from == 1 ? 1 : 2;                       // the first step looks at the bricks between too
+    for (int c = -1; c <= 1; c += by)
+        for (int b = -1; b <= 1; b += by)
+            for (int a = -1; a <= 1; a += by) {
+                const int i = min(max(x + a * g.step, 0), m.nbx - 1), j = min(max(y + b * g.step, 0), m.nby - 1),
+                          k = min(max(z + c * g.step, 0), m.nbz - 1);
+                const uint32_t e = entry((uint64_t)i + (uint64_t)m.nbx * ((uint64_t)j + (uint64_t)m.nby * k));
+                if (e >= kBoxOccupied || (e & 31u) < 2u * (uint32_t)g.from) return;
+            }
+    const uint32_t to = (uint32_t)g.to;
+    __hip_atomic_store(box + id, (uint16_t)box_extents(to, to, to), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 template <int DT, int W, bool UNIT>
@@ -691,6 +732,13 @@ void launch_extents(const MapView &m, const Scratch &p, hipStream_t s)
     expand_kernel<<<blocks((p.words + kExpandWords - 1) / kExpandWords * 64), 256, 0, s>>>(p, out);
 }
 
+void launch_widen(const MapView &m, hipStream_t s)
+{
+    const int64_t n = (int64_t)m.nbx * m.nby * m.nbz;
+    if (n == 0) return;
+    for (const Widen &g : kWiden) widen_kernel<<<blocks_for(n), 256, 0, s>>>(m, const_cast<uint16_t *>(m.box), g);
+}
+
 template <int DT>
 void launch_boxes_dt(const BoxArgs &a, hipStream_t s)
 {
@@ -700,6 +748,7 @@ void launch_boxes_dt(const BoxArgs &a, hipStream_t s)
     if (!a.scratch) {
         if (wide) launch_bricks<DT, 2, true>(a, BoxMask{}, s);
         else launch_bricks<DT, 1, true>(a, BoxMask{}, s);
+        launch_widen(m, s);
         return;
     }
     const Scratch p = scratch_at(m, a.scratch);
@@ -729,6 +778,12 @@ size_t box_scratch_bytes(const MapView &m)
 }
 
 void launch_cell_boxes(const MapView &m, uint8_t *scratch, hipStream_t s) { launch_extents(m, scratch_at(m, scratch), s); }
+
+hipError_t launch_unit_boxes(const MapView &m, hipStream_t s)
+{
+    launch_widen(m, s);
+    return hipGetLastError();
+}
 
 hipError_t launch_map_boxes(const BoxArgs &a, hipStream_t s)
 {

@@ -570,7 +570,7 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
     v.data = u8 ? nullptr : base;
     v.box = reinterpret_cast<uint16_t *>(base + box_offset);
     // scratch of the box kernels for the duration of the call: from the arena, else from the
-    // device; without any, every free brick gets a box of itself (the same results, more steps)
+    // device; without any, a free brick gets a box of few bricks (the same results, more steps)
     const size_t scratch_bytes = rmpc::box_scratch_bytes(v);
     rmpc::BoxArgs A{v, voxels, nullptr};
     size_t scratch_off = 0;
@@ -600,6 +600,7 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
         host_boxes = host_unit_boxes(v, vox.data());
         if (e == hipSuccess)
             e = hipMemcpyAsync(base, host_boxes.data(), sizeof(uint16_t) * host_boxes.size(), hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = rmpc::launch_unit_boxes(v, s);
     } else if (e == hipSuccess) {
         e = rmpc::launch_map_boxes(A, s);
     }

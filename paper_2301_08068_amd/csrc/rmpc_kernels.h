@@ -239,7 +239,7 @@ struct GatherArgs {
 struct BoxArgs {
     MapView map;                 // data and box already point into the arena
     const void *src;             // device memory: the voxels, x-fastest (map.data: in place)
-    uint8_t *scratch;            // box_scratch_bytes, or null: every free brick gets a box of itself
+    uint8_t *scratch;            // box_scratch_bytes, or null: narrower boxes
 };
 
 int ray_grid_blocks(int n_rays);
@@ -252,6 +252,8 @@ hipError_t launch_scan(const ScanArgs &a, hipStream_t s, hipEvent_t ev0 = nullpt
                        hipEvent_t ev1 = nullptr);
 hipError_t launch_directions(const DirsArgs &a, hipStream_t s);
 hipError_t launch_map_boxes(const BoxArgs &a, hipStream_t s);
+// What launch_map_boxes without scratch does to entries of single-brick boxes (m.box).
+hipError_t launch_unit_boxes(const MapView &m, hipStream_t s);
 // Scratch bytes of launch_map_boxes.
 size_t box_scratch_bytes(const MapView &m);
 hipError_t launch_compact(const CompactArgs &a, hipStream_t s);

@@ -94,3 +94,41 @@ def test_scratch_is_all_or_nothing(ctx, short):
     om = oracle.OracleMap(t, 0.1, np.zeros(3), "f32")
     x = np.array([2.03, 1.97, 1.01])
     compare_trace(ctx.trace(mid, x, 4096, P), oracle.trace(om, oracle.grid_start(om, x), oracle.directions(4096), P["max_range"]))
+
+
+@pytest.mark.parametrize("enc,source", [("f32", "device"), ("f16", "offset"), ("u8", "device"), ("u8", "host")])
+@pytest.mark.parametrize("dims,p", [((64, 64, 64), 0.0005), ((61, 47, 33), 0.001), ((63, 1, 65), 0.01), ((130, 3, 4), 0.003), ((40, 40, 40), 0.0)])
+def test_boxes_without_scratch_are_wide(monkeypatch, dims, p, enc, source):
+    """A free brick's box is the widest free cube of half extent 1, 2, 3, 5 or 9 around it (bricks
+    without an entry count as occupied, those outside the grid as free); an occupied brick's entry holds
+    its voxels and no layer."""
+    import test_gpu_boxes as T
+    from paper_2301_08068_amd import binding as B
+    create = B.rmpc_create
+
+    def limited(*a):
+        ctx = create(*a)
+        B._lib.rmpc_internal_scratch_limit(C.c_void_p(ctx), C.c_size_t(0))
+        return ctx
+
+    monkeypatch.setattr(B, "rmpc_create", limited)
+    nx, ny, nz = dims
+    occ = np.random.default_rng(sum(dims)).uniform(size=(nz, ny, nx)) < p
+    t = np.where(occ, -0.1, 0.2).astype(np.float32)
+    grid = {"f32": t, "f16": W.encode_f16(t), "u8": W.encode_u8(t)}[enc]
+    e = T._entries(B, torch, grid, enc, source).astype(np.int64)
+    full = [-(-n // 2) for n in occ.shape]
+    pad = np.zeros([2 * n for n in full], bool)
+    pad[:nz, :ny, :nx] = occ
+    vox = pad.reshape(full[0], 2, full[1], 2, full[2], 2)
+    mask = sum(vox[:, (b >> 2) & 1, :, (b >> 1) & 1, :, b & 1].astype(np.int64) << b for b in range(8))
+    nb = e.shape
+    brick = np.ones(full, bool)
+    brick[:nb[0], :nb[1], :nb[2]] = mask[:nb[0], :nb[1], :nb[2]] != 0
+    mask = mask[:nb[0], :nb[1], :nb[2]]
+    c = np.nonzero(mask == 0)
+    want = np.ones(len(c[0]), np.int64)
+    for k in (2, 3, 5, 9):
+        want[T._inside(T._sum(brick), [v - k + 1 for v in c], [v + k for v in c]) == 0] = k
+    assert np.array_equal(e[mask == 0], 2 * want * (1 | 1 << 5 | 1 << 10))
+    assert np.array_equal(e[mask != 0], mask[mask != 0] | T.OCCUPIED | 1 << T.SIDE | 3 << T.AXIS)
