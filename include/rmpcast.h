@@ -36,7 +36,7 @@ typedef enum {
     RMPC_E_INVALID = -1,        /* bad argument: NULL, NaN/Inf, size out of range, bad dtype */
     RMPC_E_NOMAP = -2,          /* unknown or released map id */
     RMPC_E_OUT_OF_BOUNDS = -3,  /* query position outside the map's grid */
-    RMPC_E_NOMEM = -4,          /* the caller's device arena has no room */
+    RMPC_E_NOMEM = -4,          /* the caller's device arena (or host memory) has no room */
     RMPC_E_HIP = -5,            /* a HIP runtime call failed */
     RMPC_E_STOPPED = -6         /* no serving loop is running, or it stopped after an error */
 } rmpc_status;

@@ -12,6 +12,8 @@
 #include <chrono>
 #include <list>
 #include <map>
+#include <memory>
+#include <new>
 #include <string>
 #include <utility>
 #include <vector>
@@ -369,19 +371,19 @@ rmpc_status dense_layout(const rmpc_map_desc &d, rmpc::MapView &v, uint64_t &n_a
 }
 
 // The entries of a uint8 grid in host memory with single-brick boxes (used when there is no
-// memory for the scratch of the box kernels).
-std::vector<uint16_t> host_unit_boxes(const rmpc::MapView &m, const uint8_t *vox)
+// memory for the scratch of the box kernels), one per brick to box.
+void host_unit_boxes(const rmpc::MapView &m, const uint8_t *vox, uint16_t *box)
 {
-    std::vector<uint16_t> box((size_t)m.nbx * m.nby * m.nbz, 0);
+    const size_t n = (size_t)m.nbx * m.nby * m.nbz;
+    std::fill(box, box + n, (uint16_t)0);
     for (int z = 0; z < m.nz; ++z)
         for (int y = 0; y < m.ny; ++y)
             for (int x = 0; x < m.nx; ++x)
                 if (vox[(size_t)x + (size_t)m.nx * (y + (size_t)m.ny * z)])
                     box[(size_t)(x / 2) + (size_t)m.nbx * (y / 2 + (size_t)m.nby * (z / 2))] |=
                         (uint16_t)(rmpc::kBoxOccupied | rmpc::kBoxNoLayer | (1u << ((x & 1) + 2 * (y & 1) + 4 * (z & 1))));
-    for (uint16_t &e : box)
-        if (!e) e = (uint16_t)rmpc::box_extents(1, 1, 1);
-    return box;
+    for (size_t k = 0; k < n; ++k)
+        if (!box[k]) box[k] = (uint16_t)rmpc::box_extents(1, 1, 1);
 }
 
 // Validates a scan query and fills everything of ScanArgs but its reduction slots.
@@ -586,7 +588,8 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
     const bool direct = voxels_on_device && hipPointerGetAttributes(&attr, voxels) == hipSuccess &&
                         attr.type == hipMemoryTypeDevice && attr.device == ctx->device;
     if (!direct) (void)hipGetLastError();
-    std::vector<uint16_t> host_boxes;
+    std::unique_ptr<uint16_t[]> host_boxes;
+    bool host_full = false;
     hipError_t e = hipSuccess;
     if (!direct && !(u8 && !A.scratch)) {
         e = hipMemcpyAsync(base, voxels, n_log * eb, voxels_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s);
@@ -594,13 +597,17 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
     }
     if (!direct && u8 && !A.scratch) {
         // in place the entries would overwrite voxels still to be read
-        std::vector<uint8_t> vox((size_t)n_log);
-        e = hipMemcpyAsync(vox.data(), voxels, (size_t)n_log, hipMemcpyDefault, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        host_boxes = host_unit_boxes(v, vox.data());
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(base, host_boxes.data(), sizeof(uint16_t) * host_boxes.size(), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) e = rmpc::launch_unit_boxes(v, s);
+        const size_t n = (size_t)v.nbx * v.nby * v.nbz;
+        std::unique_ptr<uint8_t[]> vox(new (std::nothrow) uint8_t[(size_t)n_log]);
+        host_boxes.reset(new (std::nothrow) uint16_t[n]);
+        host_full = !vox || !host_boxes;
+        if (!host_full) {
+            e = hipMemcpyAsync(vox.get(), voxels, (size_t)n_log, hipMemcpyDefault, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            if (e == hipSuccess) host_unit_boxes(v, vox.get(), host_boxes.get());
+            if (e == hipSuccess) e = hipMemcpyAsync(base, host_boxes.get(), sizeof(uint16_t) * n, hipMemcpyHostToDevice, s);
+            if (e == hipSuccess) e = rmpc::launch_unit_boxes(v, s);
+        }
     } else if (e == hipSuccess) {
         e = rmpc::launch_map_boxes(A, s);
     }
@@ -608,6 +615,10 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
     if (e != hipSuccess) (void)hipStreamSynchronize(s);
     if (in_arena) ctx->alloc.release(scratch_off);
     if (scratch_dev) (void)hipFree(scratch_dev);
+    if (host_full) {
+        ctx->alloc.release(off);
+        return fail(RMPC_E_NOMEM, "host allocation failed");
+    }
     if (e != hipSuccess) {
         ctx->alloc.release(off);
         return fail(RMPC_E_HIP, std::string("map upload: ") + hipGetErrorString(e));

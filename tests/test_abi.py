@@ -1,5 +1,6 @@
 """The C-ABI library builds, loads and exports every entry point the header declares
 (no GPU calls: these run on the CPU)."""
+import ctypes as C
 import os
 import re
 import subprocess
@@ -125,19 +126,36 @@ def test_result_columns_equal_single_results(lib_path, n):
         assert (d["rank"], d["flags"], d["visits"]) == (r.rank, r.flags, r.visits)
 
 
+class _MapView(C.Structure):
+    _fields_ = [("data", C.c_void_p), ("box", C.c_void_p)] + \
+        [(k, C.c_int32) for k in ("nx", "ny", "nz", "dtype", "nbx", "nby", "nbz", "partial", "lo", "span")]
+
+
 @pytest.mark.parametrize("dims", [(400, 400, 400), (64, 64, 64), (130, 130, 130), (8, 4096, 4096), (1, 4096, 4096),
                                   (2, 2048, 2048), (16, 2000, 2000), (6, 7, 4096), (4096, 1, 4096), (8, 8, 8), (1, 1, 1)])
 def test_upload_scratch_is_bounded(lib_path, dims):
     """The scratch of an upload: a byte and 52 bits a brick of 2^3 voxels, rows of bits padded to 64
     bricks along the axis where that costs least: below 14 bytes a brick, and 2 MiB."""
-    import ctypes as C
-
-    class MapView(C.Structure):
-        _fields_ = [("data", C.c_void_p), ("box", C.c_void_p)] + \
-            [(k, C.c_int32) for k in ("nx", "ny", "nz", "dtype", "nbx", "nby", "nbz", "partial", "lo", "span")]
-
     scratch = C.CDLL(lib_path)._ZN4rmpc17box_scratch_bytesERKNS_7MapViewE
     scratch.restype = C.c_size_t
     nb = [-(-n // 2) for n in dims]
-    m = MapView(nx=dims[0], ny=dims[1], nz=dims[2], nbx=nb[0], nby=nb[1], nbz=nb[2])
+    m = _MapView(nx=dims[0], ny=dims[1], nz=dims[2], nbx=nb[0], nby=nb[1], nbz=nb[2])
     assert scratch(C.byref(m)) < 14 * nb[0] * nb[1] * nb[2] + (2 << 20)
+
+
+@pytest.mark.parametrize("dims", [(1, 1, 1), (2, 3, 4), (5, 7, 9), (16, 6, 1)])
+def test_host_entries_of_single_bricks(lib_path, dims):
+    """The entries that the host makes of uint8 voxels when there is no scratch: the voxels of an
+    occupied brick, a box of one brick around a free one."""
+    fill = C.CDLL(lib_path)._ZN9rmpc_host15host_unit_boxesERKN4rmpc7MapViewEPKhPt
+    fill.restype = None
+    nx, ny, nz = dims
+    nb = [-(-n // 2) for n in dims]
+    vox = (np.random.default_rng(sum(dims)).uniform(size=(nz, ny, nx)) < 0.2).astype(np.uint8) * 7
+    out = np.full((nb[2], nb[1], nb[0]), 0xabcd, np.uint16)
+    m = _MapView(nx=nx, ny=ny, nz=nz, nbx=nb[0], nby=nb[1], nbz=nb[2])
+    fill(C.byref(m), vox.ctypes.data_as(C.c_void_p), out.ctypes.data_as(C.c_void_p))
+    mask = np.zeros(out.shape, np.int64)
+    for z, y, x in np.argwhere(vox):
+        mask[z // 2, y // 2, x // 2] |= 1 << (x % 2 + 2 * (y % 2) + 4 * (z % 2))
+    assert np.array_equal(out, np.where(mask > 0, mask | 0x8700, 2 * (1 | 1 << 5 | 1 << 10)))
