@@ -582,11 +582,11 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
     if (in_arena) A.scratch = ctx->arena + scratch_off;
     else if (wanted && hipMalloc(&scratch_dev, scratch_bytes) == hipSuccess) A.scratch = static_cast<uint8_t *>(scratch_dev);
     else (void)hipGetLastError();
-    // the kernels read the caller's buffer themselves when it is memory of this GPU; any other
-    // pointer is copied to the arena first
+    // the kernels read the caller's buffer themselves when it is memory of this GPU and its elements
+    // are aligned; any other pointer is copied to the arena first
     hipPointerAttribute_t attr;
-    const bool direct = voxels_on_device && hipPointerGetAttributes(&attr, voxels) == hipSuccess &&
-                        attr.type == hipMemoryTypeDevice && attr.device == ctx->device;
+    const bool direct = voxels_on_device && reinterpret_cast<uintptr_t>(voxels) % eb == 0 &&
+                        hipPointerGetAttributes(&attr, voxels) == hipSuccess && attr.type == hipMemoryTypeDevice && attr.device == ctx->device;
     if (!direct) (void)hipGetLastError();
     std::unique_ptr<uint16_t[]> host_boxes;
     bool host_full = false;

@@ -212,3 +212,31 @@ def test_the_whole_grid_is_copied(dims, dtype):
 def test_boxes_of_narrow_grids(dims, density, dtype):
     """As above, where the bit sets' words lie along another axis than x."""
     test_boxes_are_free_and_layers_exact(dims, density, dtype)
+
+
+@pytest.mark.parametrize("dtype,shift", [("f32", 1), ("f32", 2), ("f32", 6), ("f16", 1), ("f16", 5)])
+@pytest.mark.parametrize("dims", [(32, 20, 12), (31, 7, 9)])
+def test_voxels_at_any_byte(dims, dtype, shift):
+    """The caller's buffer may start anywhere: the resident grid and the rays' hits are those of an
+    aligned one."""
+    import torch
+    from paper_2301_08068_amd import binding as B
+    from paper_2301_08068_amd import workloads as W
+    nx, ny, nz = dims
+    rng = np.random.default_rng(nx + shift)
+    val = np.where(rng.uniform(size=(nz, ny, nx)) < 0.02, -0.1, rng.uniform(0.05, 0.3, (nz, ny, nx))).astype(np.float32)
+    val[nz // 2, ny // 2, nx // 2] = 0.2
+    grid = val if dtype == "f32" else W.encode_f16(val)
+    raw = torch.from_numpy(np.ascontiguousarray(grid).view(np.uint8).reshape(-1))
+    c = B.Context(0, arena_bytes=32 << 20)
+    try:
+        got = []
+        for s in (0, shift):
+            dev = torch.cat([torch.zeros(s, dtype=torch.uint8), raw]).to("cuda:0")
+            mid = B.rmpc_map_upload(c.ptr, nx, ny, nz, dtype, 0.1, (0.0, 0.0, 0.0), dev.data_ptr() + s, True)
+            x = (np.array([nx // 2, ny // 2, nz // 2]) + 0.4) * 0.1
+            got.append(c.trace(mid, x, 2000, W.params("static", max_range=5.0, subvoxel=1)))
+        for k in ("hit", "d", "visits"):
+            assert np.array_equal(got[0][k], got[1][k]), k
+    finally:
+        c.close()
