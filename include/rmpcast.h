@@ -182,7 +182,10 @@ typedef struct {
  * coordinates to slots: 16 capacity + 64 n_blocks + 512 elem_bytes n_blocks arena bytes.  Where the
  * box around the stored blocks lies within 2^16 voxels of the origin and is small enough, a
  * quarter of the capacity holds the table and the rest an index of the box (4 bytes per block of
- * it, 128 bytes per stored block), which walks use.
+ * it, 128 bytes per stored block), which walks use; the upload then takes scratch, as for a dense map
+ * of a voxel pair per block of the box, and 2 bytes per block of it and 8 per stored one: from the
+ * arena where there is room beside the map, else allocated on the device for the call; if that
+ * fails too, the map is walked by its table.
  * More than 2^27 blocks: RMPC_E_INVALID.
  * rmpc_query and rmpc_trace_debug accept sparse maps (launch configuration
  * RMPC_CONFIG_SPARSE; the start may lie anywhere whose voxels within max_range keep

@@ -386,6 +386,33 @@ void host_unit_boxes(const rmpc::MapView &m, const uint8_t *vox, uint16_t *box)
         if (!box[k]) box[k] = (uint16_t)rmpc::box_extents(1, 1, 1);
 }
 
+// Device memory for the duration of an upload: from the arena where it has room, else from the device
+// (whose allocation and release wait for everything that runs on it).
+struct UploadScratch {
+    rmpc_ctx *ctx;
+    uint8_t *p = nullptr;
+    size_t off = 0;
+    bool in_arena = false;
+    explicit UploadScratch(rmpc_ctx *c) : ctx(c) {}
+    UploadScratch(const UploadScratch &) = delete;
+    bool get(size_t n)
+    {
+        if (n == 0 || n > ctx->scratch_limit) return false;
+        in_arena = ctx->alloc.alloc(n, &off);
+        if (in_arena) p = ctx->arena + off;
+        else if (hipMalloc(reinterpret_cast<void **>(&p), n) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+        }
+        return p != nullptr;
+    }
+    ~UploadScratch()
+    {
+        if (in_arena) ctx->alloc.release(off);
+        else if (p) (void)hipFree(p);
+    }
+};
+
 // Validates a scan query and fills everything of ScanArgs but its reduction slots.
 rmpc_status setup_scan(const float *points_dev, int32_t n_points, const double v[3], const rmpc_params *params,
                        rmpc::ScanArgs &A)
@@ -573,15 +600,9 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
     v.box = reinterpret_cast<uint16_t *>(base + box_offset);
     // scratch of the box kernels for the duration of the call: from the arena, else from the
     // device; without any, a free brick gets a box of few bricks (the same results, more steps)
-    const size_t scratch_bytes = rmpc::box_scratch_bytes(v);
     rmpc::BoxArgs A{v, voxels, nullptr};
-    size_t scratch_off = 0;
-    void *scratch_dev = nullptr;
-    const bool wanted = scratch_bytes > 0 && scratch_bytes <= ctx->scratch_limit;
-    const bool in_arena = wanted && ctx->alloc.alloc(scratch_bytes, &scratch_off);
-    if (in_arena) A.scratch = ctx->arena + scratch_off;
-    else if (wanted && hipMalloc(&scratch_dev, scratch_bytes) == hipSuccess) A.scratch = static_cast<uint8_t *>(scratch_dev);
-    else (void)hipGetLastError();
+    UploadScratch scratch(ctx);
+    if (scratch.get(rmpc::box_scratch_bytes(v))) A.scratch = scratch.p;
     // the kernels read the caller's buffer themselves when it is memory of this GPU and its elements
     // are aligned; any other pointer is copied to the arena first
     hipPointerAttribute_t attr;
@@ -613,8 +634,6 @@ rmpc_status rmpc_map_upload(rmpc_ctx *ctx, const rmpc_map_desc *desc, const void
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) (void)hipStreamSynchronize(s);
-    if (in_arena) ctx->alloc.release(scratch_off);
-    if (scratch_dev) (void)hipFree(scratch_dev);
     if (host_full) {
         ctx->alloc.release(off);
         return fail(RMPC_E_NOMEM, "host allocation failed");
@@ -653,22 +672,6 @@ bool index_box(const int32_t *coords, int32_t n, int32_t lo[3], int32_t nb[3])
     return true;
 }
 
-// Device memory for the duration of a call.
-struct DeviceScratch {
-    uint8_t *p = nullptr;
-    bool get(size_t n)
-    {
-        if (hipMalloc(reinterpret_cast<void **>(&p), n) == hipSuccess) return true;
-        (void)hipGetLastError();
-        p = nullptr;
-        return false;
-    }
-    ~DeviceScratch()
-    {
-        if (p) (void)hipFree(p);
-    }
-};
-
 rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, const int32_t *block_coords_host,
                                    const void *values, int values_on_device, void *hip_stream, int32_t *map_id_out)
 {
@@ -699,7 +702,7 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
     std::memset(&v, 0, sizeof v);
     v.n_slots = n;
     const size_t table_bytes = sizeof(rmpc::HashEntry) * (size_t)cap64;
-    size_t index_at = 0, bricks_at = 0, scratch_bytes = 0;
+    size_t index_at = 0, bricks_at = 0;
     bool indexed = index_box(block_coords_host, n, v.lo, v.nb);
     if (indexed) {
         index_at = sizeof(rmpc::HashEntry) * (size_t)(cap64 / 4);
@@ -708,28 +711,27 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
     }
     DeviceGuard dg(ctx->device);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    DeviceScratch scratch;
-    if (indexed) {
-        scratch_bytes = rmpc::sparse_index_scratch_bytes(v);
-        indexed = scratch_bytes <= ctx->scratch_limit && scratch.get(scratch_bytes);
-    }
-    if (indexed) cap64 /= 4;
-    const uint32_t cap = (uint32_t)cap64;
-    std::vector<rmpc::HashEntry> table(cap, rmpc::HashEntry{rmpc::kEmptyKey, -1, 0u});
-    const uint32_t mask = cap - 1u;
-    for (int32_t k = 0; k < n; ++k) {
-        const int32_t *c = block_coords_host + 3 * (size_t)k;
-        for (int a = 0; a < 3; ++a)
-            if (c[a] < -rmpc::kBlockCoordBias || c[a] >= rmpc::kBlockCoordBias)
-                return fail(RMPC_E_INVALID, "block " + std::to_string(k) + ": coordinate out of [-2^20, 2^20)");
-        const uint64_t key = rmpc::block_key(c[0], c[1], c[2]);
-        uint32_t i = rmpc::block_hash(key, mask);
-        while (table[i].key != rmpc::kEmptyKey) {
-            if (table[i].key == key) return fail(RMPC_E_INVALID, "block " + std::to_string(k) + ": listed twice");
-            i = (i + 1u) & mask;
+    std::vector<rmpc::HashEntry> table;
+    uint32_t mask = 0;
+    auto fill_table = [&](uint32_t cap) {
+        table.assign(cap, rmpc::HashEntry{rmpc::kEmptyKey, -1, 0u});
+        mask = cap - 1u;
+        for (int32_t k = 0; k < n; ++k) {
+            const int32_t *c = block_coords_host + 3 * (size_t)k;
+            for (int a = 0; a < 3; ++a)
+                if (c[a] < -rmpc::kBlockCoordBias || c[a] >= rmpc::kBlockCoordBias)
+                    return fail(RMPC_E_INVALID, "block " + std::to_string(k) + ": coordinate out of [-2^20, 2^20)");
+            const uint64_t key = rmpc::block_key(c[0], c[1], c[2]);
+            uint32_t i = rmpc::block_hash(key, mask);
+            while (table[i].key != rmpc::kEmptyKey) {
+                if (table[i].key == key) return fail(RMPC_E_INVALID, "block " + std::to_string(k) + ": listed twice");
+                i = (i + 1u) & mask;
+            }
+            table[i] = rmpc::HashEntry{key, k, 0u};
         }
-        table[i] = rmpc::HashEntry{key, k, 0u};
-    }
+        return RMPC_OK;
+    };
+    if (rmpc_status st = fill_table((uint32_t)(indexed ? cap64 / 4 : cap64))) return st;
     const size_t eb = elem_bytes(desc->dtype);
     size_t o_table, o_occ, o_vals;
     if (!ctx->alloc.alloc(table_bytes, &o_table))
@@ -743,6 +745,13 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
         ctx->alloc.release(o_occ);
         return fail(RMPC_E_NOMEM, "arena full (sparse map values)");
     }
+    // (after the map's own memory, which the scratch must not take; without scratch the map walks by
+    // its table, of the full size)
+    UploadScratch scratch(ctx);
+    if (indexed && !scratch.get(rmpc::sparse_index_scratch_bytes(v))) {
+        indexed = false;
+        if (rmpc_status st = fill_table((uint32_t)cap64)) return st;
+    }
     rmpc::HashEntry *table_dev = reinterpret_cast<rmpc::HashEntry *>(ctx->arena + o_table);
     v.table = table_dev;
     v.table_mask = mask;
@@ -754,7 +763,7 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
     v.values = ctx->arena + o_vals;
     v.dtype = desc->dtype;
     v.free_value = free_value;
-    hipError_t e = hipMemcpyAsync(table_dev, table.data(), sizeof(rmpc::HashEntry) * (size_t)cap,
+    hipError_t e = hipMemcpyAsync(table_dev, table.data(), sizeof(rmpc::HashEntry) * table.size(),
                                   hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(ctx->arena + o_vals, values, eb * rmpc::kBlockVoxels * (size_t)n,

@@ -132,3 +132,51 @@ def test_boxes_without_scratch_are_wide(monkeypatch, dims, p, enc, source):
         want[T._inside(T._sum(brick), [v - k + 1 for v in c], [v + k for v in c]) == 0] = k
     assert np.array_equal(e[mask == 0], 2 * want * (1 | 1 << 5 | 1 << 10))
     assert np.array_equal(e[mask != 0], mask[mask != 0] | T.OCCUPIED | 1 << T.SIDE | 3 << T.AXIS)
+
+
+def test_sparse_scratch_comes_from_the_arena(tiny_map):
+    """With room, the upload of a sparse map takes its scratch from the arena (bytes past the map's own
+    change); in an arena that has just the map's own room it is uploaded all the same, with equal hits."""
+    from paper_2301_08068_amd import binding as B
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    sm = W.sparse_from_dense(tiny_map, keep_free=0.3, seed=4)
+    n, size = len(sm.coords), 48 << 20
+    cap = 1024
+    while cap < 16 * n:
+        cap *= 2
+    own = sum(-(-b // 256) * 256 for b in (16 * cap, 64 * n, 4 * 512 * n))
+    arena = torch.zeros(size, dtype=torch.uint8, device="cuda:0")
+    ctx = B.rmpc_create(0, arena.data_ptr(), size)
+    vals = torch.from_numpy(np.ascontiguousarray(sm.values, np.float32)).to("cuda:0")
+    x, _ = W.free_state(tiny_map, 3)
+
+    def upload():
+        return B.rmpc_sparse_map_upload(ctx, sm.coords, vals.data_ptr(), n, "f32", sm.voxel_m, sm.origin_m, True, free_value=0.3)
+
+    def trace(mid):
+        hit, d = torch.empty(2000, dtype=torch.int32, device="cuda:0"), torch.empty(2000, dtype=torch.float64, device="cuda:0")
+        flags = torch.empty(2000, dtype=torch.uint8, device="cuda:0")
+        B.rmpc_trace_debug(ctx, mid, x, 2000, P, hit.data_ptr(), d.data_ptr(), flags.data_ptr())
+        return hit.cpu(), d.cpu()
+
+    try:
+        before = arena.clone()
+        mid = upload()
+        changed = torch.nonzero(arena != before).reshape(-1)
+        base = int(changed[0]) // 256 * 256
+        assert int(changed[-1]) >= base + own
+        want = trace(mid)
+        byte = torch.zeros(4096 * 4096, dtype=torch.uint8, device="cuda:0")
+        for dims in ((4096, 1, 4096), (4096, 1, 512), (4096, 1, 64), (4096, 1, 8), (4096, 1, 1), (256, 1, 1)):
+            while True:
+                try:
+                    B.rmpc_map_upload(ctx, *dims, "u8", 0.1, (0, 0, 0), byte.data_ptr(), True)
+                except B.RmpcError as e:
+                    assert e.status == B.RMPC_E_NOMEM
+                    break
+        B.rmpc_map_release(ctx, mid)
+        got = trace(upload())
+        assert all(torch.equal(a, b) for a, b in zip(want, got))
+    finally:
+        B.rmpc_destroy(ctx)
