@@ -768,8 +768,7 @@ rmpc_status rmpc_sparse_map_upload(rmpc_ctx *ctx, const rmpc_sparse_desc *desc, 
     if (e == hipSuccess)
         e = hipMemcpyAsync(ctx->arena + o_vals, values, eb * rmpc::kBlockVoxels * (size_t)n,
                            values_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = rmpc::launch_sparse_masks(v, table_dev, s);
-    if (e == hipSuccess && indexed) e = rmpc::launch_sparse_index(v, scratch.p, s);
+    if (e == hipSuccess) e = rmpc::launch_sparse_build(v, table_dev, scratch.p, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipStreamSynchronize(s);

@@ -285,12 +285,10 @@ hipError_t launch_esdf(const EsdfArgs &a, hipStream_t s);
 // One map query on a sparse map (debug: per-ray outputs instead of the policy).
 hipError_t launch_sparse(const RayArgs &a, hipStream_t s, bool debug, hipEvent_t ev0 = nullptr,
                          hipEvent_t ev1 = nullptr);
-// Occupancy masks of n sparse blocks from their values, and the tables' occupied flags.
-hipError_t launch_sparse_masks(const SparseView &v, HashEntry *table, hipStream_t s);
-// The index and the brick entries of a sparse map whose masks and flags are written.  scratch:
-// sparse_index_scratch_bytes, 256-byte aligned.
+// Occupancy masks of a sparse map's blocks from their values, the table's occupied flags, and (v.index
+// not null) its index and brick entries, with scratch: sparse_index_scratch_bytes, 256-byte aligned.
 size_t sparse_index_scratch_bytes(const SparseView &v);
-hipError_t launch_sparse_index(const SparseView &v, uint8_t *scratch, hipStream_t s);
+hipError_t launch_sparse_build(const SparseView &v, HashEntry *table, uint8_t *scratch, hipStream_t s);
 // Where launch_cell_boxes reads a cell's occupancy in its scratch: one byte (0 or 255) each, cell
 // (x, y, z) at x sx + y sy + z sz (at most 2^28 cells); rows of `pitch` bytes, in all `bytes`.
 struct BoxMask {

@@ -60,81 +60,87 @@ __global__ void __launch_bounds__(kBlock, 2) sparse_trace_kernel(RayArgs A)
     }
 }
 
-// Occupancy words of every slot (thread: one slot's layer) from its stored values.
+// What an upload writes of a map's index, all null and zero for a map without one.
+struct IndexBuild {
+    uint32_t *index;                                      // cells entries
+    int64_t cells;
+    uint16_t *bricks;                                     // 64 per slot
+    BoxMask mask;                                         // the cells' occupancy
+    uint16_t *box;                                        // the cells' boxes
+    uint64_t *bits;                                       // per slot a bit per brick
+};
+
+// Occupancy words of every slot (thread: one slot's layer) from its stored values.  The same launch
+// clears the index and its cells' occupancy: an upload of few blocks is as long as its launches (with
+// 13 of them, two fills of memory among them, one of 16 blocks took 87 us, with 8 76).
 template <int DT>
-__global__ void sparse_mask_kernel(SparseView v, uint64_t *occ)
+__global__ void __launch_bounds__(256) sparse_mask_kernel(SparseView v, uint64_t *occ, IndexBuild b)
 {
     using T = typename Voxel<DT>::T;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= v.n_slots * kLayers) return;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+    for (int64_t i = t; i < b.cells; i += step) b.index[i] = 0u;
+    for (int64_t i = t; i < (int64_t)(b.mask.bytes / 8); i += step) reinterpret_cast<uint64_t *>(b.mask.at)[i] = 0ull;
+    if (t >= (int64_t)v.n_slots * kLayers) return;
     const T *vals = static_cast<const T *>(v.values) + (size_t)t * 64;   // layer z of slot t / 8
     uint64_t w = 0;
     for (int k = 0; k < 64; ++k) w |= Voxel<DT>::occ(vals[k]) ? 1ull << k : 0ull;
     occ[t] = w;
 }
 
-// Each table entry's occupied flag: whether its slot's occupancy has any bit set.
-__global__ void sparse_flag_kernel(SparseView v, HashEntry *table)
+// Table entry i: whether its slot's occupancy has any bit set; in the index an occupied block's slot,
+// and 255 in the cells' occupancy.
+__device__ __forceinline__ void table_entry(const SparseView &v, HashEntry *table, const IndexBuild &b, uint32_t i)
 {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i > v.table_mask) return;
     HashEntry &e = table[i];
     if (e.key == kEmptyKey || e.slot < 0 || e.slot >= v.n_slots) return;
     uint64_t any = 0;
     for (int k = 0; k < kLayers; ++k) any |= v.occ[(size_t)e.slot * kLayers + k];
     e.occupied = any != 0 ? 1u : 0u;
-}
-
-// The index's occupied blocks, from the table: their slots, and 255 in the cells' occupancy.
-__global__ void __launch_bounds__(256) index_slots_kernel(SparseView v, uint32_t *index, BoxMask mask)
-{
-    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i > v.table_mask) return;
-    const HashEntry e = v.table[i];
-    if (e.key == kEmptyKey || e.occupied == 0u) return;
+    if (any == 0 || !b.index) return;
     const uint32_t bits = (1u << kBlockCoordBits) - 1u;
     const int x = (int)((uint32_t)e.key & bits) - kBlockCoordBias - v.lo[0];
     const int y = (int)((uint32_t)(e.key >> 21) & bits) - kBlockCoordBias - v.lo[1];
     const int z = (int)((uint32_t)(e.key >> 42) & bits) - kBlockCoordBias - v.lo[2];
-    const int64_t row = y + (int64_t)v.nb[1] * z;
-    index[x + v.nb[0] * row] = kBlockOccupied | (uint32_t)e.slot;
-    mask.at[x * mask.sx + y * mask.sy + z * mask.sz] = 255u;
-}
-
-// The other blocks' boxes.
-__global__ void __launch_bounds__(256) index_boxes_kernel(uint32_t *index, const uint16_t *box, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n && index[i] == 0u) index[i] = box[i];
+    b.index[x + v.nb[0] * (y + (int64_t)v.nb[1] * z)] = kBlockOccupied | (uint32_t)e.slot;
+    b.mask.at[x * b.mask.sx + y * b.mask.sy + z * b.mask.sz] = 255u;
 }
 
 // A slot's 64 bricks (a wave): their voxels' occupancy, and one bit each in bits[slot].
-__global__ void __launch_bounds__(256) brick_masks_kernel(SparseView v, uint16_t *bricks, uint64_t *bits)
+__device__ __forceinline__ void brick_masks(const SparseView &v, const IndexBuild &b, int slot, int brick)
 {
-    const int slot = blockIdx.x * 4 + (threadIdx.x >> 6), b = threadIdx.x & 63;
     if (slot >= v.n_slots) return;
-    const uint64_t *w = v.occ + (size_t)slot * kLayers + 2 * (b >> 4);
-    const int at = 2 * (b & 3) + 16 * ((b >> 2) & 3);
+    const uint64_t *w = v.occ + (size_t)slot * kLayers + 2 * (brick >> 4);
+    const int at = 2 * (brick & 3) + 16 * ((brick >> 2) & 3);
     uint32_t mask = 0;
 #pragma unroll
     for (int dz = 0; dz < 2; ++dz)
         mask |= (uint32_t)(((w[dz] >> at) & 3u) | (((w[dz] >> (at + 8)) & 3u) << 2)) << (4 * dz);
     const uint64_t any = __ballot(mask != 0u);
-    bricks[(size_t)slot * 64 + b] = (uint16_t)mask;
-    if (b == 0) bits[slot] = any;
+    b.bricks[(size_t)slot * 64 + brick] = (uint16_t)mask;
+    if (brick == 0) b.bits[slot] = any;
 }
 
-// The brick entries of the occupied blocks (a wave each): an occupied brick's voxels, without a
-// free layer; around a free one the free cube, half extent 1 .. 5 (what the 27 blocks around tell),
+// The table's entries (the first table_blocks blocks, a thread each), and the slots' bricks.
+__global__ void __launch_bounds__(256) sparse_table_kernel(SparseView v, HashEntry *table, IndexBuild b, uint32_t table_blocks)
+{
+    if (blockIdx.x < table_blocks) table_entry(v, table, b, blockIdx.x * 256 + threadIdx.x);
+    else brick_masks(v, b, (int)(blockIdx.x - table_blocks) * 4 + (int)(threadIdx.x >> 6), threadIdx.x & 63);
+}
+
+// A free block's box in the index, and the brick entries of an occupied one (a wave for each of the
+// index's blocks; one that reads a neighbour's entry asks only whether it is occupied, and its slot,
+// which stay): an occupied brick's voxels, without a free layer; around a free one the free cube, half extent 1 .. 5 (what the 27 blocks around tell),
 // or where it is narrow (below 3) the widest slab one brick thick.
-__global__ void __launch_bounds__(256) brick_boxes_kernel(SparseView v, uint16_t *bricks, const uint64_t *bits)
+__global__ void __launch_bounds__(256) brick_boxes_kernel(SparseView v, IndexBuild build)
 {
     __shared__ uint32_t rows[4][144];                     // 12 bricks along x, for y and z from 4 before the block on
     const int64_t n = (int64_t)v.nb[0] * v.nb[1] * v.nb[2];
     const int64_t at = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const uint32_t e = at < n ? v.index[at] : 0u;
+    const uint32_t e = at < n ? build.index[at] : 0u;
     const bool mine = (e & kBlockOccupied) != 0u;
+    if (!mine && at < n && lane == 0) build.index[at] = build.box[at];
     uint32_t *row = rows[threadIdx.x >> 6];
     if (mine) {
         const int64_t yz = at / v.nb[0];
@@ -144,8 +150,8 @@ __global__ void __launch_bounds__(256) brick_boxes_kernel(SparseView v, uint16_t
         if (lane < 27) {
             const int px = x + lane % 3 - 1, py = y + lane / 3 % 3 - 1, pz = z + lane / 9 - 1;
             if ((unsigned)px < (unsigned)v.nb[0] && (unsigned)py < (unsigned)v.nb[1] && (unsigned)pz < (unsigned)v.nb[2]) {
-                const uint32_t q = v.index[px + v.nb[0] * (py + (int64_t)v.nb[1] * pz)];
-                if (q & kBlockOccupied) near = bits[q & ~kBlockOccupied];
+                const uint32_t q = build.index[px + v.nb[0] * (py + (int64_t)v.nb[1] * pz)];
+                if (q & kBlockOccupied) near = build.bits[q & ~kBlockOccupied];
             }
         }
 #pragma unroll
@@ -163,7 +169,7 @@ __global__ void __launch_bounds__(256) brick_boxes_kernel(SparseView v, uint16_t
     }
     __syncthreads();
     if (!mine) return;
-    uint16_t *out = bricks + ((size_t)(e & ~kBlockOccupied) * 64 + lane);
+    uint16_t *out = build.bricks + ((size_t)(e & ~kBlockOccupied) * 64 + lane);
     const uint32_t mask = *out;
     if (mask) {
         *out = (uint16_t)(kBoxOccupied | kBoxNoLayer | mask);
@@ -241,39 +247,33 @@ size_t sparse_index_scratch_bytes(const SparseView &v)
     return round256(box_scratch_bytes(index_cells(v))) + round256(sizeof(uint16_t) * cells) + sizeof(uint64_t) * (size_t)v.n_slots;
 }
 
-hipError_t launch_sparse_index(const SparseView &v, uint8_t *scratch, hipStream_t s)
-{
-    MapView m = index_cells(v);
-    const int64_t cells = (int64_t)v.nb[0] * v.nb[1] * v.nb[2];
-    uint16_t *box = reinterpret_cast<uint16_t *>(scratch + round256(box_scratch_bytes(m)));
-    uint64_t *bits = reinterpret_cast<uint64_t *>(reinterpret_cast<uint8_t *>(box) + round256(sizeof(uint16_t) * (size_t)cells));
-    uint32_t *index = const_cast<uint32_t *>(v.index);
-    uint16_t *bricks = const_cast<uint16_t *>(v.bricks);
-    m.box = box;
-    const BoxMask mask = box_mask(m, scratch);
-    if (hipError_t e = hipMemsetAsync(scratch, 0, mask.bytes, s)) return e;
-    if (hipError_t e = hipMemsetAsync(index, 0, sizeof(uint32_t) * (size_t)cells, s)) return e;
-    index_slots_kernel<<<(v.table_mask + 256) / 256, 256, 0, s>>>(v, index, mask);
-    launch_cell_boxes(m, scratch, s);
-    index_boxes_kernel<<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(index, box, cells);
-    brick_masks_kernel<<<(unsigned)((v.n_slots + 3) / 4), 256, 0, s>>>(v, bricks, bits);
-    brick_boxes_kernel<<<(unsigned)((cells + 3) / 4), 256, 0, s>>>(v, bricks, bits);
-    return hipGetLastError();
-}
-
-hipError_t launch_sparse_masks(const SparseView &v, HashEntry *table, hipStream_t s)
+hipError_t launch_sparse_build(const SparseView &v, HashEntry *table, uint8_t *scratch, hipStream_t s)
 {
     uint64_t *occ = const_cast<uint64_t *>(v.occ);
-    const int n = v.n_slots * kLayers;
-    if (n > 0) {
-        switch (v.dtype) {
-        case RMPC_TSDF_F32: sparse_mask_kernel<RMPC_TSDF_F32><<<(n + 255) / 256, 256, 0, s>>>(v, occ); break;
-        case RMPC_TSDF_F16: sparse_mask_kernel<RMPC_TSDF_F16><<<(n + 255) / 256, 256, 0, s>>>(v, occ); break;
-        default: sparse_mask_kernel<RMPC_OCC_U8><<<(n + 255) / 256, 256, 0, s>>>(v, occ); break;
-        }
+    MapView m{};
+    IndexBuild b{};
+    if (v.index) {
+        m = index_cells(v);
+        b.index = const_cast<uint32_t *>(v.index);
+        b.cells = (int64_t)v.nb[0] * v.nb[1] * v.nb[2];
+        b.bricks = const_cast<uint16_t *>(v.bricks);
+        b.mask = box_mask(m, scratch);
+        b.box = reinterpret_cast<uint16_t *>(scratch + round256(box_scratch_bytes(m)));
+        b.bits = reinterpret_cast<uint64_t *>(reinterpret_cast<uint8_t *>(b.box) + round256(sizeof(uint16_t) * (size_t)b.cells));
+        m.box = b.box;
     }
-    const uint32_t cap = v.table_mask + 1u;
-    sparse_flag_kernel<<<(cap + 255) / 256, 256, 0, s>>>(v, table);
+    const unsigned n = (unsigned)((v.n_slots * kLayers + 255) / 256);
+    switch (v.dtype) {
+    case RMPC_TSDF_F32: sparse_mask_kernel<RMPC_TSDF_F32><<<n, 256, 0, s>>>(v, occ, b); break;
+    case RMPC_TSDF_F16: sparse_mask_kernel<RMPC_TSDF_F16><<<n, 256, 0, s>>>(v, occ, b); break;
+    default: sparse_mask_kernel<RMPC_OCC_U8><<<n, 256, 0, s>>>(v, occ, b); break;
+    }
+    const uint32_t table_blocks = v.table_mask / 256 + 1, slot_blocks = v.index ? ((uint32_t)v.n_slots + 3) / 4 : 0u;
+    sparse_table_kernel<<<table_blocks + slot_blocks, 256, 0, s>>>(v, table, b, table_blocks);
+    if (v.index) {
+        launch_cell_boxes(m, scratch, s);
+        brick_boxes_kernel<<<(unsigned)((b.cells + 3) / 4), 256, 0, s>>>(v, b);
+    }
     return hipGetLastError();
 }
 
