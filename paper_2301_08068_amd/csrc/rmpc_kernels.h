@@ -57,6 +57,7 @@ constexpr int32_t kFarVoxel = 1 << 24;
 // A sparse map: 8 x 8 x 8-voxel blocks stored where the world has content (every other voxel
 // is free), found through an open-addressed hash table from block coordinates to slots.
 constexpr int kBlockLog2 = 3;
+constexpr int kBlockEdge = 1 << kBlockLog2;
 constexpr int kBlockVoxels = 512;
 // Block coordinates are signed 21-bit integers (|voxel coordinate| < 2^23 voxels).
 constexpr int kBlockCoordBits = 21;
@@ -91,8 +92,8 @@ __host__ __device__ inline uint32_t block_hash(uint64_t k, uint32_t mask)
 }
 
 constexpr uint32_t kBlockOccupied = 1u << 31;
-// A map's index is built, and a query uses it, where no coordinate exceeds this (in float32 terms:
-// 1/60 of a voxel).
+// A map's index is built where no coordinate exceeds this, and a query walks by it where none of the
+// walk's does (in float32 terms: 1/60 of a voxel).
 constexpr int32_t kIndexSpan = 1 << 16;
 struct SparseView {
     const HashEntry *table;      // table_mask + 1 entries (a power of two, at least twice the blocks)
@@ -133,6 +134,8 @@ struct RayArgs {
     int32_t n_rays;
     float g[3];                  // start in grid units, float32((x - origin) / h)
     int32_t v0[3];               // start voxel floor(g)
+    int32_t base[3];             // sparse maps walked by their index far from the origin: the voxel that g, v0 and
+                                 //   sp.lo count from, else 0
     int32_t lin0;                // its logical index
     uint32_t start_flags;        // RMPC_RAY_START_FACE when g is within 1e-5 of a face
     float tmax_lo, tmax_hi;      // float32 guard band around max_range / h

@@ -3,7 +3,7 @@
 // block is free, and the world has no edge) by its block table, shared by the single-query kernel
 // (sparse.hip) and the batch kernel (raycast.hip).  It serves maps without an index (blocks so
 // scattered that an index over the box around them would not fit beside a smaller table) and
-// positions too far from the origin for one; every other query walks by the index (rmpc_dense.h).
+// ranges too long for one; every other query walks by the index (rmpc_dense.h).
 //
 // S adjacent lanes walk the S segments of one ray (as in the dense kernel: segment k starts
 // at the voxel that holds the float64-located boundary near k max_range / S and ends at the

@@ -300,13 +300,13 @@ __device__ __forceinline__ double subvoxel_at(const RayArgs &A, const Value &val
 {
 #pragma clang fp contract(off)
     const double t = d / A.h;
+    const double gx = (double)A.g[0] + A.base[0], gy = (double)A.g[1] + A.base[1], gz = (double)A.g[2] + A.base[2];
     double tk[8], phi[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         const double s = t + 0.5 * (double)k - 1.5;
         tk[k] = s > 0.0 ? s : 0.0;
-        phi[k] = trilinear_field(value, (double)A.g[0] + tk[k] * (double)rx, (double)A.g[1] + tk[k] * (double)ry,
-                                 (double)A.g[2] + tk[k] * (double)rz);
+        phi[k] = trilinear_field(value, gx + tk[k] * (double)rx, gy + tk[k] * (double)ry, gz + tk[k] * (double)rz);
     }
     for (int k = 0; k < 7; ++k)
         if (phi[k] > 0.0 && phi[k + 1] <= 0.0) {

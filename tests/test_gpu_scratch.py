@@ -180,3 +180,34 @@ def test_sparse_scratch_comes_from_the_arena(tiny_map):
         assert all(torch.equal(a, b) for a, b in zip(want, got))
     finally:
         B.rmpc_destroy(ctx)
+
+
+@pytest.mark.parametrize("enc,subvoxel", [("f32", 0), ("f32", 1), ("f16", 1), ("u8", 0)])
+@pytest.mark.parametrize("at", [(8100, 8150, 20), (-8180, -8100, -8150)])
+def test_far_queries_on_indexed_maps(ctx, tiny_map, enc, subvoxel, at):
+    """Beyond 2^16 voxels from the origin a map's index serves as well as its table does (an upload
+    without scratch has no index): bit for bit from starts among the blocks, beside them and out of
+    reach of them, far from the origin and at the end of the allowed range."""
+    sm = W.sparse_from_dense(tiny_map, offset_blocks=at, keep_free=0.3, seed=4, origin_m=(0.0, 0.0, 0.0))
+    data = {"f32": sm.values, "f16": W.encode_f16(sm.values), "u8": W.encode_u8(sm.values)}[enc]
+    far = ctx.upload_sparse(sm.coords, data, sm.voxel_m, sm.origin_m, enc)
+    _limit(ctx, 0)
+    mid = ctx.upload_sparse(sm.coords, data, sm.voxel_m, sm.origin_m, enc)
+    lo = np.asarray(at) * 8.0
+    p = dict(P, max_range=40.0, subvoxel=subvoxel)                      # 400 voxels
+    starts = [lo + g for g in ((17.3, 40.6, 30.2), (50.01, 9.99, 33.5), (-300.4, 20.1, 30.7), (70.2, 90.3, -80.1), (32.0, 32.0, 70.0))]
+    starts += [lo + 30000.7, np.full(3, 8.38e6), -np.full(3, 8.38e6)]
+    hits = 0
+    for g in starts:
+        x = sm.origin_m + g * sm.voxel_m
+        a, b = ctx.trace(far, x, 4096, p), ctx.trace(mid, x, 4096, p)
+        for k in ("hit", "d", "visits"):
+            assert np.array_equal(a[k], b[k]), (g, k)
+        assert np.array_equal(a["flags"] & 0xfe, b["flags"] & 0xfe), g
+        hits += int((a["hit"] >= 0).sum())
+        v = np.array([1.0, -0.5, 0.3])
+        _same_query(ctx.query(far, x, v, 3000, p), ctx.query(mid, x, v, 3000, p))
+        if not subvoxel:
+            q = [dict(kind="map", map_id=m, n=700, x=x, v=v) for m in (far, mid)]
+            _same_query(*ctx.query_batch(q, p, None))
+    assert hits > 4096
