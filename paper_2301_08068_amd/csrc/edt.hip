@@ -157,6 +157,7 @@ __global__ void __launch_bounds__(256) edt_rows_kernel(MapView m, int group_log2
 // it needs none of those.  A result that reaches it (no occupied voxel within 255 voxels) raises
 // flag[0], and the wide passes below do the transform again; a last strip without a value below kCap
 // gets -1, which is its result if all strips are such (flag[1]: one was, flag[2]: one was not).
+// Where the grid is too small for any of that, flag is null.
 // ------------------------------------------------------------------------------------------
 constexpr int32_t kCap = 65535;
 constexpr int kPad = 3;
@@ -221,8 +222,8 @@ __device__ __forceinline__ bool load_strip(Quad *lds, const int32_t *g, const Ro
 
 template <bool WORDS, int CLOG>
 __global__ void __launch_bounds__(256) edt_strip_kernel(int32_t *g, const RowWord *words, int32_t len, int64_t stride,
-                                                        int32_t nx, int32_t strips, int64_t outer, uint32_t *flag,
-                                                        uint32_t *flag_host)
+                                                        int32_t nx, int32_t strips, int64_t outer, int last_pass,
+                                                        uint32_t *flag, uint32_t *flag_host)
 {
     extern __shared__ Quad strip_mem[];                   // [len + 2 kPad][lines / 4]
     Quad *strip = strip_mem;
@@ -279,7 +280,7 @@ __global__ void __launch_bounds__(256) edt_strip_kernel(int32_t *g, const RowWor
             }
         }
         int32_t v[4] = {best.a.x, best.a.y, best.b.x, best.b.y};
-        if (flag && !any) v[0] = v[1] = v[2] = v[3] = -1;
+        if (last_pass && !any) v[0] = v[1] = v[2] = v[3] = -1;
         int32_t *p = g + base + c + i * stride;
         if (left >= 4) {
             *reinterpret_cast<Int4At4 *>(p) = Int4{v[0], v[1], v[2], v[3]};
@@ -503,14 +504,14 @@ inline int strip_clog(int len) { return len <= 208 ? 5 : len <= 832 ? 4 : len <=
 
 template <bool WORDS>
 hipError_t launch_strips(int32_t *g, const RowWord *words, int32_t len, int64_t stride, int32_t nx, int64_t others,
-                         int64_t outer, uint32_t *flag, uint32_t *flag_host, hipStream_t s)
+                         int64_t outer, int last_pass, uint32_t *flag, uint32_t *flag_host, hipStream_t s)
 {
     const int clog = strip_clog(len);
     const int32_t strips = (nx + (1 << clog) - 1) >> clog;
     const auto kernel = clog == 5 ? edt_strip_kernel<WORDS, 5>
                       : clog == 4 ? edt_strip_kernel<WORDS, 4> : clog == 3 ? edt_strip_kernel<WORDS, 3> : edt_strip_kernel<WORDS, 2>;
     kernel<<<(unsigned)(others * strips), 256, (size_t)(len + 2 * kPad) * 2 << clog, s>>>(g, words, len, stride, nx, strips, outer,
-                                                                            flag, flag_host);
+                                                                            last_pass, flag, flag_host);
     return hipGetLastError();
 }
 
@@ -639,10 +640,15 @@ hipError_t launch_edt(const MapView &m, int32_t *out, void *scratch, size_t scra
     const int64_t plane = (int64_t)m.nx * m.ny;
     if (hipError_t e = launch_rows(m, words, out, flag, s)) return e;
     // y: lines (x, z), elements nx apart; z: lines (x, y), elements nx ny apart
-    const hipError_t e = words ? launch_strips<true>(out, words, m.ny, m.nx, m.nx, m.nz, plane, nullptr, nullptr, s)
-                               : launch_strips<false>(out, nullptr, m.ny, m.nx, m.nx, m.nz, plane, nullptr, nullptr, s);
+    const hipError_t e = words ? launch_strips<true>(out, words, m.ny, m.nx, m.nx, m.nz, plane, 0, nullptr, nullptr, s)
+                               : launch_strips<false>(out, nullptr, m.ny, m.nx, m.nx, m.nz, plane, 0, nullptr, nullptr, s);
     if (e != hipSuccess) return e;
-    return launch_strips<false>(out, nullptr, m.nz, plane, m.nx, m.ny, m.nx, flag, flag_host, s);
+    // no distance in a grid of this diagonal reaches kCap, and one occupied voxel leaves a value below it
+    // in every strip of the last pass: no need to watch for either (16^3 25.9 -> 25.6 us, 25.4
+    // with the passes before; 96^3 46.5 -> 39.7)
+    const int64_t dx = m.nx - 1, dy = m.ny - 1, dz = m.nz - 1;
+    const bool near = dx * dx + dy * dy + dz * dz < kCap;
+    return launch_strips<false>(out, nullptr, m.nz, plane, m.nx, m.ny, m.nx, 1, near ? nullptr : flag, flag_host, s);
 }
 
 hipError_t launch_edt_wide(const MapView &m, int32_t *out, hipStream_t s)

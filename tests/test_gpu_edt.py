@@ -207,3 +207,17 @@ def test_given_up_while_other_blocks_run(ctx, shape, at):
         assert torch.equal(ctx.edt(mid, shape), want)
     finally:
         ctx.release(mid)
+
+
+# (diagonals around the narrow limit, 255^2 + 255^2 ... : 65,534, 65,536 and beyond) no occupied voxel,
+# one in a corner, all
+@pytest.mark.parametrize("shape", [(1, 1, 1), (2, 3, 5), (8, 8, 8), (64, 64, 64), (2, 1, 256), (148, 149, 149), (149, 149, 149),
+                                   (16, 8, 256), (1, 1, 257)])
+def test_small_grids_without_a_watch(ctx, shape):
+    for fill in (0, 1, 2):
+        occ = np.full(shape, fill == 2, np.uint8)
+        occ.reshape(-1)[-1] |= fill == 1
+        z, y, x = (np.arange(n - 1, -1, -1) ** 2 for n in shape)
+        one = z[:, None, None] + y[None, :, None] + x[None, None, :]
+        want = {0: np.full(shape, -1), 1: one, 2: np.zeros(shape)}[fill]
+        assert np.array_equal(_gpu_edt(ctx, occ, 0.1, "u8"), want), fill
