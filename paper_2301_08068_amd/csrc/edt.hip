@@ -496,10 +496,17 @@ hipError_t launch_lines(int32_t *g, int32_t len, int64_t stride, int32_t nx, int
     return hipGetLastError();
 }
 
-// log2 of a strip's lines.  The search is bound by LDS latency, so at most 13 KiB (26 KiB above 832
-// elements), which leaves a CU to its full number of waves: at 400 elements strips of 8, 16, 32 and
-// 64 lines took 582, 511, 557 and 779 us; below, 32 lines (64-byte rows in LDS, 128-byte ones in
-// memory) were as good or better than 16 (96^3, one in ten occupied: 34 us against 37).
+// log2 of a strip's lines.  Wider strips read and write longer rows of memory, above all in the z pass;
+// narrower ones take less LDS (2 bytes per line and element: 13 KiB at 208 elements, 26 at 832, 63 at
+// 4,000, where two blocks share a CU), which leaves a CU more waves for a search that waits for LDS.
+// Transforms of 150 lines of planes with y (z) lines of n elements, one voxel in 1,000 occupied, by strips
+// of 8, 16 and 32 lines, us:
+//   400    154 (207)  153 (162)  176 (153)      2,000  174 (212), 16 lines 232 (211)
+//   832    143 (187)  155 (152)  202 (163)      3,500  251 (290),  4 lines 224 (367)
+//   1,300  188 (246)  221 (202)  221 (204; 32 lines do not fit)
+// so 16 lines up to 832, 8 beyond (to 1,300 about as good for both axes together), and 4 where 8 do not
+// fit 64 KiB; up to 208 elements 32 lines were as good or better than 16 (96^3, one in ten occupied:
+// 34 us against 37).
 inline int strip_clog(int len) { return len <= 208 ? 5 : len <= 832 ? 4 : len <= 4000 ? 3 : 2; }
 
 template <bool WORDS>
