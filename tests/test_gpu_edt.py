@@ -221,3 +221,34 @@ def test_small_grids_without_a_watch(ctx, shape):
         one = z[:, None, None] + y[None, :, None] + x[None, None, :]
         want = {0: np.full(shape, -1), 1: one, 2: np.zeros(shape)}[fill]
         assert np.array_equal(_gpu_edt(ctx, occ, 0.1, "u8"), want), fill
+
+
+@pytest.mark.parametrize("enc", ["f32", "u8"])
+@pytest.mark.parametrize("shape,p", [((64, 65, 33), 0.003), ((129, 66, 31), 0.002), ((2, 257, 65), 0.002), ((300, 3, 40), 0.2),
+                                     ((3, 2, 257), 0.0), ((182, 182, 2), 0.0)])
+def test_room_for_the_flags_alone(shape, p, enc):
+    """An arena with 256 bytes left: the narrow passes with the row distances through the field (and
+    the wide ones after them where a distance reaches 256)."""
+    from paper_2301_08068_amd import binding
+    rng = np.random.default_rng(sum(shape))
+    occ = rng.uniform(size=shape) < p
+    occ[-1, -1, -1] = True
+    t = np.where(occ, -0.05, 0.3).astype(np.float32)
+    data = t if enc == "f32" else W.encode_u8(t)
+    c = binding.Context(0, arena_bytes=24 << 20)
+    try:
+        mid = c.upload(data, 0.1, np.zeros(3), enc)
+        assert binding.rmpc_map_footprint(256, 1, 1, "u8", 0.1, (0, 0, 0)) == 256
+        held = c.upload(np.zeros((1, 1, 256), np.uint8), 0.1, np.zeros(3), "u8")
+        for dims in ((4096, 1, 256), (256, 1, 256), (16, 1, 256), (1, 1, 256)):
+            while True:
+                try:
+                    c.upload(np.zeros(dims, np.uint8), 0.1, np.zeros(3), "u8")
+                except binding.RmpcError as e:
+                    assert e.status == binding.RMPC_E_NOMEM
+                    break
+        c.release(held)
+        g = c.edt(mid, shape).cpu().numpy()
+    finally:
+        c.close()
+    assert np.array_equal(g, oracle.edt(oracle.OracleMap(data, 0.1, np.zeros(3), enc)))
