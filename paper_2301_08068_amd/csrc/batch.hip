@@ -404,6 +404,8 @@ rmpc_status rmpc_tune_batch(rmpc_ctx *ctx, const rmpc_query_desc *q, int32_t n,
             }
         cache_store(cache_path, key, chosen);
     }
+    // (a cached entry holds the lookahead of when it was stored)
+    chosen.lookahead = ctx->cfg[RMPC_CONFIG_BATCH].lookahead;
     chosen.use_graph = ctx->cfg[RMPC_CONFIG_BATCH].use_graph;
     ctx->cfg[RMPC_CONFIG_BATCH] = chosen;
     if (best) *best = chosen;

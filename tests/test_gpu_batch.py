@@ -203,3 +203,22 @@ def test_every_tile_finds_its_query(env, tiny_map, n):
     for k, (g, key) in enumerate(zip(got, kinds)):
         for f in ("S", "b", "f", "n_hit", "visits"):
             assert np.array_equal(g[f], want[key][f]), (k, key, f)
+
+
+def test_tuner_keeps_the_lookahead_as_set(env, tiny_map, tmp_path):
+    """Timed or taken from the cache, a tuned configuration has the lookahead that was set, whatever
+    it was when the entry was stored."""
+    from paper_2301_08068_amd import binding as B
+    ctx, maps = env
+    before = B.rmpc_config_get(ctx.ptr, B.CONFIG_BATCH)
+    x, v = W.free_state(tiny_map, 5)
+    descs = B.query_descs([dict(kind="map", map_id=maps["tiny"], n=500, x=x, v=v)] * 3)
+    path = str(tmp_path / "tune.json")
+    try:
+        for la in (16, 4, 8):
+            B.rmpc_config_set(ctx.ptr, B.CONFIG_BATCH, la, 14, 0, 0)
+            got = B.rmpc_tune_batch(ctx.ptr, descs, P_TINY, None, cache_path=path)
+            assert got["lookahead"] == la and B.rmpc_config_get(ctx.ptr, B.CONFIG_BATCH) == got
+        assert len(json.load(open(path))) == 1
+    finally:
+        B.rmpc_config_set(ctx.ptr, B.CONFIG_BATCH, *(before[k] for k in ("lookahead", "lane_target_log2", "blocks_per_cu", "use_graph")))
