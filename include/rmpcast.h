@@ -331,8 +331,9 @@ rmpc_status rmpc_config_get(rmpc_ctx *ctx, int32_t which, rmpc_launch_config *cf
  * (segmentation target, resident blocks) and keep the fastest as the context's
  * RMPC_CONFIG_BATCH (lookahead and use_graph are kept as set).
  *   cache_path: optional JSON file; a configuration cached there under this GPU's
- *     architecture, the batch's storage types and its mean ray count bucket is used without
- *     timing, and a newly timed one is added.  NULL: no file.
+ *     architecture and batch kernel, the batch's storage types (dense or with sparse maps) and its
+ *     mean ray count bucket is used without timing, and a newly timed one is added (entries of
+ *     other kernels stay unused).  NULL: no file.
  *   best: optional, receives the chosen configuration.
  * Runs the batch several times.  Errors: as rmpc_query_batch.
  */

@@ -275,7 +275,10 @@ rmpc_status run_batch(rmpc_ctx *ctx, const rmpc_query_desc *q, int32_t n, const 
     return RMPC_OK;
 }
 
-// Cache key of a tuned configuration: architecture, storage types present, ray-count bucket.
+// Cache key of a tuned configuration: architecture, the batch kernel it was timed with (raised when
+// what is fastest changes: 2, walks by free boxes), storage types of dense and sparse maps present,
+// ray-count bucket.
+constexpr const char *kTuneKernel = "|k2|";
 std::string tune_key(rmpc_ctx *ctx, const rmpc_query_desc *q, int32_t n)
 {
     hipDeviceProp_t prop;
@@ -283,19 +286,22 @@ std::string tune_key(rmpc_ctx *ctx, const rmpc_query_desc *q, int32_t n)
     if (hipGetDeviceProperties(&prop, ctx->device) == hipSuccess) arch = prop.gcnArchName;
     arch = arch.substr(0, arch.find(':'));
     bool dt[3] = {false, false, false};
-    bool scan = false;
+    bool scan = false, sparse = false;
     double mean = 0.0;
     for (int k = 0; k < n; ++k) {
         if (q[k].kind == RMPC_KIND_SCAN) { scan = true; continue; }
         auto it = ctx->maps.find(q[k].map_id);
-        if (it != ctx->maps.end()) dt[it->second.desc.dtype] = true;
+        if (it != ctx->maps.end()) {
+            dt[it->second.desc.dtype] = true;
+            sparse = sparse || it->second.sparse;
+        }
         mean += q[k].n;
     }
     mean /= std::max(1, n);
     int bucket = 0;
     while ((1 << (bucket + 1)) <= mean) ++bucket;
-    return arch + "|" + (dt[0] ? "f32" : "") + (dt[1] ? "f16" : "") + (dt[2] ? "u8" : "") +
-           (scan ? "+scan" : "") + "|n2^" + std::to_string(bucket) + "|q" + std::to_string(n >= 64 ? 64 : n);
+    return arch + kTuneKernel + (dt[0] ? "f32" : "") + (dt[1] ? "f16" : "") + (dt[2] ? "u8" : "") +
+           (sparse ? "+sparse" : "") + (scan ? "+scan" : "") + "|n2^" + std::to_string(bucket) + "|q" + std::to_string(n >= 64 ? 64 : n);
 }
 
 // Tiny JSON cache: one object of "key": [lookahead, lane_target_log2, blocks_per_cu].

@@ -222,3 +222,30 @@ def test_tuner_keeps_the_lookahead_as_set(env, tiny_map, tmp_path):
         assert len(json.load(open(path))) == 1
     finally:
         B.rmpc_config_set(ctx.ptr, B.CONFIG_BATCH, *(before[k] for k in ("lookahead", "lane_target_log2", "blocks_per_cu", "use_graph")))
+
+
+def test_tuner_keys_kernels_and_sparse_maps_apart(env, tiny_map, tmp_path):
+    """A configuration timed for a dense batch is not taken for a sparse one of the same size, nor one
+    that was stored for the batch kernel before."""
+    from paper_2301_08068_amd import binding as B
+    ctx, maps = env
+    before = B.rmpc_config_get(ctx.ptr, B.CONFIG_BATCH)
+    sm = W.sparse_from_dense(tiny_map)
+    mid = ctx.upload_sparse(sm.coords, sm.values, sm.voxel_m, sm.origin_m, "f32")
+    x, v = W.free_state(tiny_map, 5)
+    path = str(tmp_path / "tune.json")
+    try:
+        keys = []
+        for m in (maps["tiny"], mid):
+            B.rmpc_tune_batch(ctx.ptr, B.query_descs([dict(kind="map", map_id=m, n=500, x=x, v=v)] * 3), P_TINY, None, cache_path=path)
+            keys.append(list(json.load(open(path))))
+        assert len(keys[1]) == 2 and sum("sparse" in k for k in keys[1]) == 1
+        old = keys[0][0].split("|")
+        stale = "|".join([old[0]] + old[2:])                    # the key without the kernel's mark
+        json.dump({stale: [8, 22, 0]}, open(path, "w"))
+        got = B.rmpc_tune_batch(ctx.ptr, B.query_descs([dict(kind="map", map_id=maps["tiny"], n=500, x=x, v=v)] * 3), P_TINY, None,
+                                cache_path=path)
+        assert got["lane_target_log2"] != 22 and set(json.load(open(path))) == {stale, keys[0][0]}
+    finally:
+        ctx.release(mid)
+        B.rmpc_config_set(ctx.ptr, B.CONFIG_BATCH, *(before[k] for k in ("lookahead", "lane_target_log2", "blocks_per_cu", "use_graph")))
