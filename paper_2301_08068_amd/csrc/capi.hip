@@ -78,6 +78,8 @@ rmpc::PolicyF policy_f(const rmpc_params *p, const double v[3])
     P.radius = (float)p->radius;
     P.inv_radius = (float)(1.0 / p->radius);
     P.eps = (float)p->eps;
+    P.tame = P.c >= 1e-30f && P.c <= 1e38f && P.eta_rep <= 1e30f && std::isfinite(P.inv_nu_rep) &&
+             std::isfinite(P.inv_radius);
     return P;
 }
 

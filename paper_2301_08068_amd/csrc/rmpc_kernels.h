@@ -115,6 +115,9 @@ struct SparseView {
 struct PolicyF {
     float vx, vy, vz;            // robot velocity
     float c, eta_rep, inv_nu_rep, eta_damp, inv_nu_damp, radius, inv_radius, eps;
+    // non-zero: none of them makes a ray's terms NaN whose damping is zero or that hits beyond the
+    // radius (quotients 0 / 0, products 0 inf of a parameter that is zero, huge or infinite in float32)
+    int32_t tame;
 };
 
 // One entry of an ordered ray list: the float32 direction of Halton ray i and i itself, so

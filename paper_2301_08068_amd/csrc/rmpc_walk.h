@@ -189,15 +189,14 @@ __device__ __forceinline__ float4 load_ray(const RayRec *rays, int j)
 //   a = w_r(d) sigma^2,  phi = eta_rep exp(-d/nu_rep) + q,  w_r(d) = (1 - d/r)^2 on [0, r].
 // Returns false when every term is zero: a ray along or away from which the robot does not move
 // (half of all, and of whole waves: neighbouring lanes hold neighbouring directions), or a hit
-// beyond the radius.  Nothing but zeros is left out: parameters and quotients that would make a
-// term NaN are computed.
+// beyond the radius.  Nothing but zeros is left out: parameters (P.tame), distances and quotients that
+// would make a term NaN are computed.
 __device__ __forceinline__ bool policy_terms(const PolicyF &P, float rx, float ry, float rz, float d, float (&x)[9])
 {
     const float vr = P.vx * rx + P.vy * ry + P.vz * rz;
     const float pp = vr > 0.0f ? vr * vr : 0.0f;
     const float q = P.eta_damp * pp / (d * P.inv_nu_damp + P.eps);
-    const bool tame = P.c >= 1e-30f && P.eta_rep <= 1e30f;      // no quotient 0 / 0, no product 0 inf below
-    if (tame && (q == 0.0f || (d > P.radius && q < 1e30f))) return false;
+    if (P.tame != 0 && d < kInf && (q == 0.0f || (d > P.radius && q < 1e30f))) return false;
     const float rn2 = rx * rx + ry * ry + rz * rz;
     const float mq = q * sqrtf(rn2);
     const float sigma = q / (mq + P.c * log1pf(expf(-2.0f * P.c * mq)));
