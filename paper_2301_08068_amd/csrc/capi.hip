@@ -310,7 +310,7 @@ rmpc_status setup_query(rmpc_ctx *ctx, int32_t map_id, const double x[3], int32_
 // errors only once the wait has lasted kStreamCheck, and then once per kStreamCheck (measured:
 // with a stream query every 1,024 spins a query whose kernel takes 20 us returned after 40 us;
 // with none in its first millisecond, after 25 us).
-rmpc_status wait_done(const uint64_t *done, hipStream_t s, uint64_t seq)
+rmpc_status wait_done(const uint64_t *done, hipStream_t s, uint64_t seq, std::chrono::seconds limit)
 {
     using Clock = std::chrono::steady_clock;
     const auto t0 = Clock::now();
@@ -319,8 +319,8 @@ rmpc_status wait_done(const uint64_t *done, hipStream_t s, uint64_t seq)
         if (__atomic_load_n(done, __ATOMIC_ACQUIRE) == seq) return RMPC_OK;
         if ((it & 255) == 0 && Clock::now() >= next_check) {
             next_check = Clock::now() + kStreamCheck;
-            if (Clock::now() - t0 > std::chrono::seconds(60))
-                return fail(RMPC_E_HIP, "query kernel did not finish within 60 s");
+            if (Clock::now() - t0 > limit)
+                return fail(RMPC_E_HIP, "query kernel did not finish within " + std::to_string(limit.count()) + " s");
             const hipError_t e = hipStreamQuery(s);
             if (e == hipSuccess) {
                 if (__atomic_load_n(done, __ATOMIC_ACQUIRE) == seq) return RMPC_OK;
@@ -1005,7 +1005,8 @@ rmpc_status rmpc_esdf_query(rmpc_ctx *ctx, int32_t map_id, const int32_t *sqdist
     A.done = ctx->done_host;
     A.seq = ++ctx->seq;
     RMPC_HIP(rmpc::launch_esdf(A, s));
-    if (rmpc_status st = wait_done(ctx->done_host, s, A.seq)) return st;
+    // (a lookup waits for the stream, whatever stands before it there)
+    if (rmpc_status st = wait_done(ctx->done_host, s, A.seq, kNoLimit)) return st;
     std::memcpy(out, ctx->result_host, sizeof(rmpc_result));
     return RMPC_OK;
 }

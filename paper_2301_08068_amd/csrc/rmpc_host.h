@@ -136,9 +136,11 @@ constexpr int32_t kMaxScanPoints = 1 << 24;
 rmpc_status setup_scan(const float *points_dev, int32_t n_points, const double v[3], const rmpc_params *params,
                        rmpc::ScanArgs &A);
 // Spin until *done == seq (the kernel's publication), checking the stream for errors once the
-// wait has lasted kStreamCheck, and once per kStreamCheck after that.
+// wait has lasted kStreamCheck, and once per kStreamCheck after that.  Fails once it has lasted `limit`
+// (the queries' own; a call that may stand behind any amount of the caller's work has none).
 constexpr std::chrono::microseconds kStreamCheck(1000);
-rmpc_status wait_done(const uint64_t *done, hipStream_t s, uint64_t seq);
+constexpr std::chrono::hours kNoLimit(24 * 365);
+rmpc_status wait_done(const uint64_t *done, hipStream_t s, uint64_t seq, std::chrono::seconds limit = std::chrono::seconds(60));
 
 // Launch slots of the batch kernel.
 rmpc_status slot_create(rmpc_ctx *ctx, LaunchSlot &slot, int max_queries, int max_tiles);
