@@ -387,7 +387,9 @@ __device__ __forceinline__ BoxEnd box_end(const RayArgs &A, const BoxRay &R, con
 __device__ __forceinline__ bool box_range_tie(const RayArgs &A, const BoxRay &R, double t64, int a)
 {
     const MapView &m = A.map;
-    const float t = 0.5f * (A.tmax_lo + A.tmax_hi), tol = box_tol(m, t);
+    const float t = 0.5f * (A.tmax_lo + A.tmax_hi);
+    // a crossing that far from max_range leaves its face up to 1e-5 from the ray's point there
+    const float tol = box_tol(m, t) + 1.1e-5f;
     const int n[3] = {m.nx, m.ny, m.nz};
     const float gs[3] = {R.gsx, R.gsy, R.gsz}, r[3] = {R.rx, R.ry, R.rz};
     bool tie = false;

@@ -141,3 +141,25 @@ def test_long_lines(lib, shape):
     dirs = np.concatenate([dirs / np.linalg.norm(dirs, axis=1, keepdims=True), oracle.directions(200)])
     for k in range(6):
         _check(lib, occ, _free(rng, occ, k % 3 == 0), [5000.0, 777.0, 2600.5][k % 3], dirs)
+
+
+@pytest.mark.parametrize("off", [0.0, 2e-6, 8e-6, 9.9e-6, 1.1e-5, 1.9e-5, 3e-5])
+@pytest.mark.parametrize("shape,faces", [((9, 12, 10), 1), ((9, 12, 10), 5), ((33, 70, 35), 2), ((33, 70, 35), 30)])
+def test_range_near_ties(lib, shape, faces, off):
+    """Ranges that end just before and behind faces that rays along and across the axes reach, in grids
+    where the walk knows a float32 position better than to 1e-5 voxel and where it does not: the
+    decision, and the flag of a crossing within 1e-5 voxel of the range."""
+    rng = np.random.default_rng(faces)
+    d = np.array([[i, j, k] for i in (-1, 0, 1) for j in (-1, 0, 1) for k in (-1, 0, 1) if i or j or k], np.float64)
+    dirs = np.concatenate([d / np.linalg.norm(d, axis=1, keepdims=True),
+                           rng.uniform(-1.0, 1.0, (200, 3)) * [0.2, 1.0, 0.2]])
+    dirs[26:] /= np.linalg.norm(dirs[26:], axis=1, keepdims=True)
+    slant = np.abs(dirs[26:].astype(np.float32)[:, 1]).astype(np.float64)
+    for density in (0.0, 0.02):
+        occ = rng.uniform(size=shape) < density
+        mid = [n // 2 for n in shape]
+        occ[tuple(slice(k - 1, k + 2) for k in mid)] = False
+        g = np.array([mid[2], mid[1] + 0.5, mid[0] + 0.5])
+        for sign in (-1.0, 1.0):
+            for reach in [float(faces), faces - 0.5] + list((faces - 0.5) / slant[:3]):
+                _check(lib, occ, g, reach + sign * off, dirs, segments=(1, 4))
