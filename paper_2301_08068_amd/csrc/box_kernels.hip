@@ -96,6 +96,9 @@ Scratch scratch_at(const MapView &m, uint8_t *p)
     return s;
 }
 
+// (what the extents below reach, and twice it fits five bits)
+static_assert(13 <= kBoxMax && 2 * kBoxMax < 32, "half extents of box entries");
+
 __device__ __forceinline__ uint16_t unit_entry(uint32_t mask)
 {
     return (uint16_t)(mask ? kBoxOccupied | kBoxNoLayer | mask : kUnitBox);

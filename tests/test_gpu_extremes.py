@@ -46,7 +46,7 @@ def _sums(p, v, r, d):
         bb = -a * rn2 * phi
         t = [a * r[:, i] * r[:, j] for i in range(3) for j in range(i, 3)] + [bb * r[:, i] for i in range(3)]
         t = np.stack(t).astype(np.float64)
-    return np.where(np.isfinite(t).all(axis=1), t.sum(axis=1), np.nan)
+        return np.where(np.isfinite(t).all(axis=1), t.sum(axis=1), np.nan)
 
 
 def _check(g, want):
